@@ -71,6 +71,7 @@ static void free_device(rambo_s *h) {
     if (h->d_hp) (void)hipFree(h->d_hp);
     if (h->d_cells) (void)hipFree(h->d_cells);
     if (h->d_cells0) (void)hipFree(h->d_cells0);
+    if (h->d_docslot) (void)hipFree(h->d_docslot);
     if (h->d_ids_counts) (void)hipFree(h->d_ids_counts);
     if (h->d_ids_wm) (void)hipFree(h->d_ids_wm);
     if (h->d_ids_aux) (void)hipFree(h->d_ids_aux);
@@ -126,6 +127,17 @@ static int upload_tables(rambo_s *h) {
         memcpy(&cells0[k * 8], &cells[(size_t)bdoc[k] * 8], 16);
     HIP_CHECK(hipMalloc(&h->d_cells0, cells0.size() * 2));
     HIP_CHECK(hipMemcpy(h->d_cells0, cells0.data(), cells0.size() * 2, hipMemcpyHostToDevice));
+    // and by repetition, in the order the group resolve of term queries reads
+    // them: 512 documents a record row, as slots of its LDS array
+    const uint64_t chunks = (h->W + 7) / 8;
+    std::vector<uint16_t> docslot((size_t)h->R * chunks * 512, 0);
+    for (uint32_t r = 0; r < h->R; r++)
+        for (uint64_t d = 0; d < h->K; d++) {
+            const uint32_t c = h->phi[(size_t)r * h->K + d];
+            docslot[((r * chunks + d / 512) * 64 + d % 64) * 8 + (d / 64) % 8] = (uint16_t)(c + c / 64);
+        }
+    HIP_CHECK(hipMalloc(&h->d_docslot, docslot.size() * 2));
+    HIP_CHECK(hipMemcpy(h->d_docslot, docslot.data(), docslot.size() * 2, hipMemcpyHostToDevice));
     if (!h->gids.empty() && !h->d_gids) {
         HIP_CHECK(hipMalloc(&h->d_gids, h->gids.size() * 8));
         HIP_CHECK(hipMemcpy(h->d_gids, h->gids.data(), h->gids.size() * 8, hipMemcpyHostToDevice));
@@ -175,12 +187,15 @@ rambo_s *rambo::create_index(uint64_t K, uint32_t B, uint32_t R, uint64_t m, uin
     h->tune.seg = default_seg(rw);
     h->W = (K + 63) / 64;
     h->rows_bytes = (uint64_t)R * m * rw * 4;
+    int lds = 0;
     if (hipGetDevice(&h->device) != hipSuccess ||
-        hipDeviceGetAttribute(&h->n_cu, hipDeviceAttributeMultiprocessorCount, h->device) != hipSuccess) {
+        hipDeviceGetAttribute(&h->n_cu, hipDeviceAttributeMultiprocessorCount, h->device) != hipSuccess ||
+        hipDeviceGetAttribute(&lds, hipDeviceAttributeMaxSharedMemoryPerBlock, h->device) != hipSuccess) {
         fail(RAMBO_EDEVICE, "rambo_create: no usable HIP device");
         delete h;
         return nullptr;
     }
+    h->lds_max = (uint32_t)lds;
     derive_hashes(h);
     if (hipMalloc(&h->rows, h->rows_bytes) != hipSuccess) {
         (void)hipGetLastError();
@@ -304,10 +319,11 @@ RAMBO_API int rambo_fold(rambo_t *h) {
     (void)hipFree(h->d_hp);
     (void)hipFree(h->d_cells);
     (void)hipFree(h->d_cells0);
+    (void)hipFree(h->d_docslot);
     (void)hipFree(h->d_boff);
     (void)hipFree(h->d_bdoc);
     h->d_hp = nullptr;
-    h->d_cells = h->d_cells0 = nullptr;
+    h->d_cells = h->d_cells0 = h->d_docslot = nullptr;
     h->d_boff = h->d_bdoc = nullptr;
     st = upload_tables(h);
     std::lock_guard<std::mutex> g(h->mu);

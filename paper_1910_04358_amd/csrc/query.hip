@@ -1,5 +1,5 @@
-// Plain one-batch query kernels (Algorithm 2; Section 3.3.1 for sequences)
-// and the bitset -> id-list compaction.
+// Plain one-batch sequence queries (Algorithm 2, Section 3.3.1) and the
+// bitset -> id-list compaction.
 //
 // Per term: R * eta row reads (one per Bloom hash and repetition), ANDed
 // over j into the B-bit mask M_r of positive BFUs of repetition r. A
@@ -11,151 +11,6 @@
 
 namespace rambo {
 
-
-// -------------------------------------------------------------------------
-// single k-mer queries: 64 / G terms per wave, then one resolve per term
-// -------------------------------------------------------------------------
-template <int SEG, int G>
-__global__ __launch_bounds__(256) void k_query_kmers(Index ix, const uint64_t *__restrict__ kmers, uint64_t n,
-                                                     uint64_t *__restrict__ out, unsigned long long *invalid,
-                                                     int rmode, int use_res) {
-    constexpr int KPW = 64 / G;
-    extern __shared__ uint64_t smem64[];
-    const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const uint32_t mwords = ((KPW * ix.R * ix.RW) + 1) & ~1u;
-    const uint32_t per_wave = mwords + (use_res ? 2 * ix.W : 0);
-    uint32_t *M = reinterpret_cast<uint32_t *>(smem64) + wave * per_wave;
-    uint64_t *res = use_res ? reinterpret_cast<uint64_t *>(M + mwords) : nullptr;
-
-    const uint64_t base = ((uint64_t)blockIdx.x * (blockDim.x >> 6) + wave) * KPW;
-    if (base >= n) return;
-    const uint32_t g = lane / G, seg = lane % G;
-    const uint64_t q = base + g;
-
-    Seg<SEG> acc[MAXR];
-    set_ones(acc);
-    if (q < n) {
-        const uint64_t x = kmers[q];
-        if (!ix.opaque && (x >> 62)) {
-            if (seg == 0) atomicAdd(invalid, 1ULL);
-#pragma unroll
-            for (int r = 0; r < MAXR; r++)
-#pragma unroll
-                for (int s = 0; s < SEG; s++) acc[r].w[s] = 0;
-        } else {
-            probe_and<SEG>(ix, ix.opaque ? x : canonical(x), seg, acc);
-        }
-    }
-    // stage every term's masks; alive = no repetition mask is empty
-    uint64_t alive = ~0ULL;
-    const uint64_t gm = (G >= 64) ? ~0ULL : ((1ULL << G) - 1);
-#pragma unroll
-    for (int r = 0; r < MAXR; r++) {
-        if (r < (int)ix.R) {
-            uint32_t o = 0;
-#pragma unroll
-            for (int s = 0; s < SEG; s++) {
-                M[(g * ix.R + r) * ix.RW + seg * SEG + s] = acc[r].w[s];
-                o |= acc[r].w[s];
-            }
-            const uint64_t bal = __ballot(o != 0);
-            uint64_t a = 0;
-#pragma unroll
-            for (int t = 0; t < KPW; t++) a |= (uint64_t)(((bal >> (t * G)) & gm) != 0) << t;
-            alive &= a;
-        }
-    }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    const bool dense = rmode == RAMBO_RESOLVE_DENSE || res == nullptr || (rmode == RAMBO_RESOLVE_AUTO && ix.W <= 64);
-    if (!dense) {
-        for (int t = 0; t < KPW; t++) {
-            const uint64_t row = base + t;
-            if (row >= n) break;
-            uint64_t *o = out + row * ix.W;
-            if (!((alive >> t) & 1)) write_zeros(o, ix.W, lane);
-            else resolve(ix, M + t * ix.R * ix.RW, res, o, lane, rmode);
-        }
-        return;
-    }
-    uint64_t live = alive;
-    if (KPW < 64) live &= (1ULL << KPW) - 1;
-    if (n - base < (uint64_t)KPW) live &= (1ULL << (n - base)) - 1;
-    for (int t = 0; t < KPW; t++) {
-        const uint64_t row = base + t;
-        if (row >= n) break;
-        if (!((live >> t) & 1)) write_zeros(out + row * ix.W, ix.W, lane);
-    }
-    if (!live) return;
-    if constexpr (G == 1) {
-        // One lane per term (B <= 128): transposed dense resolve. T[r][c] is
-        // the 64-bit set of the wave's live terms whose repetition-r mask has
-        // cell c; a document's terms are the AND over r of T[r][phi_r(d)],
-        // and a 64 x 64 bit transpose turns the documents' term sets into
-        // the terms' result words.
-        uint64_t *T = reinterpret_cast<uint64_t *>(M);  // R * B words, fits the staging area
-        const bool me_live = (live >> lane) & 1;
-#pragma unroll
-        for (int r = 0; r < MAXR; r++) {
-            if (r < (int)ix.R) {
-                uint64_t t0 = 0, t1 = 0;  // cells lane and 64 + lane
-#pragma unroll
-                for (int wi = 0; wi < SEG; wi++) {
-                    for (uint32_t k = 0; k < 32; k++) {
-                        const uint32_t c = (uint32_t)wi * 32 + k;
-                        if (c >= ix.B) break;
-                        const uint64_t tset = __ballot(me_live && ((acc[r].w[wi] >> k) & 1u));
-                        if ((c & 63) == lane) {
-                            if (c < 64) t0 = tset;
-                            else t1 = tset;
-                        }
-                    }
-                }
-                if (lane < ix.B) T[r * ix.B + lane] = t0;
-                if (64 + lane < ix.B) T[r * ix.B + 64 + lane] = t1;
-            }
-        }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        for (uint32_t w = 0; w < ix.W; w++) {
-            const uint64_t d = (uint64_t)w * 64 + lane;
-            uint64_t tm = 0;
-            if (d < ix.K) {
-                const uint4 cd = ix.cells[d];
-                tm = ~0ULL;
-#pragma unroll
-                for (int r = 0; r < MAXR; r++)
-                    if (r < (int)ix.R) tm &= T[r * ix.B + cell_at(cd, r)];
-            }
-            const uint64_t col = wave_transpose64(tm, lane);
-            if (me_live) out[(base + lane) * ix.W + w] = col;
-        }
-        return;
-    }
-    // Dense resolve, word by word: the cells phi_r(d) of the word's 64
-    // documents are loaded once and tested against every live term's masks.
-    for (uint32_t w = 0; w < ix.W; w++) {
-        const uint64_t d = (uint64_t)w * 64 + lane;
-        const bool real = d < ix.K;
-        const uint4 cd = real ? ix.cells[d] : make_uint4(0u, 0u, 0u, 0u);
-        uint32_t ph[MAXR];
-#pragma unroll
-        for (int r = 0; r < MAXR; r++) ph[r] = cell_at(cd, r);
-        uint64_t mine = 0, todo = live;
-        while (todo) {
-            const int t = __builtin_ctzll(todo);
-            todo &= todo - 1;
-            const uint32_t *Mt = M + t * ix.R * ix.RW;
-            uint32_t keep = real ? 1u : 0u;
-#pragma unroll
-            for (int r = 0; r < MAXR; r++)
-                if (r < (int)ix.R) keep &= mask_bit(Mt + r * ix.RW, ph[r]);
-            const uint64_t word = __ballot(keep);
-            if (lane == (uint32_t)t) mine = word;
-        }
-        if ((live >> lane) & 1) out[(base + lane) * ix.W + w] = mine;
-    }
-}
 
 // -------------------------------------------------------------------------
 // sequence queries, plain form: one wave per read, 64 windows per step
@@ -197,106 +52,6 @@ __global__ __launch_bounds__(256) void k_query_seqs_plain(Index ix, const uint8_
     answer_read(ix, M, res, o, lane, opt.rmode, opt.counts, read, opt.wm);
 }
 
-// -------------------------------------------------------------------------
-// term-set queries: one wave per set, 64 terms per step; repetition 0 over
-// every term first, then the other repetitions (Section 3.3.1 order)
-// -------------------------------------------------------------------------
-template <int SEG, int G>
-__global__ __launch_bounds__(256) void k_query_termsets(Index ix, const uint64_t *__restrict__ terms,
-                                                        const uint64_t *__restrict__ offs, uint64_t n,
-                                                        uint64_t *__restrict__ out, QueryOpts opt, int use_res,
-                                                        unsigned long long *invalid) {
-    extern __shared__ __align__(16) uint64_t smem64[];
-    const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const WaveLds L = wave_lds(ix.R * ix.RW, ix.W, use_res != 0, false);
-    uint32_t *M = reinterpret_cast<uint32_t *>(smem64) + wave * L.total;
-    uint64_t *res = use_res ? reinterpret_cast<uint64_t *>(M + L.res) : nullptr;
-
-    const uint64_t q = (uint64_t)blockIdx.x * (blockDim.x >> 6) + wave;
-    if (q >= n) return;
-    const uint64_t beg = offs[q];
-    uint64_t end = offs[q + 1];
-    if (end < beg) end = beg;
-    const uint64_t len = end - beg;
-    uint64_t *o = out + q * ix.W;
-    if (len == 0 && lane == 0) atomicAdd(opt.emptyq, 1ULL);
-
-    // a k-mer index takes 31-mer codes only: a set holding another value
-    // answers no document
-    bool bad = false;
-    if (!ix.opaque)
-        for (uint64_t w = 0; w < len && !bad; w += 64)
-            bad = __ballot(w + lane < len && (terms[beg + w + lane] >> 62)) != 0;
-    if (bad) {
-        if (lane == 0) atomicAdd(invalid, 1ULL);
-        write_zeros(o, ix.W, lane);
-        return;
-    }
-    init_masks(ix, M, lane);
-    uint64_t issued = 0;
-    bool ended = false;
-    for (int pass = 0; pass < 2 && !ended; pass++) {
-        if (pass == 1 && ix.R == 1) break;
-        for (uint64_t w = 0; w < len; w += 64) {
-            const bool valid = w + lane < len;
-            const uint64_t x = valid ? terms[beg + w + lane] : 0;
-            Window wv;
-            wv.canon = ix.opaque ? x : canonical(x);
-            wv.valid = valid;
-            const uint64_t nv = (uint64_t)__popcll(__ballot(valid));
-            bool alive;
-            if (pass == 0) {
-                alive = probe_group<SEG, G, 0, 1>(ix, step_params(ix), wv, valid, lane, M);
-                issued += nv;
-            } else {
-                alive = probe_group<SEG, G, 1, 4>(ix, step_params(ix), wv, valid, lane, M);
-                issued += nv * (min(ix.R, 5u) - 1);
-                if ((int)ix.R > 5 && (alive || !opt.early_exit)) {
-                    alive &= probe_group<SEG, G, 5, MAXR - 5>(ix, step_params(ix), wv, valid, lane, M);
-                    issued += nv * (ix.R - 5);
-                }
-            }
-            if (opt.early_exit && !alive) {
-                ended = true;
-                break;
-            }
-        }
-    }
-    if (opt.probes && lane == 0 && issued) atomicAdd(opt.probes, (unsigned long long)(issued * ix.eta));
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    if (masks_some_rep_empty(ix, M, lane)) {
-        write_zeros(o, ix.W, lane);
-        return;
-    }
-    resolve(ix, M, res, o, lane, opt.rmode);
-}
-
-static constexpr uint32_t kMaxLds = 64 * 1024;
-
-int launch_query_kmers(rambo_s *h, const uint64_t *kmers, uint64_t n, uint64_t *out, hipStream_t s) {
-    const Index ix = make_index(h);
-    const int seg = default_seg(h->RW), G = (int)h->RW / seg;
-    const int KPW = 64 / G, WPB = 4;
-    const uint32_t mwords = ((KPW * h->R * h->RW) + 1) & ~1u;
-    int use_res = 1;
-    size_t lds = (size_t)WPB * (mwords + 2 * h->W) * 4;
-    if (lds > kMaxLds) {
-        use_res = 0;
-        lds = (size_t)WPB * mwords * 4;
-    }
-    const uint64_t waves = (n + KPW - 1) / KPW;
-    const uint64_t blocks = (waves + WPB - 1) / WPB;
-    if (blocks > 0x7FFFFFFFULL) return fail(RAMBO_EINVAL, "rambo_query_kmers: batch too large");
-#define RAMBO_SPLIT_BODY_                                                                                  \
-    hipLaunchKernelGGL((k_query_kmers<SEG, G>), dim3((unsigned)blocks), dim3(64 * WPB), lds, s, ix, kmers, n, out, \
-                       h->d_invalid, h->resolve, use_res)
-    RAMBO_DISPATCH_SPLIT(seg, G)
-#undef RAMBO_SPLIT_BODY_
-    HIP_CHECK(hipGetLastError());
-    return RAMBO_OK;
-}
-
 int launch_query_seqs_plain(rambo_s *h, const uint8_t *seqs, const uint64_t *offs, uint64_t n, uint64_t *out,
                             hipStream_t s, int seg, const InputHdr *hdr, unsigned long long *counts, uint64_t *wm) {
     // with hdr, the batch is read on the device and n is only its capacity
@@ -321,29 +76,6 @@ int launch_query_seqs_plain(rambo_s *h, const uint8_t *seqs, const uint64_t *off
     else                                                                                                   \
         hipLaunchKernelGGL((k_query_seqs_plain<SEG, G, false>), dim3((unsigned)blocks), dim3(64 * WPB), lds, s, ix, \
                            seqs, offs, n, hdr, out, opt, use_res)
-    RAMBO_DISPATCH_SPLIT(seg, G)
-#undef RAMBO_SPLIT_BODY_
-    HIP_CHECK(hipGetLastError());
-    return RAMBO_OK;
-}
-
-int launch_query_termsets(rambo_s *h, const uint64_t *terms, const uint64_t *offs, uint64_t n, uint64_t *out,
-                          hipStream_t s) {
-    const Index ix = make_index(h);
-    const int seg = default_seg(h->RW), G = (int)h->RW / seg;
-    const int WPB = 4;
-    int use_res = 1;
-    size_t lds = (size_t)WPB * wave_lds(h->R * h->RW, h->W, true, false).total * 4;
-    if (lds > kMaxLds) {
-        use_res = 0;
-        lds = (size_t)WPB * wave_lds(h->R * h->RW, h->W, false, false).total * 4;
-    }
-    const uint64_t blocks = (n + WPB - 1) / WPB;
-    if (blocks > 0x7FFFFFFFULL) return fail(RAMBO_EINVAL, "rambo_query_term_sets: batch too large");
-    QueryOpts opt{h->resolve, h->early_exit, h->probe_counter, SCHED_SWEEP, nullptr, h->d_emptyq};
-#define RAMBO_SPLIT_BODY_                                                                                  \
-    hipLaunchKernelGGL((k_query_termsets<SEG, G>), dim3((unsigned)blocks), dim3(64 * WPB), lds, s, ix, terms, offs, \
-                       n, out, opt, use_res, h->d_invalid)
     RAMBO_DISPATCH_SPLIT(seg, G)
 #undef RAMBO_SPLIT_BODY_
     HIP_CHECK(hipGetLastError());

@@ -219,22 +219,6 @@ __device__ __forceinline__ void set_ones(Seg<SEG> (&acc)[MAXR]) {
         for (int s = 0; s < SEG; s++) acc[r].w[s] = 0xFFFFFFFFu;
 }
 
-// 64 x 64 bit-matrix transpose across a wave: lane i holds row i on entry
-// and column i on exit (bit j of lane i's input = bit i of lane j's output).
-// Six butterfly stages, each swapping the off-diagonal blocks of one size.
-__device__ __forceinline__ uint64_t wave_transpose64(uint64_t x, uint32_t lane) {
-    const uint64_t masks[6] = {0x00000000FFFFFFFFULL, 0x0000FFFF0000FFFFULL, 0x00FF00FF00FF00FFULL,
-                               0x0F0F0F0F0F0F0F0FULL, 0x3333333333333333ULL, 0x5555555555555555ULL};
-#pragma unroll
-    for (int k = 0; k < 6; k++) {
-        const uint32_t s = 32u >> k;
-        const uint64_t m = masks[k];
-        const uint64_t y = __shfl_xor(x, (int)s);
-        x = (lane & s) ? ((x & ~m) | ((y & ~m) >> s)) : ((x & m) | ((y & m) << s));
-    }
-    return x;
-}
-
 // AND across the k-mer groups of a wave: lanes l and l ^ off (off >= G) hold
 // the same row segment of different terms.
 // With one lane per term (G = 1) the AND of all 64 lanes, by lane moves

@@ -65,6 +65,10 @@ struct rambo_s {
     rambo::HashParams *d_hp = nullptr;
     uint4 *d_cells = nullptr;  // [K] phi_r(d) of every repetition, 16 bits each
     uint4 *d_cells0 = nullptr; // [K] the same records in repetition 0's cell grouping (bdoc order)
+    // [R][ceil(W / 8)][64] records of eight 16-bit slots: slot k of record (r, c, l) is cell
+    // phi_r(d) of document d = 64 (8 c + k) + l, as phi + phi / 64 (the group resolve's LDS layout)
+    uint4 *d_docslot = nullptr;
+    uint32_t lds_max = 0;      // LDS bytes a workgroup may have
     uint32_t *d_boff = nullptr, *d_bdoc = nullptr;
     unsigned long long *d_invalid = nullptr;  // [2]: invalid inputs, queries without a term
     unsigned long long *d_emptyq = nullptr;   // = d_invalid + 1
@@ -130,10 +134,12 @@ int launch_fold(rambo_s *h, const uint32_t *in, uint32_t *out, uint32_t RWi, uin
 // Checksum of the row array (index files), synchronous on s.
 int rows_checksum(rambo_s *h, uint64_t *out, hipStream_t s);
 
-// query.hip
+// terms.hip
 int launch_query_kmers(rambo_s *h, const uint64_t *kmers, uint64_t n, uint64_t *out, hipStream_t s);
 int launch_query_termsets(rambo_s *h, const uint64_t *terms, const uint64_t *offs, uint64_t n, uint64_t *out,
                           hipStream_t s);
+
+// query.hip
 // With hdr (device), the batch is read from it on the device and n is only
 // the capacity the grid is sized for. With counts, id-list mode (QueryOpts).
 int launch_query_seqs_plain(rambo_s *h, const uint8_t *seqs, const uint64_t *offs, uint64_t n,
@@ -162,6 +168,9 @@ void drop_graphs(rambo_s *h);
     X(1, 1) X(2, 1) X(4, 1) X(1, 2) X(2, 2) X(4, 2) X(1, 4) X(2, 4) X(4, 4) X(1, 8) X(2, 8) X(4, 8) \
     X(1, 16) X(2, 16) X(4, 16) X(1, 32) X(2, 32) X(4, 32) X(1, 64) X(2, 64) X(4, 64)
 
+// the pairs with the default segment (default_seg)
+#define RAMBO_DEFAULT_SPLITS(X) X(1, 1) X(2, 1) X(4, 1) X(4, 2) X(4, 4) X(4, 8) X(4, 16) X(4, 32) X(4, 64)
+
 #define RAMBO_SPLIT_CASE_(S_, G_) case (S_) * 1000 + (G_): { constexpr int SEG = (S_), G = (G_); RAMBO_SPLIT_BODY_; } break;
 
 // Expands RAMBO_SPLIT_BODY_ (defined by the caller, using SEG and G) for the
@@ -169,6 +178,14 @@ void drop_graphs(rambo_s *h);
 #define RAMBO_DISPATCH_SPLIT(SEGV, GV)                                                              \
     switch ((SEGV) * 1000 + (GV)) {                                                                 \
         RAMBO_SPLITS(RAMBO_SPLIT_CASE_)                                                             \
+    default:                                                                                        \
+        return ::rambo::fail(RAMBO_EINVAL, "unsupported row split seg=%d lanes=%d", (int)(SEGV), (int)(GV)); \
+    }
+
+// As RAMBO_DISPATCH_SPLIT for kernels that only run with the default segment.
+#define RAMBO_DISPATCH_DEFAULT_SPLIT(SEGV, GV)                                                      \
+    switch ((SEGV) * 1000 + (GV)) {                                                                 \
+        RAMBO_DEFAULT_SPLITS(RAMBO_SPLIT_CASE_)                                                     \
     default:                                                                                        \
         return ::rambo::fail(RAMBO_EINVAL, "unsupported row split seg=%d lanes=%d", (int)(SEGV), (int)(GV)); \
     }
