@@ -140,21 +140,22 @@ __device__ __forceinline__ bool base_ok(uint32_t c) {
     return l == 'a' || l == 'c' || l == 'g' || l == 't';
 }
 
-// Morton spread: bit i of the low 32 bits goes to bit 2i.
-__device__ __forceinline__ uint64_t spread32(uint64_t v) {
-    v &= 0xFFFFFFFFULL;
-    v = (v | (v << 16)) & 0x0000FFFF0000FFFFULL;
-    v = (v | (v << 8)) & 0x00FF00FF00FF00FFULL;
-    v = (v | (v << 4)) & 0x0F0F0F0F0F0F0F0FULL;
-    v = (v | (v << 2)) & 0x3333333333333333ULL;
-    v = (v | (v << 1)) & 0x5555555555555555ULL;
-    return v;
+// Each bit of v twice in a row: bit i at bits 2i and 2i + 1 (one scalar
+// instruction; v is wave-uniform).
+__device__ __forceinline__ uint64_t double_bits(uint32_t v) {
+    uint64_t r;
+    asm("s_bitreplicate_b64_b32 %0, %1" : "=s"(r) : "s"(v));
+    return r;
 }
 
-// Bits [l, l + 31) of the 128-bit value (hi:lo).
-__device__ __forceinline__ uint32_t window31(uint64_t lo, uint64_t hi, uint32_t l) {
-    const uint64_t w = l ? ((lo >> l) | (hi << (64 - l))) : lo;
-    return (uint32_t)w & 0x7FFFFFFFu;
+// 32 two-bit codes from their bit planes: code i at bits 2i (lo) and 2i + 1 (hi).
+__device__ __forceinline__ uint64_t interleave32(uint32_t lo, uint32_t hi) {
+    return (double_bits(lo) & 0x5555555555555555ULL) | (double_bits(hi) & 0xAAAAAAAAAAAAAAAAULL);
+}
+
+// Bits [l, l + 64) of the 128-bit value (hi:lo), l < 64.
+__device__ __forceinline__ uint64_t bits64(uint64_t lo, uint64_t hi, uint32_t l) {
+    return (lo >> l) | ((hi << 1) << (63 - l));
 }
 
 struct Window {
@@ -166,19 +167,27 @@ struct Window {
 // byte at position p0 + l (c0) and, for l < 30, the byte at p0 + 64 + l (c1);
 // bytes outside the sequence are passed as 0. Lane l receives the canonical
 // code of the window starting at p0 + l and whether all its 31 bytes are
-// bases. Three ballots per plane build the 2-bit code planes of the 94
-// bytes; each lane then cuts its window out of the planes. Must be called
-// by all 64 lanes.
+// bases. Ballots build the bit planes of the 94 bytes' codes; the planes are
+// interleaved on the scalar unit, once for the wave, and each lane cuts its
+// 62 bits out of the interleaved string (with every lane cutting its window out
+// of the planes and interleaving it the extraction took about 200 vector
+// instructions, now about 60). Must be called by all 64 lanes.
 __device__ __forceinline__ Window extract_windows(uint32_t c0, uint32_t c1, uint32_t lane) {
-    const uint32_t k0 = base_code(c0), k1 = base_code(c1);
-    const uint64_t L0 = __ballot(k0 & 1u), L1 = __ballot(k1 & 1u);
-    const uint64_t H0 = __ballot(k0 >> 1), H1 = __ballot(k1 >> 1);
-    const uint64_t I0 = __ballot(!base_ok(c0)), I1 = __ballot(!base_ok(c1));
+    // a base's code: bit 1 is bit 2 of its letter, bit 0 bit 1 xor bit 2; a byte
+    // is a base iff, made lowercase, it is the letter that its code stands for
+    const uint64_t H0 = __ballot(c0 & 4u), H1 = __ballot(c1 & 4u);
+    const uint64_t L0 = __ballot(c0 & 2u) ^ H0, L1 = __ballot(c1 & 2u) ^ H1;
+    const uint64_t I0 = __ballot((c0 | 0x20u) != (__builtin_amdgcn_perm(0u, 0x74676361u, base_code(c0)) & 0xFFu));
+    const uint64_t I1 = __ballot((c1 | 0x20u) != (__builtin_amdgcn_perm(0u, 0x74676361u, base_code(c1)) & 0xFFu));
+    const uint64_t S0 = interleave32((uint32_t)L0, (uint32_t)H0);
+    const uint64_t S1 = interleave32((uint32_t)(L0 >> 32), (uint32_t)(H0 >> 32));
+    const uint64_t S2 = interleave32((uint32_t)L1, (uint32_t)H1);
     Window w;
-    w.valid = window31(I0, I1, lane) == 0;
+    w.valid = ((uint32_t)bits64(I0, I1, lane) & 0x7FFFFFFFu) == 0;
     // s = sum c_i 4^i over the window's bases i = 0..30
-    const uint64_t s = spread32(window31(L0, L1, lane)) | (spread32(window31(H0, H1, lane)) << 1);
-    const uint64_t rc = (~s) & MASK62;
+    const bool upper = lane & 32;
+    const uint64_t s = bits64(upper ? S1 : S0, upper ? S2 : S1, 2 * (lane & 31)) & MASK62;
+    const uint64_t rc = s ^ MASK62;
     const uint64_t fwd = reverse_groups31(s);
     w.canon = fwd < rc ? fwd : rc;
     return w;
