@@ -72,6 +72,8 @@ static void free_device(rambo_s *h) {
     if (h->d_cells) (void)hipFree(h->d_cells);
     if (h->d_cells0) (void)hipFree(h->d_cells0);
     if (h->d_docslot) (void)hipFree(h->d_docslot);
+    if (h->d_parts) (void)hipFree(h->d_parts);
+    if (h->parts_done) (void)hipEventDestroy(h->parts_done);
     if (h->d_ids_counts) (void)hipFree(h->d_ids_counts);
     if (h->d_ids_wm) (void)hipFree(h->d_ids_wm);
     if (h->d_ids_aux) (void)hipFree(h->d_ids_aux);

@@ -327,13 +327,6 @@ __device__ __forceinline__ uint64_t find_read(const uint64_t *off, uint64_t n, u
     return lo;
 }
 
-// a wave-uniform value, kept in scalar registers
-__device__ __forceinline__ uint64_t uniform64(uint64_t x) {
-    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)x);
-    const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(x >> 32));
-    return ((uint64_t)hi << 32) | lo;
-}
-
 __device__ __forceinline__ uint32_t load_coherent(const uint32_t *p) {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }

@@ -41,6 +41,13 @@ struct Index {
     uint32_t opaque;         // terms are opaque 64-bit values (no k-mer encoding)
 };
 
+// a wave-uniform value, kept in scalar registers
+__device__ __forceinline__ uint64_t uniform64(uint64_t x) {
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)x);
+    const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(x >> 32));
+    return ((uint64_t)hi << 32) | lo;
+}
+
 // phi_r(d) from document d's cell record
 __device__ __forceinline__ uint32_t cell_at(const uint4 &c, int r) {
     const uint32_t w = r < 2 ? c.x : r < 4 ? c.y : r < 6 ? c.z : c.w;
@@ -88,12 +95,11 @@ __host__ __device__ inline WaveLds wave_lds(uint32_t mask_words, uint64_t W, boo
 // a multiply-high, which is the plain top-bits shift when m = 2^t).
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ uint64_t bloom_pos(const HashRec &p, uint64_t m, uint64_t x) {
-    const uint64_t alo = p.alo, ahi = p.ahi, clo = p.clo, chi = p.chi;
-    const uint64_t lo = alo * x;
-    uint64_t hi = __umul64hi(alo, x) + ahi * x;
-    const uint64_t lo2 = lo + clo;
-    hi += chi + (lo2 < lo ? 1 : 0);
-    return __umul64hi(hi, m);
+    // (128-bit arithmetic: the compiler then shares the four products of alo x
+    // between its halves)
+    typedef unsigned __int128 u128;
+    const u128 s = (u128)p.alo * x + (((u128)p.chi << 64) | p.clo);
+    return __umul64hi((uint64_t)(s >> 64) + p.ahi * x, m);
 }
 
 // Hash function i of the table at hp, read through the constant address

@@ -61,6 +61,12 @@ struct rambo_s {
     uint64_t *d_ids_aux = nullptr;
     uint64_t ids_counts_cap = 0;
     std::mutex ids_mu;
+    // scratch of partitioned insertions (build.hip): one insertion at a time,
+    // the next one's stream waits for parts_done
+    void *d_parts = nullptr;
+    uint64_t parts_bytes = 0;
+    hipEvent_t parts_done = nullptr;
+    std::mutex parts_mu;
     uint32_t *rows = nullptr;
     rambo::HashParams *d_hp = nullptr;
     uint4 *d_cells = nullptr;  // [K] phi_r(d) of every repetition, 16 bits each
