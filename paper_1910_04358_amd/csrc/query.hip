@@ -52,6 +52,109 @@ __global__ __launch_bounds__(256) void k_query_seqs_plain(Index ix, const uint8_
     answer_read(ix, M, res, o, lane, opt.rmode, opt.counts, read, opt.wm);
 }
 
+// As k_query_seqs_plain with a workgroup of up to 16 waves per read, for batches
+// too small to fill the chip with one wave per read: the waves share the
+// read's windows (each a contiguous part, repetition 0 first) in masks of their
+// own, which are then ANDed, and resolve it together. Bound by the chain of
+// round trips of the longest read (offsets, bytes, repetition 0's rows, the
+// other repetitions' rows, the resolve): with one wave per read a read of
+// 1,500 bases took 24 steps of 64 windows one after the other, here two (16
+// reads at K=10,000: 53 us a call, now 21).
+template <int SEG, int G>
+__global__ __launch_bounds__(1024) void k_query_seqs_team(Index ix, const uint8_t *__restrict__ seqs,
+                                                          const uint64_t *__restrict__ offs, uint64_t n,
+                                                          const InputHdr *hdr, uint64_t *__restrict__ out,
+                                                          QueryOpts opt, int use_res) {
+    if (hdr) {
+        n = hdr->n;
+        offs = hdr->offs;
+        seqs = hdr->seqs;
+    }
+    const uint64_t read = blockIdx.x;
+    if (read >= n) return;
+    extern __shared__ __align__(16) uint64_t smem64[];
+    __shared__ unsigned long long issued, kept;
+    const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6, waves = blockDim.x >> 6;
+    const uint32_t mw = ix.R * ix.RW, pitch = wave_lds(mw, ix.W, false, false).total;
+    uint32_t *M0 = reinterpret_cast<uint32_t *>(smem64), *M = M0 + wave * pitch;
+    uint64_t *res = use_res ? reinterpret_cast<uint64_t *>(M0 + waves * pitch) : nullptr;
+    const uint64_t beg = offs[read];
+    uint64_t end = offs[read + 1];
+    if (end < beg) end = beg;
+    const uint64_t nwin = n_windows(beg, end);
+    constexpr uint32_t kGrain = 64 / G;  // terms that the wave's lanes take together
+    const uint64_t part = ((nwin + kGrain - 1) / kGrain + waves - 1) / waves * kGrain;  // windows per wave
+    const uint32_t used = part ? (uint32_t)((nwin + part - 1) / part) : 0;  // waves that have any
+    if (threadIdx.x == 0) issued = kept = 0;
+    init_masks(ix, M, lane);
+    __syncthreads();
+    const uint64_t w_lo = min(nwin, wave * part), w_hi = min(nwin, w_lo + part);
+    const bool ee = opt.early_exit != 0;
+    bool live = true;
+    uint64_t got = 0;
+    if (w_lo < w_hi)
+        got = sweep_rep0<SEG, G>(ix, seqs, beg, end, w_lo, w_hi, lane, M, ee, false, 0, 0, live);
+    __syncthreads();
+    if (ee && used) {
+        // the read ends here if the parts' AND is empty
+        uint32_t any = 0;
+        for (uint32_t w = lane; w < ix.RW; w += 64) {
+            uint32_t v = 0xFFFFFFFFu;
+            for (uint32_t k = 0; k < used; k++) v &= M0[k * pitch + w];
+            any |= v;
+        }
+        live = __ballot(any != 0) != 0;
+    }
+    if (w_lo < w_hi && ix.R > 1 && (live || !ee))
+        got += sweep_rest<SEG, G>(ix, seqs, beg, end, w_lo, w_hi, lane, M, ee);
+    if (lane == 0 && got) atomicAdd(&issued, (unsigned long long)got);
+    __syncthreads();
+    for (uint32_t w = threadIdx.x; w < mw; w += blockDim.x) {
+        uint32_t v = M0[w];
+        for (uint32_t k = 1; k < used; k++) v &= M0[k * pitch + w];
+        M0[w] = v;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        if (opt.probes && issued) atomicAdd(opt.probes, issued * ix.eta);
+        if (issued == 0) atomicAdd(opt.emptyq, 1ULL);
+    }
+    uint64_t *o = out + read * ix.W;
+    if (masks_some_rep_empty(ix, M0, lane)) {
+        if (!opt.counts)
+            for (uint32_t w = threadIdx.x; w < ix.W; w += blockDim.x) o[w] = 0;
+        else if (threadIdx.x == 0) opt.counts[read] = 0;
+        return;
+    }
+    uint64_t *wm = (opt.counts && opt.wm) ? opt.wm + read * ((ix.W + 63) / 64) : nullptr;
+    const uint64_t pc = resolve(ix, M0, res, o, lane, opt.rmode, wm, WholeGroup{wave, waves});
+    if (opt.counts) {
+        if (lane == 0 && pc) atomicAdd(&kept, (unsigned long long)pc);
+        __syncthreads();
+        if (threadIdx.x == 0) opt.counts[read] = kept;
+    }
+}
+
+// LDS of a team of waves: their masks and one candidate bitset.
+static size_t team_lds(const rambo_s *h, uint32_t waves, bool use_res) {
+    return (size_t)waves * wave_lds(h->R * h->RW, h->W, false, false).total * 4 + (use_res ? (size_t)h->W * 8 : 0);
+}
+
+// Waves per read of a batch of n reads (1: the one-wave kernel): a workgroup of
+// 16 waves a compute unit at most, then two of 8, then four a read until one
+// wave per read fills the chip. Times (one call alone, us) at K=10,000 and
+// K=101,000 with 1 wave: 16 reads 57-86 and 24-100, 257 81-110 and 120-140, 512
+// 95-111 and 123-156, 2,000 167-227 and 133-176, 4,000 194-239 and 175-195,
+// 8,000 261-272 and 217-241; with 16 waves at 257 reads 49-60 and 47-52 (4: 55-66
+// and 57-62); with 8 at 512 57-65 and 49-53; with 4 at 2,000 114-135 and 77-85,
+// at 4,000 172-187 and 118-124, at 8,000 293-315 and 197-218.
+static uint32_t team_waves(const rambo_s *h, uint64_t n) {
+    const uint64_t cu = (uint64_t)h->n_cu;
+    uint32_t t = n <= cu + cu / 8 ? 16 : n <= 2 * cu ? 8 : n <= 16 * cu ? 4 : 1;
+    while (t > 1 && team_lds(h, t, seq_lds_result(h->W)) + 64 > h->lds_max) t /= 2;
+    return t;
+}
+
 int launch_query_seqs_plain(rambo_s *h, const uint8_t *seqs, const uint64_t *offs, uint64_t n, uint64_t *out,
                             hipStream_t s, int seg, const InputHdr *hdr, unsigned long long *counts, uint64_t *wm) {
     // with hdr, the batch is read on the device and n is only its capacity
@@ -68,6 +171,17 @@ int launch_query_seqs_plain(rambo_s *h, const uint8_t *seqs, const uint64_t *off
     // answer sizes (the caller zeroes it), bitset mode in the handle
     QueryOpts opt{h->resolve, h->early_exit, h->probe_counter, sched, counts, counts ? counts + n : h->d_emptyq,
                   h->sparse_counter, counts ? wm : nullptr};
+    const uint32_t team = opt.rplus ? 1 : team_waves(h, n);
+    if (team > 1) {
+        const size_t tlds = team_lds(h, team, use_res != 0);
+#define RAMBO_SPLIT_BODY_                                                                                  \
+    hipLaunchKernelGGL((k_query_seqs_team<SEG, G>), dim3((unsigned)n), dim3(64 * team), tlds, s, ix, seqs, offs, n, \
+                       hdr, out, opt, use_res)
+        RAMBO_DISPATCH_DEFAULT_SPLIT(seg, G)
+#undef RAMBO_SPLIT_BODY_
+        HIP_CHECK(hipGetLastError());
+        return RAMBO_OK;
+    }
     // the RAMBO+ tallies have a kernel of their own (measurement only)
 #define RAMBO_SPLIT_BODY_                                                                                  \
     if (opt.rplus)                                                                                         \
@@ -76,7 +190,7 @@ int launch_query_seqs_plain(rambo_s *h, const uint8_t *seqs, const uint64_t *off
     else                                                                                                   \
         hipLaunchKernelGGL((k_query_seqs_plain<SEG, G, false>), dim3((unsigned)blocks), dim3(64 * WPB), lds, s, ix, \
                            seqs, offs, n, hdr, out, opt, use_res)
-    RAMBO_DISPATCH_SPLIT(seg, G)
+    RAMBO_DISPATCH_DEFAULT_SPLIT(seg, G)
 #undef RAMBO_SPLIT_BODY_
     HIP_CHECK(hipGetLastError());
     return RAMBO_OK;

@@ -815,6 +815,97 @@ __device__ __forceinline__ uint64_t sweep_rest_g1(const Index &ix, const uint8_t
     }
 }
 
+// Repetition 0 of the windows [w_lo, w_hi) ANDed into M (skipping the scout
+// windows of [sk_lo, sk_hi) with skip0); live is cleared once its mask is empty,
+// and with early exit the probing then stops. Returns the probes issued.
+template <int SEG, int G>
+__device__ __forceinline__ uint64_t sweep_rep0(const Index &ix, const uint8_t *__restrict__ seqs, uint64_t beg,
+                                               uint64_t end, uint64_t w_lo, uint64_t w_hi, uint32_t lane, uint32_t *M,
+                                               bool early_exit, bool skip0, uint64_t sk_lo, uint64_t sk_hi,
+                                               bool &live) {
+    uint64_t issued = 0;
+    if (G == 1 && ix.eta <= 2) {
+        // one lane per term: repetition 0 over U0 steps at a time, their
+        // rows in flight together (a lane holds U0 terms), the next
+        // group's bytes loaded meanwhile
+        constexpr int U0 = 4;
+        StepBytes nb[U0];
+#pragma unroll
+        for (int u = 0; u < U0; u++) nb[u] = load_bytes(seqs, beg, end, w_lo + 64 * u, lane);
+        for (uint64_t w = w_lo; w < w_hi; w += 64 * U0) {
+            uint64_t xs[U0];
+            bool vs[U0];
+            uint64_t nv = 0;
+#pragma unroll
+            for (int u = 0; u < U0; u++) {
+                const uint64_t wu = w + 64 * u;
+                const Window wv = extract_windows(nb[u].c0, nb[u].c1, lane);
+                vs[u] = wv.valid && (wu + lane < w_hi) && !(skip0 && is_scout(sk_lo, sk_hi, wu + lane));
+                xs[u] = wv.canon;
+                nv += (uint64_t)__popcll(__ballot(vs[u]));
+            }
+            if (w + 64 * U0 < w_hi)
+#pragma unroll
+                for (int u = 0; u < U0; u++) nb[u] = load_bytes(seqs, beg, end, w + 64 * (U0 + u), lane);
+            Seg<SEG> cm;
+#pragma unroll
+            for (int t = 0; t < SEG; t++) cm.w[t] = 0xFFFFFFFFu;
+            if (ix.eta == 2) probe_terms_eta<SEG, U0, 2>(ix, step_params(ix), 0, xs, vs, 0, cm);
+            else probe_terms_eta<SEG, U0, 1>(ix, step_params(ix), 0, xs, vs, 0, cm);
+            const bool alive = fold_rep<SEG, G>(cm, M, lane);
+            issued += nv;
+            if (!alive) {
+                live = false;
+                if (early_exit) return issued;
+            }
+        }
+    } else {
+        StepBytes next = load_bytes(seqs, beg, end, w_lo, lane);
+        for (uint64_t w = w_lo; w < w_hi; w += 64) {
+            const StepBytes cur = next;
+            if (w + 64 < w_hi) next = load_bytes(seqs, beg, end, w + 64, lane);
+            const Window wv = extract_windows(cur.c0, cur.c1, lane);
+            const bool valid = wv.valid && (w + lane < w_hi) && !(skip0 && is_scout(sk_lo, sk_hi, w + lane));
+            const bool alive = probe_group<SEG, G, 0, 1>(ix, step_params(ix), wv, valid, lane, M);
+            issued += (uint64_t)__popcll(__ballot(valid));
+            if (!alive) {
+                live = false;
+                if (early_exit) return issued;
+            }
+        }
+    }
+    return issued;
+}
+
+// Repetitions 1 .. R-1 of the windows [w_lo, w_hi), likewise.
+template <int SEG, int G, bool RPLUS = false>
+__device__ __forceinline__ uint64_t sweep_rest(const Index &ix, const uint8_t *__restrict__ seqs, uint64_t beg,
+                                               uint64_t end, uint64_t w_lo, uint64_t w_hi, uint32_t lane, uint32_t *M,
+                                               bool early_exit, unsigned long long *rplus = nullptr) {
+    uint64_t issued = 0;
+    if constexpr (G == 1 && !RPLUS) {
+        if (ix.R <= 5 && ix.eta == 2) return issued + sweep_rest_g1<SEG, 2>(ix, seqs, beg, end, w_lo, w_hi, lane, M, early_exit);
+        if (ix.R <= 5 && ix.eta == 1) return issued + sweep_rest_g1<SEG, 1>(ix, seqs, beg, end, w_lo, w_hi, lane, M, early_exit);
+    }
+    StepBytes next = load_bytes(seqs, beg, end, w_lo, lane);
+    for (uint64_t w = w_lo; w < w_hi; w += 64) {
+        const StepBytes cur = next;
+        if (w + 64 < w_hi) next = load_bytes(seqs, beg, end, w + 64, lane);
+        const Window wv = extract_windows(cur.c0, cur.c1, lane);
+        const bool valid = wv.valid && (w + lane < w_hi);
+        const uint64_t nv = (uint64_t)__popcll(__ballot(valid));
+        if constexpr (RPLUS) rplus_tally(ix, M, lane, nv, rplus);
+        bool alive = probe_group<SEG, G, 1, 4>(ix, step_params(ix), wv, valid, lane, M);
+        issued += nv * (min(ix.R, 5u) - 1);
+        if ((int)ix.R > 5 && (alive || !early_exit)) {
+            alive &= probe_group<SEG, G, 5, MAXR - 5>(ix, step_params(ix), wv, valid, lane, M);
+            issued += nv * (ix.R - 5);
+        }
+        if (early_exit && !alive) return issued;
+    }
+    return issued;
+}
+
 // Probe windows [w_lo, w_hi) of the read held in seqs[beg, end) into the
 // running masks in M, 64 windows per step; the step's masks are ANDed across
 // the wave (G lanes share a term). With early exit the probing stops once a
@@ -871,71 +962,10 @@ __device__ __forceinline__ uint64_t probe_windows(const Index &ix, const uint8_t
         }
     }
     if ((sched == SCHED_SWEEP || skip0) && ix.R > 1) {
-        if (G == 1 && ix.eta <= 2) {
-            // one lane per term: repetition 0 over U0 steps at a time, their
-            // rows in flight together (a lane holds U0 terms), the next
-            // group's bytes loaded meanwhile
-            constexpr int U0 = 4;
-            StepBytes nb[U0];
-#pragma unroll
-            for (int u = 0; u < U0; u++) nb[u] = load_bytes(seqs, beg, end, w_lo + 64 * u, lane);
-            for (uint64_t w = w_lo; w < w_hi; w += 64 * U0) {
-                uint64_t xs[U0];
-                bool vs[U0];
-                uint64_t nv = 0;
-#pragma unroll
-                for (int u = 0; u < U0; u++) {
-                    const uint64_t wu = w + 64 * u;
-                    const Window wv = extract_windows(nb[u].c0, nb[u].c1, lane);
-                    vs[u] = wv.valid && (wu + lane < w_hi) && !(skip0 && is_scout(sk_lo, sk_hi, wu + lane));
-                    xs[u] = wv.canon;
-                    nv += (uint64_t)__popcll(__ballot(vs[u]));
-                }
-                if (w + 64 * U0 < w_hi)
-#pragma unroll
-                    for (int u = 0; u < U0; u++) nb[u] = load_bytes(seqs, beg, end, w + 64 * (U0 + u), lane);
-                Seg<SEG> cm;
-#pragma unroll
-                for (int t = 0; t < SEG; t++) cm.w[t] = 0xFFFFFFFFu;
-                if (ix.eta == 2) probe_terms_eta<SEG, U0, 2>(ix, step_params(ix), 0, xs, vs, 0, cm);
-                else probe_terms_eta<SEG, U0, 1>(ix, step_params(ix), 0, xs, vs, 0, cm);
-                const bool alive = fold_rep<SEG, G>(cm, M, lane);
-                issued += nv;
-                if (early_exit && !alive) return issued;
-            }
-        } else {
-            StepBytes next = load_bytes(seqs, beg, end, w_lo, lane);
-            for (uint64_t w = w_lo; w < w_hi; w += 64) {
-                const StepBytes cur = next;
-                if (w + 64 < w_hi) next = load_bytes(seqs, beg, end, w + 64, lane);
-                const Window wv = extract_windows(cur.c0, cur.c1, lane);
-                const bool valid = wv.valid && (w + lane < w_hi) && !(skip0 && is_scout(sk_lo, sk_hi, w + lane));
-                const bool alive = probe_group<SEG, G, 0, 1>(ix, step_params(ix), wv, valid, lane, M);
-                issued += (uint64_t)__popcll(__ballot(valid));
-                if (early_exit && !alive) return issued;
-            }
-        }
-        if constexpr (G == 1 && !RPLUS) {
-            if (ix.R <= 5 && ix.eta == 2) return issued + sweep_rest_g1<SEG, 2>(ix, seqs, beg, end, w_lo, w_hi, lane, M, early_exit);
-            if (ix.R <= 5 && ix.eta == 1) return issued + sweep_rest_g1<SEG, 1>(ix, seqs, beg, end, w_lo, w_hi, lane, M, early_exit);
-        }
-        StepBytes next = load_bytes(seqs, beg, end, w_lo, lane);
-        for (uint64_t w = w_lo; w < w_hi; w += 64) {
-            const StepBytes cur = next;
-            if (w + 64 < w_hi) next = load_bytes(seqs, beg, end, w + 64, lane);
-            const Window wv = extract_windows(cur.c0, cur.c1, lane);
-            const bool valid = wv.valid && (w + lane < w_hi);
-            const uint64_t nv = (uint64_t)__popcll(__ballot(valid));
-            if constexpr (RPLUS) rplus_tally(ix, M, lane, nv, rplus);
-            bool alive = probe_group<SEG, G, 1, 4>(ix, step_params(ix), wv, valid, lane, M);
-            issued += nv * (min(ix.R, 5u) - 1);
-            if ((int)ix.R > 5 && (alive || !early_exit)) {
-                alive &= probe_group<SEG, G, 5, MAXR - 5>(ix, step_params(ix), wv, valid, lane, M);
-                issued += nv * (ix.R - 5);
-            }
-            if (early_exit && !alive) return issued;
-        }
-        return issued;
+        bool live = true;
+        issued += sweep_rep0<SEG, G>(ix, seqs, beg, end, w_lo, w_hi, lane, M, early_exit, skip0, sk_lo, sk_hi, live);
+        if (early_exit && !live) return issued;
+        return issued + sweep_rest<SEG, G, RPLUS>(ix, seqs, beg, end, w_lo, w_hi, lane, M, early_exit, rplus);
     }
     StepBytes next = load_bytes(seqs, beg, end, w_lo, lane);
     for (uint64_t w = w_lo; w < w_hi; w += 64) {
@@ -976,6 +1006,29 @@ __device__ __forceinline__ uint32_t cell_mask(const Index &ix, uint32_t wi) {
 }
 
 
+// Who resolves a read: one wave, or all waves of a workgroup (wave of waves).
+// sync() makes every member's earlier LDS and global writes visible to the rest.
+struct OneWave {
+    static constexpr uint32_t wave = 0, waves = 1;
+    __device__ __forceinline__ bool dense(uint32_t) const { return false; }
+    __device__ __forceinline__ void sync() const {
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    }
+};
+struct WholeGroup {
+    uint32_t wave, waves;
+    // Every document in four round trips at most, however many candidates there
+    // are: a k-mer that a family of documents shares has thousands, which took
+    // 33 us of a 31-base read's 42 (K=10,000, 8 to 16 waves). With five round
+    // trips of four waves the candidates are the faster again.
+    __device__ __forceinline__ bool dense(uint32_t W) const { return W <= 32 * waves; }
+    __device__ __forceinline__ void sync() const {
+        __builtin_amdgcn_s_waitcnt(0);
+        __syncthreads();
+    }
+};
+
 // Document d's cells are all set in the masks M (repetitions FIRST..R-1).
 template <int FIRST>
 __device__ __forceinline__ bool doc_kept(const Index &ix, const uint32_t *M, const uint4 &cd) {
@@ -992,7 +1045,7 @@ __device__ __forceinline__ bool doc_kept(const Index &ix, const uint32_t *M, con
 // With wm (id-list mode), only the non-zero words are written, and wm[k]
 // marks which of words 64 k .. 64 k + 63 those are.
 __device__ __forceinline__ uint64_t resolve_dense(const Index &ix, const uint32_t *M, uint64_t *out, uint32_t lane,
-                                                  uint64_t *wm) {
+                                                  uint64_t *wm, const OneWave &) {
     constexpr uint32_t U = 8;
     uint64_t pc = 0;  // this lane's documents kept
     for (uint32_t w0 = 0; w0 < ix.W; w0 += 64) {
@@ -1025,6 +1078,40 @@ __device__ __forceinline__ uint64_t resolve_dense(const Index &ix, const uint32_
     return pc;
 }
 
+// The same by all waves of a workgroup, eight words (one round trip) a wave at
+// a time; the mark word of 64 words is then written by bytes.
+__device__ __forceinline__ uint64_t resolve_dense(const Index &ix, const uint32_t *M, uint64_t *out, uint32_t lane,
+                                                  uint64_t *wm, const WholeGroup &who) {
+    constexpr uint32_t U = 8;
+    uint64_t pc = 0;
+    const uint32_t end = wm ? (ix.W + 63) / 64 * 64 : ix.W;
+    for (uint32_t w0 = who.wave * U; w0 < end; w0 += who.waves * U) {
+        uint4 cd[U];
+        bool real[U];
+#pragma unroll
+        for (uint32_t u = 0; u < U; u++) {
+            const uint64_t d = (uint64_t)(w0 + u) * 64 + lane;
+            real[u] = d < ix.K;
+            cd[u] = real[u] ? ix.cells[d] : make_uint4(0u, 0u, 0u, 0u);
+        }
+        uint64_t mine = 0;
+#pragma unroll
+        for (uint32_t u = 0; u < U; u++) {
+            const uint64_t word = __ballot(real[u] && doc_kept<0>(ix, M, cd[u]));
+            if (lane == u) mine = word;
+        }
+        if (wm) {
+            const uint64_t nz = __ballot(mine != 0);
+            if (lane == 0) reinterpret_cast<uint8_t *>(wm)[w0 / U] = (uint8_t)nz;
+        }
+        if (lane < U && w0 + lane < ix.W) {
+            if (!wm || mine) out[w0 + lane] = mine;
+            pc += (uint64_t)__popcll(mine);
+        }
+    }
+    return pc;
+}
+
 // Candidate: only documents of positive repetition-0 cells can survive the
 // intersection (Algorithm 2); each is tested in repetitions 1..R-1 and set in
 // an LDS bitset `res` (W words), which is then written out. The candidates
@@ -1033,12 +1120,12 @@ __device__ __forceinline__ uint64_t resolve_dense(const Index &ix, const uint32_
 // each lane then tests candidates k = lane, lane + 64, ... -- the cell range
 // loads, the document ids and their cell records each take one round trip
 // for up to 128 candidates.
+template <class Who>
 __device__ __forceinline__ uint64_t resolve_candidates(const Index &ix, const uint32_t *M, uint64_t *res,
-                                                       uint64_t *out, uint32_t lane, uint64_t *wm) {
-    for (uint32_t w = lane; w < ix.W; w += 64) res[w] = 0;
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    for (uint32_t c0 = 0; c0 < ix.B; c0 += 64) {
+                                                       uint64_t *out, uint32_t lane, uint64_t *wm, const Who &who) {
+    for (uint32_t w = who.wave * 64 + lane; w < ix.W; w += who.waves * 64) res[w] = 0;
+    who.sync();
+    for (uint32_t c0 = who.wave * 64; c0 < ix.B; c0 += who.waves * 64) {
         const uint32_t b = c0 + lane;
         const bool set = b < ix.B && mask_bit(M, b);
         if (__ballot(set) == 0) continue;
@@ -1088,10 +1175,9 @@ __device__ __forceinline__ uint64_t resolve_candidates(const Index &ix, const ui
                     atomicOr((unsigned long long *)&res[d[u] >> 6], 1ULL << (d[u] & 63));
         }
     }
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
+    who.sync();
     uint64_t pc = 0;
-    for (uint32_t w0 = 0; w0 < ix.W; w0 += 64) {
+    for (uint32_t w0 = who.wave * 64; w0 < ix.W; w0 += who.waves * 64) {
         const uint32_t w = w0 + lane;
         const uint64_t v = w < ix.W ? res[w] : 0;
         if (wm) {
@@ -1110,16 +1196,17 @@ __device__ __forceinline__ uint64_t resolve_candidates(const Index &ix, const ui
 // stores have completed each kept candidate sets its bit with an atomic OR
 // (the documents of distinct cells are distinct, so each bit is set once).
 // Returns this lane's number of documents kept.
+template <class Who>
 __device__ __forceinline__ uint64_t resolve_candidates_out(const Index &ix, const uint32_t *M, uint64_t *out,
-                                                           uint32_t lane, uint64_t *wm) {
-    for (uint32_t w = lane; w < ix.W; w += 64) out[w] = 0;
+                                                           uint32_t lane, uint64_t *wm, const Who &who) {
+    for (uint32_t w = who.wave * 64 + lane; w < ix.W; w += who.waves * 64) out[w] = 0;
     if (wm)
-        for (uint32_t k = lane; k < (ix.W + 63) / 64; k += 64) wm[k] = 0;
+        for (uint32_t k = who.wave * 64 + lane; k < (ix.W + 63) / 64; k += who.waves * 64) wm[k] = 0;
     // every lane's zeros are performed (acknowledged by L2) before any OR
     __builtin_amdgcn_s_waitcnt(0);
-    __builtin_amdgcn_wave_barrier();
+    who.sync();
     uint64_t kept = 0;
-    for (uint32_t c0 = 0; c0 < ix.B; c0 += 64) {
+    for (uint32_t c0 = who.wave * 64; c0 < ix.B; c0 += who.waves * 64) {
         const uint32_t b = c0 + lane;
         const bool set = b < ix.B && mask_bit(M, b);
         if (__ballot(set) == 0) continue;
@@ -1180,20 +1267,24 @@ __device__ __forceinline__ uint64_t estimate_candidates(const Index &ix, const u
 
 // resolve: 0 auto, 1 dense, 2 candidate (with res, an LDS bitset of W words,
 // the candidates collect there; without, straight in the output row).
-// Returns the number of documents reported (wave-uniform).
+// Returns the number of documents reported by this wave's part (wave-uniform).
+template <class Who>
 __device__ __forceinline__ uint64_t resolve(const Index &ix, const uint32_t *M, uint64_t *res, uint64_t *out,
-                                            uint32_t lane, int mode, uint64_t *wm = nullptr) {
+                                            uint32_t lane, int mode, uint64_t *wm, const Who &who) {
     bool cand = false;
     if (mode == 2) cand = true;
-    else if (mode == 0) cand = estimate_candidates(ix, M) * (ix.R - 1) * 2 < ix.K * ix.R;
-    uint64_t pc = !cand              ? resolve_dense(ix, M, out, lane, wm)
-                  : res != nullptr ? resolve_candidates(ix, M, res, out, lane, wm)
-                                   : resolve_candidates_out(ix, M, out, lane, wm);
+    else if (mode == 0) cand = !who.dense(ix.W) && estimate_candidates(ix, M) * (ix.R - 1) * 2 < ix.K * ix.R;
+    uint64_t pc = !cand              ? resolve_dense(ix, M, out, lane, wm, who)
+                  : res != nullptr ? resolve_candidates(ix, M, res, out, lane, wm, who)
+                                   : resolve_candidates_out(ix, M, out, lane, wm, who);
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) pc += __shfl_xor(pc, off);
     return pc;
 }
-
+__device__ __forceinline__ uint64_t resolve(const Index &ix, const uint32_t *M, uint64_t *res, uint64_t *out,
+                                            uint32_t lane, int mode, uint64_t *wm = nullptr) {
+    return resolve(ix, M, res, out, lane, mode, wm, OneWave());
+}
 
 __device__ __forceinline__ void write_zeros(uint64_t *out, uint32_t W, uint32_t lane) {
     for (uint32_t w = lane; w < W; w += 64) out[w] = 0;
