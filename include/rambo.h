@@ -340,6 +340,11 @@ int rambo_query_seqs_ids(rambo_t *h, const uint8_t *seqs, const uint64_t *offset
                          uint64_t *scratch, uint32_t *ids, uint64_t *id_offsets, uint64_t ids_cap,
                          void *stream);
 
+/* The total (id_offsets[n]) of this thread's last id-list call, which the call
+ * has learned already: a caller need not read it back from the device. 0 if that
+ * call failed before it knew. */
+uint64_t rambo_last_ids_total(void);
+
 /* For callers that cannot allocate device memory (serving loops and
  * harnesses that forbid hipMalloc between calls): rambo_query_seqs_ids with
  * the same arguments, results and statuses, making no allocation of any kind.

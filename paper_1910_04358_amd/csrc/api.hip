@@ -77,6 +77,7 @@ static void free_device(rambo_s *h) {
     if (h->d_ids_counts) (void)hipFree(h->d_ids_counts);
     if (h->d_ids_wm) (void)hipFree(h->d_ids_wm);
     if (h->d_ids_aux) (void)hipFree(h->d_ids_aux);
+    if (h->ids_host) (void)hipHostFree(h->ids_host);
     if (h->d_boff) (void)hipFree(h->d_boff);
     if (h->d_bdoc) (void)hipFree(h->d_bdoc);
     if (h->d_invalid) (void)hipFree(h->d_invalid);
@@ -211,9 +212,9 @@ rambo_s *rambo::create_index(uint64_t K, uint32_t B, uint32_t R, uint64_t m, uin
     int st = RAMBO_OK;
     if (hipMemset(h->rows, 0, h->rows_bytes) != hipSuccess) st = fail(RAMBO_EDEVICE, "rambo_create: memset failed");
     if (st == RAMBO_OK) st = upload_tables(h);
-    if (st == RAMBO_OK && hipMalloc(&h->d_invalid, 2 * sizeof(unsigned long long)) != hipSuccess)
+    if (st == RAMBO_OK && hipMalloc(&h->d_invalid, 3 * sizeof(unsigned long long)) != hipSuccess)
         st = fail(RAMBO_ENOMEM, "rambo_create: counter allocation failed");
-    if (st == RAMBO_OK && hipMemset(h->d_invalid, 0, 2 * sizeof(unsigned long long)) != hipSuccess)
+    if (st == RAMBO_OK && hipMemset(h->d_invalid, 0, 3 * sizeof(unsigned long long)) != hipSuccess)
         st = fail(RAMBO_EDEVICE, "rambo_create: memset failed");
     if (st == RAMBO_OK) h->d_emptyq = h->d_invalid + 1;
     if (st == RAMBO_OK && hipStreamCreateWithFlags(&h->aux, hipStreamNonBlocking) != hipSuccess)
@@ -454,7 +455,7 @@ RAMBO_API int rambo_query_seqs_ids(rambo_t *h, const uint8_t *seqs, const uint64
     if (!id_offsets) return fail(RAMBO_EINVAL, "rambo_query_seqs_ids: null id_offsets");
     if (h->opaque) return fail(RAMBO_EINVAL, "rambo_query_seqs_ids: the index holds opaque terms, not 31-mers");
     if (n > 0 && (!scratch || !seqs || !offsets)) return fail(RAMBO_EINVAL, "rambo_query_seqs_ids: null array");
-    if (n == 0) return launch_ids(h, scratch, 0, ids, id_offsets, ids_cap, (hipStream_t)stream, nullptr, nullptr);
+    if (n == 0) return launch_ids(h, scratch, 0, ids, id_offsets, ids_cap, (hipStream_t)stream, IdsOut(), nullptr, nullptr);
     // id-list mode: the query writes each read's answer size and the bitsets
     // of non-empty answers only
     std::lock_guard<std::mutex> g(h->ids_mu);
@@ -466,20 +467,26 @@ RAMBO_API int rambo_query_seqs_ids(rambo_t *h, const uint8_t *seqs, const uint64
         h->d_ids_wm = nullptr;
         h->d_ids_aux = nullptr;
         h->ids_counts_cap = 0;
-        HIP_CHECK(hipMalloc(&h->d_ids_counts, (n + 1) * 8));
+        HIP_CHECK(hipMalloc(&h->d_ids_counts, n * 8));
         HIP_CHECK(hipMalloc(&h->d_ids_wm, n * ((h->W + 63) / 64) * 8));
         HIP_CHECK(hipMalloc(&h->d_ids_aux, ids_aux_words(n) * 8));
         h->ids_counts_cap = n;
     }
+    if (!h->ids_host && hipHostMalloc((void **)&h->ids_host, 16) != hipSuccess) {
+        h->ids_host = nullptr;
+        (void)hipGetLastError();
+        return fail(RAMBO_ENOMEM, "rambo_query_seqs_ids: cannot allocate pinned memory");
+    }
     const hipStream_t s = (hipStream_t)stream;
-    int st = launch_store_u64(reinterpret_cast<uint64_t *>(h->d_ids_counts) + n, 0, s);  // reads without a term
+    IdsOut io;
+    io.counts = h->d_ids_counts;
+    io.wm = h->d_ids_wm;
+    io.noterm = h->d_invalid + 2;
+    const int st = h->mode == RAMBO_MODE_BATCHED
+                       ? query_seqs_batched(h, seqs, offsets, n, scratch, s, io)
+                       : launch_query_seqs_plain(h, seqs, offsets, n, scratch, s, default_seg(h->RW), nullptr, io);
     if (st != RAMBO_OK) return st;
-    st = h->mode == RAMBO_MODE_BATCHED
-                 ? query_seqs_batched(h, seqs, offsets, n, scratch, s, h->d_ids_counts, h->d_ids_wm)
-                 : launch_query_seqs_plain(h, seqs, offsets, n, scratch, s, default_seg(h->RW), nullptr,
-                                           h->d_ids_counts, h->d_ids_wm);
-    if (st != RAMBO_OK) return st;
-    return launch_ids(h, scratch, n, ids, id_offsets, ids_cap, s, h->d_ids_counts, h->d_ids_aux, h->d_ids_wm);
+    return launch_ids(h, scratch, n, ids, id_offsets, ids_cap, s, io, h->d_ids_aux, h->ids_host);
 }
 
 RAMBO_API int rambo_set_mode(rambo_t *h, int mode) {

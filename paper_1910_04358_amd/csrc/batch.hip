@@ -466,7 +466,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(G == 1 ? 1 
 }
 
 
-static int enqueue_prep(rambo_s *h, const Tune &tu, BatchGraph &bg, uint64_t *out, unsigned long long *counts,
+static int enqueue_prep(rambo_s *h, const Tune &tu, BatchGraph &bg, uint64_t *out, const IdsOut &io,
                         hipStream_t s) {
     const uint32_t mw = h->R * h->RW;
     const bool pre = tu.sched == SCHED_SCOUT;
@@ -476,7 +476,7 @@ static int enqueue_prep(rambo_s *h, const Tune &tu, BatchGraph &bg, uint64_t *ou
         const Index ix = make_index(h);
         const int G = (int)h->RW / tu.seg;
         // a grid of what fits on the device at once strides over the reads
-        const bool narrow = counts != nullptr;
+        const bool narrow = io.counts != nullptr;
         const uint64_t GS = (uint64_t)scout_group(G, narrow);
         int fit = 0;
 #define RAMBO_SPLIT_BODY_                                                                                    \
@@ -486,8 +486,8 @@ static int enqueue_prep(rambo_s *h, const Tune &tu, BatchGraph &bg, uint64_t *ou
 #undef RAMBO_SPLIT_BODY_
         const uint64_t blocks = std::max<uint64_t>(
             1, std::min<uint64_t>((bg.cap * GS + 255) / 256, (uint64_t)std::max(1, fit) * h->n_cu));
-        QueryOpts opt{h->resolve, h->early_exit, h->probe_counter, tu.sched, counts,
-                      counts ? counts + bg.cap : h->d_emptyq};
+        QueryOpts opt{h->resolve, h->early_exit, h->probe_counter, tu.sched, io.counts,
+                      io.counts ? io.noterm : h->d_emptyq};
 #define RAMBO_SPLIT_BODY_                                                                                   \
     if (narrow)                                                                                             \
         hipLaunchKernelGGL((k_batch_scout<SEG, G, 1>), dim3((unsigned)blocks), dim3(256), 0, s, ix, bg.in, out,   \
@@ -513,7 +513,7 @@ static int enqueue_prep(rambo_s *h, const Tune &tu, BatchGraph &bg, uint64_t *ou
 }
 
 static int enqueue_main(rambo_s *h, const Tune &tu, BatchGraph &bg, uint64_t *out, hipStream_t s,
-                        unsigned long long *counts, uint64_t *wm) {
+                        const IdsOut &io) {
     const Index ix = make_index(h);
     const uint32_t mw = h->R * h->RW;
     const int G = (int)h->RW / tu.seg;
@@ -521,8 +521,8 @@ static int enqueue_main(rambo_s *h, const Tune &tu, BatchGraph &bg, uint64_t *ou
     const size_t lds = (size_t)tu.wpb * wave_lds(mw, h->W, use_res != 0, false).total * 4;
     // the scout schedule has run its scout windows in the scout pass already
     const int ksched = tu.sched == SCHED_SCOUT ? SCHED_PRESCOUT : tu.sched;
-    QueryOpts opt{h->resolve, h->early_exit, h->probe_counter, ksched, counts, counts ? counts + bg.cap : h->d_emptyq,
-                  nullptr, counts ? wm : nullptr};
+    QueryOpts opt{h->resolve, h->early_exit, h->probe_counter, ksched, io.counts,
+                  io.counts ? io.noterm : h->d_emptyq, nullptr, io.counts ? io.wm : nullptr};
     // a persistent grid must be resident: never more workgroups than fit
 #define RAMBO_SPLIT_BODY_                                                                                  \
     {                                                                                                      \
@@ -610,17 +610,17 @@ static int alloc_graph_state(rambo_s *h, BatchGraph &bg, uint64_t cap, bool batc
 }
 
 int make_batch_graph(rambo_s *h, const Tune &tu, const InputHdr *in_dev, const InputHdr *init, uint64_t cap,
-                     uint64_t *out, std::shared_ptr<BatchGraph> &res, unsigned long long *counts, uint64_t *wm) {
+                     uint64_t *out, std::shared_ptr<BatchGraph> &res, const IdsOut &io) {
     auto bg = std::make_shared<BatchGraph>();
     bg->cap = cap;
     bg->tune = tu;
     int st = alloc_graph_state(h, *bg, cap, true, in_dev, init);
     if (st == RAMBO_OK)
         st = capture(h, &bg->graph_prep, &bg->exec_prep,
-                     [&](hipStream_t s) { return enqueue_prep(h, tu, *bg, out, counts, s); });
+                     [&](hipStream_t s) { return enqueue_prep(h, tu, *bg, out, io, s); });
     if (st == RAMBO_OK)
         st = capture(h, &bg->graph_main, &bg->exec_main,
-                     [&](hipStream_t s) { return enqueue_main(h, tu, *bg, out, s, counts, wm); });
+                     [&](hipStream_t s) { return enqueue_main(h, tu, *bg, out, s, io); });
     if (st != RAMBO_OK) return st;
     res = bg;
     return RAMBO_OK;
@@ -651,26 +651,26 @@ int launch_batch_graph(rambo_s *h, BatchGraph &bg, hipStream_t s) {
 }
 
 static std::string graph_key(const Tune &tu, const uint8_t *seqs, const uint64_t *offs, uint64_t n, uint64_t *out,
-                             const unsigned long long *counts, const uint64_t *wm) {
+                             const IdsOut &io) {
     char buf[320];
     snprintf(buf, sizeof buf, "%p/%p/%llu/%p/%p/%p/%d.%d.%d.%d.%d.%d", (const void *)seqs, (const void *)offs,
-             (unsigned long long)n, (void *)out, (const void *)counts, (const void *)wm, tu.seg, tu.tile,
+             (unsigned long long)n, (void *)out, (const void *)io.counts, (const void *)io.wm, tu.seg, tu.tile,
              tu.waves_per_cu, tu.wpb, tu.grab, tu.sched);
     return buf;
 }
 
 static int run_graph(rambo_s *h, const Tune &tu, const uint8_t *seqs, const uint64_t *offs, uint64_t n,
-                     uint64_t *out, hipStream_t s, unsigned long long *counts = nullptr, uint64_t *wm = nullptr) {
+                     uint64_t *out, hipStream_t s, const IdsOut &io = IdsOut()) {
     std::shared_ptr<BatchGraph> bg;
     std::lock_guard<std::mutex> g(h->mu);
-    const std::string key = graph_key(tu, seqs, offs, n, out, counts, wm);
+    const std::string key = graph_key(tu, seqs, offs, n, out, io);
     auto it = h->graphs.find(key);
     if (it != h->graphs.end()) {
         bg = it->second;
     } else {
         if (h->graphs.size() >= 16) h->graphs.clear();
         const InputHdr init{n, offs, seqs, 0};
-        int st = make_batch_graph(h, tu, nullptr, &init, n, out, bg, counts, wm);
+        int st = make_batch_graph(h, tu, nullptr, &init, n, out, bg, io);
         if (st != RAMBO_OK) return st;
         h->graphs[key] = bg;
     }
@@ -814,7 +814,7 @@ int autotune(rambo_s *h, const uint8_t *seqs, const uint64_t *offs, uint64_t n, 
 }
 
 int query_seqs_batched(rambo_s *h, const uint8_t *seqs, const uint64_t *offs, uint64_t n, uint64_t *out,
-                       hipStream_t s, unsigned long long *counts, uint64_t *wm) {
+                       hipStream_t s, const IdsOut &io) {
     if (!h->tuned) {
         h->tune.seg = default_seg(h->RW);
         const char *mode = getenv("RAMBO_TUNE");
@@ -831,7 +831,7 @@ int query_seqs_batched(rambo_s *h, const uint8_t *seqs, const uint64_t *offs, ui
         std::lock_guard<std::mutex> g(h->mu);
         tu = h->tune;
     }
-    return run_graph(h, tu, seqs, offs, n, out, s, counts, wm);
+    return run_graph(h, tu, seqs, offs, n, out, s, io);
 }
 
 }  // namespace rambo

@@ -80,7 +80,9 @@ RAMBO_API int rambo_query_seqs_ids_noalloc(rambo_t *h, const uint8_t *seqs, cons
     uint64_t *base = nullptr;
     int st = scratch_on(h->device, &base);
     if (st != RAMBO_OK) return st;
-    unsigned long long *counts = reinterpret_cast<unsigned long long *>(base);  // n + 1 words
+    IdsOut io;
+    io.counts = reinterpret_cast<unsigned long long *>(base);  // n words, then the reads without a term
+    io.noterm = io.counts + n;
     uint64_t *aux = base + n + 1;                                                // ids_aux_words(n) words
     if (n + 1 + ids_aux_words(n) > kScratchWords)
         return fail(RAMBO_EINVAL, "rambo_query_seqs_ids_noalloc: scratch too small for %llu reads",
@@ -89,9 +91,9 @@ RAMBO_API int rambo_query_seqs_ids_noalloc(rambo_t *h, const uint8_t *seqs, cons
     // reads without a term is cleared first (by a kernel, not a memset)
     st = launch_store_u64(base + n, 0, s);
     if (st == RAMBO_OK)
-        st = launch_query_seqs_plain(h, seqs, offsets, n, bits, s, default_seg(h->RW), nullptr, counts);
+        st = launch_query_seqs_plain(h, seqs, offsets, n, bits, s, default_seg(h->RW), nullptr, io);
     if (st != RAMBO_OK) return st;
     // the scan and compaction end with a wait on s, so nothing of this call
     // uses the array once it returns
-    return launch_ids(h, bits, n, ids, id_offsets, ids_cap, s, counts, aux);
+    return launch_ids(h, bits, n, ids, id_offsets, ids_cap, s, io, aux, nullptr);
 }

@@ -156,7 +156,7 @@ static uint32_t team_waves(const rambo_s *h, uint64_t n) {
 }
 
 int launch_query_seqs_plain(rambo_s *h, const uint8_t *seqs, const uint64_t *offs, uint64_t n, uint64_t *out,
-                            hipStream_t s, int seg, const InputHdr *hdr, unsigned long long *counts, uint64_t *wm) {
+                            hipStream_t s, int seg, const InputHdr *hdr, const IdsOut &io) {
     // with hdr, the batch is read on the device and n is only its capacity
     const Index ix = make_index(h);
     const int G = (int)h->RW / seg;
@@ -167,10 +167,8 @@ int launch_query_seqs_plain(rambo_s *h, const uint8_t *seqs, const uint64_t *off
     const size_t lds = (size_t)WPB * wave_lds(h->R * h->RW, h->W, use_res != 0, stage).total * 4;
     const uint64_t blocks = (n + WPB - 1) / WPB;
     if (blocks > 0x7FFFFFFFULL) return fail(RAMBO_EINVAL, "rambo_query_seqs: batch too large");
-    // id-list mode counts queries without a term in the word after the n
-    // answer sizes (the caller zeroes it), bitset mode in the handle
-    QueryOpts opt{h->resolve, h->early_exit, h->probe_counter, sched, counts, counts ? counts + n : h->d_emptyq,
-                  h->sparse_counter, counts ? wm : nullptr};
+    QueryOpts opt{h->resolve, h->early_exit, h->probe_counter, sched, io.counts,
+                  io.counts ? io.noterm : h->d_emptyq, h->sparse_counter, io.counts ? io.wm : nullptr};
     const uint32_t team = opt.rplus ? 1 : team_waves(h, n);
     if (team > 1) {
         const size_t tlds = team_lds(h, team, use_res != 0);
@@ -199,74 +197,31 @@ int launch_query_seqs_plain(rambo_s *h, const uint8_t *seqs, const uint64_t *off
 // -------------------------------------------------------------------------
 // bitsets -> ascending id lists
 // -------------------------------------------------------------------------
-// One wave per 64 reads: the reads with ids (a few per cent in id-list
-// workloads) are found with one ballot and compacted one after the other by
-// the whole wave; empty answers cost nothing more. A row is read 64 words at
-// a time (one coalesced load), eight such loads in flight together; each
-// 64-word chunk is placed by a prefix sum of its words' id counts. The total
-// (off[n]) is checked here: over cap, nothing is written and the host reports
-// the shortfall after the pass.
-__global__ __launch_bounds__(256) void k_compact(const uint64_t *__restrict__ bits, uint64_t n, uint32_t W,
-                                                 const uint64_t *__restrict__ off, uint32_t *__restrict__ ids,
-                                                 uint64_t cap) {
-    constexpr uint32_t U = 8;  // chunks in flight
-    const uint32_t lane = threadIdx.x & 63;
-    const uint64_t i0 = (((uint64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6) * 64;
-    if (i0 >= n || off[n] > cap) return;
-    const uint64_t mine = i0 + lane;
-    uint64_t todo = __ballot(mine < n && off[mine + 1] != off[mine]);
-    while (todo) {
-        const uint64_t i = i0 + (uint64_t)__builtin_ctzll(todo);
-        todo &= todo - 1;
-        const uint64_t *row = bits + i * W;
-        uint64_t base = off[i];
-        for (uint32_t c0 = 0; c0 < W; c0 += 64 * U) {
-            uint64_t word[U];
+// One read's ids, ascending, from ids[base] on, by one wave. With marks (the
+// query's marks of its non-zero bitset words, (W + 63) / 64 words) only the
+// marked words are read: per mark word, the lanes take its 64 bitset words, load
+// the marked ones, and number their ids by a prefix sum. Without, the whole row
+// is read, 64 words a load, eight loads in flight.
+__device__ __forceinline__ void place_ids(uint64_t v, uint32_t w, uint32_t lane, uint64_t &base,
+                                          uint32_t *__restrict__ ids) {
+    const uint32_t pc = (uint32_t)__popcll(v);
+    uint32_t incl = pc;
 #pragma unroll
-            for (uint32_t u = 0; u < U; u++) {
-                const uint32_t w = c0 + 64 * u + lane;
-                word[u] = w < W ? row[w] : 0;
-            }
-#pragma unroll
-            for (uint32_t u = 0; u < U; u++) {
-                const uint32_t w = c0 + 64 * u + lane;
-                const uint32_t pc = (uint32_t)__popcll(word[u]);
-                uint32_t incl = pc;
-#pragma unroll
-                for (int d = 1; d < 64; d <<= 1) {
-                    const uint32_t v = __shfl_up(incl, d);
-                    if ((int)lane >= d) incl += v;
-                }
-                uint64_t pos = base + incl - pc;
-                uint64_t x = word[u];
-                while (x) {
-                    ids[pos++] = w * 64 + (uint32_t)__builtin_ctzll(x);
-                    x &= x - 1;
-                }
-                base += __shfl(incl, 63);
-            }
-        }
+    for (int d = 1; d < 64; d <<= 1) {
+        const uint32_t t = __shfl_up(incl, d);
+        if ((int)lane >= d) incl += t;
     }
+    uint64_t pos = base + incl - pc;
+    while (v) {
+        ids[pos++] = w * 64 + (uint32_t)__builtin_ctzll(v);
+        v &= v - 1;
+    }
+    base += __shfl(incl, 63);
 }
-
-// As k_compact, reading only the words the query marked non-zero in wm
-// ((W + 63) / 64 words per read): per mark word, the lanes take its 64
-// bitset words, load the marked ones, and number their ids by a prefix sum,
-// mark words in order, so each read's ids come out ascending.
-__global__ __launch_bounds__(256) void k_compact_marked(const uint64_t *__restrict__ bits,
-                                                        const uint64_t *__restrict__ wm, uint64_t n, uint32_t W,
-                                                        const uint64_t *__restrict__ off, uint32_t *__restrict__ ids,
-                                                        uint64_t cap) {
-    const uint32_t lane = threadIdx.x & 63, WM = (W + 63) / 64;
-    const uint64_t i0 = (((uint64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6) * 64;
-    if (i0 >= n || off[n] > cap) return;
-    const uint64_t mine = i0 + lane;
-    uint64_t todo = __ballot(mine < n && off[mine + 1] != off[mine]);
-    while (todo) {
-        const uint64_t i = i0 + (uint64_t)__builtin_ctzll(todo);
-        todo &= todo - 1;
-        const uint64_t *row = bits + i * W, *marks = wm + i * WM;
-        uint64_t base = off[i];
+__device__ __forceinline__ void compact_read(const uint64_t *__restrict__ row, const uint64_t *__restrict__ marks,
+                                             uint32_t W, uint64_t base, uint32_t lane, uint32_t *__restrict__ ids) {
+    if (marks) {
+        const uint32_t WM = (W + 63) / 64;
         for (uint32_t m0 = 0; m0 < WM; m0 += 64) {
             const uint64_t mw = m0 + lane < WM ? marks[m0 + lane] : 0;
             uint64_t src = __ballot(mw != 0);
@@ -277,24 +232,83 @@ __global__ __launch_bounds__(256) void k_compact_marked(const uint64_t *__restri
                 const uint64_t m = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(mw >> 32), (int)j) << 32) |
                                    (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)mw, (int)j);
                 const uint32_t w = (m0 + j) * 64 + lane;
-                const uint64_t v = (((m >> lane) & 1) && w < W) ? row[w] : 0;
-                const uint32_t pc = (uint32_t)__popcll(v);
-                uint32_t incl = pc;
-#pragma unroll
-                for (int d = 1; d < 64; d <<= 1) {
-                    const uint32_t t = __shfl_up(incl, d);
-                    if ((int)lane >= d) incl += t;
-                }
-                uint64_t pos = base + incl - pc;
-                uint64_t x = v;
-                while (x) {
-                    ids[pos++] = w * 64 + (uint32_t)__builtin_ctzll(x);
-                    x &= x - 1;
-                }
-                base += __shfl(incl, 63);
+                place_ids((((m >> lane) & 1) && w < W) ? row[w] : 0, w, lane, base, ids);
             }
         }
+        return;
     }
+    constexpr uint32_t U = 8;
+    for (uint32_t c0 = 0; c0 < W; c0 += 64 * U) {
+        uint64_t word[U];
+#pragma unroll
+        for (uint32_t u = 0; u < U; u++) {
+            const uint32_t w = c0 + 64 * u + lane;
+            word[u] = w < W ? row[w] : 0;
+        }
+#pragma unroll
+        for (uint32_t u = 0; u < U; u++) place_ids(word[u], c0 + 64 * u + lane, lane, base, ids);
+    }
+}
+
+// What the host waits for: the total and the reads without a term (cleared for
+// the next call).
+__device__ __forceinline__ void tell_host(uint64_t *host, uint64_t total, unsigned long long *noterm) {
+    if (!host) return;
+    host[0] = total;
+    host[1] = *noterm;
+    *noterm = 0;
+}
+
+// A wave takes `per` reads (1 to 64): those with ids (a few per cent in id-list
+// workloads) are found with one ballot and compacted one after the other;
+// empty answers cost nothing more. The total (off[n]) is checked here: over cap,
+// nothing is written and the host reports the shortfall after the pass.
+__global__ __launch_bounds__(256) void k_compact(const uint64_t *__restrict__ bits, const uint64_t *__restrict__ wm,
+                                                 uint64_t n, uint32_t W, const uint64_t *__restrict__ off,
+                                                 uint32_t *__restrict__ ids, uint64_t cap, uint32_t per,
+                                                 unsigned long long *noterm, uint64_t *host) {
+    const uint32_t lane = threadIdx.x & 63, WM = (W + 63) / 64;
+    const uint64_t total = off[n];
+    if (blockIdx.x == 0 && threadIdx.x == 0) tell_host(host, total, noterm);
+    const uint64_t i0 = (((uint64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6) * per;
+    if (i0 >= n || total > cap) return;
+    const uint64_t mine = i0 + lane;
+    uint64_t todo = __ballot(lane < per && mine < n && off[mine + 1] != off[mine]);
+    while (todo) {
+        const uint64_t i = i0 + (uint64_t)__builtin_ctzll(todo);
+        todo &= todo - 1;
+        compact_read(bits + i * W, wm ? wm + i * WM : nullptr, W, off[i], lane, ids);
+    }
+}
+
+// Scan and compaction of a small batch in one launch, a wave per read: each
+// adds up the sizes before its own (n / 64 loads a lane).
+__global__ __launch_bounds__(256) void k_compact_small(const uint64_t *__restrict__ bits,
+                                                       const uint64_t *__restrict__ wm, uint32_t n, uint32_t W,
+                                                       const unsigned long long *__restrict__ counts,
+                                                       uint64_t *__restrict__ off, uint32_t *__restrict__ ids,
+                                                       uint64_t cap, unsigned long long *noterm, uint64_t *host) {
+    const uint32_t lane = threadIdx.x & 63, i = (blockIdx.x * blockDim.x + threadIdx.x) >> 6;
+    if (i >= n) return;
+    uint64_t before = 0, total = 0;
+#pragma unroll 4
+    for (uint32_t j = lane; j < n; j += 64) {
+        const uint64_t c = counts[j];
+        total += c;
+        before += j < i ? c : 0;
+    }
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) {
+        total += __shfl_xor(total, d);
+        before += __shfl_xor(before, d);
+    }
+    if (lane == 0) off[i] = before;
+    if (i == n - 1 && lane == 0) {
+        off[n] = total;
+        tell_host(host, total, noterm);
+    }
+    if (counts[i] == 0 || total > cap) return;
+    compact_read(bits + (uint64_t)i * W, wm ? wm + (uint64_t)i * ((W + 63) / 64) : nullptr, W, before, lane, ids);
 }
 
 __global__ void k_store_u64(uint64_t *p, uint64_t v) {
@@ -303,37 +317,55 @@ __global__ void k_store_u64(uint64_t *p, uint64_t v) {
 
 uint64_t ids_aux_words(uint64_t n) { return scan_parts_needed(n) + 1; }
 
+// one-launch id lists up to this many reads: 2,000 sizes are 32 loads a lane
+static constexpr uint64_t kSmallIds = 2048;
+
+// total of this thread's last id-list call
+static thread_local uint64_t g_ids_total = 0;
+
 int launch_ids(rambo_s *h, const uint64_t *bits, uint64_t n, uint32_t *ids, uint64_t *id_off, uint64_t ids_cap,
-               hipStream_t s, const unsigned long long *counts, uint64_t *aux, const uint64_t *wm) {
+               hipStream_t s, const IdsOut &io, uint64_t *aux, uint64_t *host) {
     const uint32_t W = (uint32_t)h->W;
     uint64_t total = 0;
+    g_ids_total = 0;
     if (n == 0) {
         HIP_CHECK(hipMemsetAsync(id_off, 0, 8, s));
         HIP_CHECK(hipStreamSynchronize(s));
         return RAMBO_OK;
     }
-    uint64_t *parts = aux, *d_n = aux + scan_parts_needed(n);
-    hipLaunchKernelGGL(k_store_u64, dim3(1), dim3(64), 0, s, d_n, n);
-    HIP_CHECK(hipGetLastError());
-    int sst = launch_exclusive_scan(reinterpret_cast<const uint64_t *>(counts), d_n, n, id_off, parts, s);
-    if (sst != RAMBO_OK) return sst;
-    // the compaction checks the total against ids_cap itself: no round trip
-    // to the host before it
-    if (ids) {
-        const uint64_t waves = (n + 63) / 64;
-        if (wm)
-            hipLaunchKernelGGL(k_compact_marked, dim3((unsigned)((waves + 3) / 4)), dim3(256), 0, s, bits, wm, n, W,
-                               id_off, ids, ids_cap);
-        else
-            hipLaunchKernelGGL(k_compact, dim3((unsigned)((waves + 3) / 4)), dim3(256), 0, s, bits, n, W, id_off,
-                               ids, ids_cap);
+    // the compaction checks the total against the capacity itself: no round
+    // trip to the host before it
+    const uint64_t cap = ids ? ids_cap : 0;
+    if (n <= kSmallIds) {
+        hipLaunchKernelGGL(k_compact_small, dim3((unsigned)((n + 3) / 4)), dim3(256), 0, s, bits, io.wm, (uint32_t)n, W,
+                           io.counts, id_off, ids, cap, io.noterm, host);
+    } else {
+        uint64_t *parts = aux, *d_n = aux + scan_parts_needed(n);
+        hipLaunchKernelGGL(k_store_u64, dim3(1), dim3(64), 0, s, d_n, n);
         HIP_CHECK(hipGetLastError());
+        const int sst = launch_exclusive_scan(reinterpret_cast<const uint64_t *>(io.counts), d_n, n, id_off, parts, s);
+        if (sst != RAMBO_OK) return sst;
+        // reads per wave: as many as leave every place for a wave one
+        uint32_t per = 64;
+        while (per > 1 && n < (uint64_t)per * h->n_cu * 16) per /= 2;
+        const uint64_t waves = (n + per - 1) / per;
+        hipLaunchKernelGGL(k_compact, dim3((unsigned)((waves + 3) / 4)), dim3(256), 0, s, bits, io.wm, n, W, id_off, ids,
+                           cap, per, io.noterm, host);
     }
+    HIP_CHECK(hipGetLastError());
     unsigned long long noterm = 0;
-    hipError_t e = hipMemcpyAsync(&total, id_off + n, 8, hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess && counts) e = hipMemcpyAsync(&noterm, counts + n, 8, hipMemcpyDeviceToHost, s);
+    hipError_t e = hipSuccess;
+    if (!host) {
+        e = hipMemcpyAsync(&total, id_off + n, 8, hipMemcpyDeviceToHost, s);
+        if (e == hipSuccess) e = hipMemcpyAsync(&noterm, io.noterm, 8, hipMemcpyDeviceToHost, s);
+    }
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) return fail(RAMBO_EDEVICE, "rambo_query_seqs_ids: %s", hipGetErrorString(e));
+    if (host) {
+        total = host[0];
+        noterm = host[1];
+    }
+    g_ids_total = total;
     if (total > ids_cap)
         return fail(RAMBO_ETRUNC, "rambo_query_seqs_ids: %llu ids do not fit %llu", (unsigned long long)total,
                     (unsigned long long)ids_cap);
@@ -348,3 +380,7 @@ int launch_store_u64(uint64_t *p, uint64_t v, hipStream_t s) {
 }
 
 }  // namespace rambo
+
+using namespace rambo;
+
+RAMBO_API uint64_t rambo_last_ids_total(void) { return g_ids_total; }

@@ -29,6 +29,15 @@ int ok();                                     // clears nothing, returns RAMBO_O
             return ::rambo::fail(RAMBO_EDEVICE, "%s failed: %s", #expr, hipGetErrorString(e_));    \
     } while (0)
 
+// Where an id-list query leaves its answer sizes (counts, one per read), the
+// marks of their non-zero bitset words (wm, or null) and, added up, the reads
+// without a term (noterm). Null counts: a bitset query.
+struct IdsOut {
+    unsigned long long *counts = nullptr;
+    uint64_t *wm = nullptr;
+    unsigned long long *noterm = nullptr;
+};
+
 // Launch shape of the sequence-query kernels; what the autotuner searches.
 struct Tune {
     int seg = 4;          // 32-bit words of a row one lane reads (1, 2 or 4)
@@ -60,6 +69,7 @@ struct rambo_s {
     uint64_t *d_ids_wm = nullptr;  // [ids_counts_cap][(W + 63) / 64] non-zero word marks
     uint64_t *d_ids_aux = nullptr;
     uint64_t ids_counts_cap = 0;
+    uint64_t *ids_host = nullptr;  // pinned, [2]: an id-list call's total and its reads without a term
     std::mutex ids_mu;
     // scratch of partitioned insertions (build.hip): one insertion at a time,
     // the next one's stream waits for parts_done
@@ -76,7 +86,8 @@ struct rambo_s {
     uint4 *d_docslot = nullptr;
     uint32_t lds_max = 0;      // LDS bytes a workgroup may have
     uint32_t *d_boff = nullptr, *d_bdoc = nullptr;
-    unsigned long long *d_invalid = nullptr;  // [2]: invalid inputs, queries without a term
+    unsigned long long *d_invalid = nullptr;  // [3]: invalid inputs, queries without a term, and those of
+                                              // the id-list call that runs (zero between calls)
     unsigned long long *d_emptyq = nullptr;   // = d_invalid + 1
     std::vector<uint64_t> pa, pb, Alo, Ahi, Clo, Chi;
     std::vector<uint32_t> phi;  // [R][K]
@@ -150,22 +161,20 @@ int launch_query_termsets(rambo_s *h, const uint64_t *terms, const uint64_t *off
 // the capacity the grid is sized for. With counts, id-list mode (QueryOpts).
 int launch_query_seqs_plain(rambo_s *h, const uint8_t *seqs, const uint64_t *offs, uint64_t n,
                             uint64_t *out, hipStream_t s, int seg, const InputHdr *hdr = nullptr,
-                            unsigned long long *counts = nullptr, uint64_t *wm = nullptr);
-// Bitsets of an id-list mode query to id lists: counts holds the n answer
-// sizes the query wrote, aux ids_aux_words(n) words of scan scratch.
+                            const IdsOut &io = IdsOut());
+// Bitsets of an id-list mode query to id lists; aux: ids_aux_words(n) words of
+// scan scratch. With host (two words of pinned memory) the total and the reads
+// without a term reach the host through it, and io.noterm is left zero for the
+// next call; without, by copies.
 uint64_t ids_aux_words(uint64_t n);
-// counts has n + 1 words: the answer sizes, then the number of reads without
-// a term (RAMBO_OK_EMPTYQ is returned if it is not zero).
-// With wm (the query's non-zero word marks), only the marked words are read.
-int launch_ids(rambo_s *h, const uint64_t *bits, uint64_t n, uint32_t *ids, uint64_t *id_off,
-               uint64_t ids_cap, hipStream_t s, const unsigned long long *counts, uint64_t *aux,
-               const uint64_t *wm = nullptr);
+int launch_ids(rambo_s *h, const uint64_t *bits, uint64_t n, uint32_t *ids, uint64_t *id_off, uint64_t ids_cap,
+               hipStream_t s, const IdsOut &io, uint64_t *aux, uint64_t *host);
 // *p = v on stream s (a one-thread kernel: no memset node in captured work)
 int launch_store_u64(uint64_t *p, uint64_t v, hipStream_t s);
 
 // batch.hip
 int query_seqs_batched(rambo_s *h, const uint8_t *seqs, const uint64_t *offs, uint64_t n, uint64_t *out,
-                       hipStream_t s, unsigned long long *counts = nullptr, uint64_t *wm = nullptr);
+                       hipStream_t s, const IdsOut &io = IdsOut());
 void drop_graphs(rambo_s *h);
 
 // Row split: a lane reads SEG words of a row, G = row_words / SEG lanes share

@@ -63,6 +63,7 @@ SIGNATURES = {
     "rambo_query_kmers": ([_vp, _vp, _u64, _vp, _vp], _i32),
     "rambo_query_seqs": ([_vp, _vp, _vp, _u64, _vp, _vp], _i32),
     "rambo_query_seqs_ids": ([_vp, _vp, _vp, _u64, _vp, _vp, _vp, _u64, _vp], _i32),
+    "rambo_last_ids_total": ([], _u64),
     "rambo_query_seqs_ids_noalloc": ([_vp, _vp, _vp, _u64, _vp, _vp, _vp, _u64, _vp], _i32),
     "rambo_route": ([_vp, _u64, _u32, _u64, _vp, _vp], _i32),
     "rambo_create_shard": ([_u64, _u32, _u32, _u64, _u32, _u64, _vp], _vp),
@@ -388,10 +389,10 @@ class Rambo:
                                         _dptr(id_off, "id_offsets", _i64()), ids_cap, _stream(stream))
         if st == ETRUNC:
             e = RamboError(st, lib().rambo_last_error().decode())
-            e.required = int(id_off[-1].item())
+            e.required = int(lib().rambo_last_ids_total())
             raise e
         self.last_status = _check(st)
-        return ids[: int(id_off[-1].item())], id_off
+        return ids[: int(lib().rambo_last_ids_total())], id_off
 
     # -- options
     def set_mode(self, mode: int) -> None:
