@@ -364,10 +364,20 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(G == 1 ? 1 
     const uint64_t c3 = uniform64(bb.cls[48]), c2 = uniform64(bb.cls[32]), c1 = uniform64(bb.cls[16]);
     const uint64_t total = c3 + c2 + c1 + uniform64(bb.cls[0]) + n_extra;  // queued reads and extra tiles
     uint64_t issued = 0;
+    // A wave's first items come with its place in the grid, the longest to
+    // different workgroups; the queue's head counts from there. (Taken from the
+    // head as well, by all 4,096 waves at once, they came 30 us late: the atomics
+    // on one word are performed one after the other.)
+    const uint64_t waves = (uint64_t)gridDim.x * (blockDim.x >> 6);
+    bool started = false;
     for (;;) {
-        uint64_t t0 = 0;
-        if (lane == 0) t0 = atomicAdd(bb.head, (unsigned long long)grab);
-        t0 = uniform64(__shfl(t0, 0));
+        uint64_t t0 = ((uint64_t)wave * gridDim.x + blockIdx.x) * grab;
+        if (started) {
+            if (lane == 0) t0 = waves * grab + atomicAdd(bb.head, (unsigned long long)grab);
+            t0 = __shfl(t0, 0);
+        }
+        started = true;
+        t0 = uniform64(t0);
         if (t0 >= total) break;
         const uint64_t t1 = min(total, t0 + grab);
         for (uint64_t t = t0; t < t1; t++) {

@@ -10,6 +10,7 @@
 
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include <type_traits>
 
 namespace rambo {
 
@@ -1029,14 +1030,30 @@ struct WholeGroup {
     }
 };
 
-// Document d's cells are all set in the masks M (repetitions FIRST..R-1).
-template <int FIRST>
-__device__ __forceinline__ bool doc_kept(const Index &ix, const uint32_t *M, const uint4 &cd) {
-    bool keep = true;
+// keep[u] of documents with cell records cd[u] only if their cells are all set
+// in the masks M. The mask words of four repetitions of all N documents are
+// read together (a repetition past R reads repetition 0's word again): tested
+// one by one, each read waiting for the last, eight documents a lane took 3.5 us.
+template <int N>
+__device__ __forceinline__ void docs_kept(const Index &ix, const uint32_t *M, const uint4 (&cd)[N], bool (&keep)[N]) {
+    auto four = [&](auto from) {
+        constexpr int R0 = decltype(from)::value;
+        uint32_t bits[N];
 #pragma unroll
-    for (int r = FIRST; r < MAXR; r++)
-        if (r < (int)ix.R) keep = keep && mask_bit(M + r * ix.RW, cell_at(cd, r));
-    return keep;
+        for (int u = 0; u < N; u++) {
+            bits[u] = 1u;
+#pragma unroll
+            for (int r = R0; r < R0 + 4; r++) {
+                const bool real = r < (int)ix.R;
+                const uint32_t c = real ? cell_at(cd[u], r) : cell_at(cd[u], 0);
+                bits[u] &= M[(real ? r * ix.RW : 0u) + (c >> 5)] >> (c & 31);
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < N; u++) keep[u] = keep[u] & (bool)(bits[u] & 1u);
+    };
+    four(std::integral_constant<int, 0>{});
+    if (ix.R > 4) four(std::integral_constant<int, 4>{});
 }
 
 // Dense: every document tests its R cells; lane l handles document 64 w + l
@@ -1060,9 +1077,10 @@ __device__ __forceinline__ uint64_t resolve_dense(const Index &ix, const uint32_
                 real[u] = t + u < nw && d < ix.K;
                 cd[u] = real[u] ? ix.cells[d] : make_uint4(0u, 0u, 0u, 0u);
             }
+            docs_kept<(int)U>(ix, M, cd, real);
 #pragma unroll
             for (uint32_t u = 0; u < U; u++) {
-                const uint64_t word = __ballot(real[u] && doc_kept<0>(ix, M, cd[u]));
+                const uint64_t word = __ballot(real[u]);
                 if (lane == t + u) mine = word;
             }
         }
@@ -1095,9 +1113,10 @@ __device__ __forceinline__ uint64_t resolve_dense(const Index &ix, const uint32_
             cd[u] = real[u] ? ix.cells[d] : make_uint4(0u, 0u, 0u, 0u);
         }
         uint64_t mine = 0;
+        docs_kept<(int)U>(ix, M, cd, real);
 #pragma unroll
         for (uint32_t u = 0; u < U; u++) {
-            const uint64_t word = __ballot(real[u] && doc_kept<0>(ix, M, cd[u]));
+            const uint64_t word = __ballot(real[u]);
             if (lane == u) mine = word;
         }
         if (wm) {
@@ -1112,71 +1131,146 @@ __device__ __forceinline__ uint64_t resolve_dense(const Index &ix, const uint32_
     return pc;
 }
 
+// position of the n-th set bit of x (n from 0, below popc(x))
+__device__ __forceinline__ uint32_t nth_bit(uint32_t x, uint32_t n) {
+    uint32_t at = 0;
+#pragma unroll
+    for (uint32_t h = 16; h; h >>= 1) {
+        const uint32_t c = (uint32_t)__popc((x >> at) & ((1u << h) - 1u));
+        if (n >= c) {
+            n -= c;
+            at += h;
+        }
+    }
+    return at;
+}
+
+__device__ __forceinline__ uint32_t wave_inclusive(uint32_t v, uint32_t lane) {
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const uint32_t t = __shfl_up(v, d);
+        if ((int)lane >= d) v += t;
+    }
+    return v;
+}
+
+// The cells set in a repetition's mask M0, numbered in ascending order. Lane l
+// counts those of words nw l .. nw l + nw - 1 (RW <= 256: nw <= 4).
+struct SetCells {
+    uint32_t nw, incl, total;
+    __device__ __forceinline__ SetCells(const Index &ix, const uint32_t *M0, uint32_t lane) {
+        nw = (ix.RW + 63) / 64;
+        uint32_t c = 0;
+        for (uint32_t k = 0; k < nw; k++) {
+            const uint32_t w = lane * nw + k;
+            if (w < ix.RW) c += (uint32_t)__popc(M0[w] & cell_mask(ix, w));
+        }
+        incl = wave_inclusive(c, lane);
+        total = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+    }
+    // cell number i (below total; the lanes may ask for different ones)
+    __device__ __forceinline__ uint32_t at(const Index &ix, const uint32_t *M0, uint32_t i) const {
+        uint32_t lo = 0;  // its lane: the number of lanes whose inclusive count is <= i
+#pragma unroll
+        for (uint32_t st = 32; st; st >>= 1)
+            if (__shfl(incl, (int)(lo + st - 1)) <= i) lo += st;
+        const uint32_t before = __shfl(incl, (int)(lo ? lo - 1 : 0));
+        uint32_t n = i - (lo ? before : 0), w = lo * nw;
+        uint32_t x = w < ix.RW ? M0[w] & cell_mask(ix, w) : 0;
+        for (uint32_t k = 1; k < nw; k++) {
+            const uint32_t c = (uint32_t)__popc(x);
+            if (n < c) break;
+            n -= c;
+            w++;
+            x = M0[w] & cell_mask(ix, w);
+        }
+        return w * 32 + nth_bit(x, n);
+    }
+};
+
 // Candidate: only documents of positive repetition-0 cells can survive the
-// intersection (Algorithm 2); each is tested in repetitions 1..R-1 and set in
-// an LDS bitset `res` (W words), which is then written out. The candidates
-// are spread over the lanes: per 64 cells, lane l takes cell c0 + l (its
-// range of bdoc), a prefix sum over the lanes numbers the candidates, and
-// each lane then tests candidates k = lane, lane + 64, ... -- the cell range
-// loads, the document ids and their cell records each take one round trip
-// for up to 128 candidates.
+// intersection (Algorithm 2); each is tested in repetitions 1..R-1. The set
+// cells are listed 64 at a time, one a lane, with their ranges of documents; a
+// range is cut into slots of 64 documents (lane l tests the l-th), and the ids
+// and cell records of kSlotsAhead slots are loaded in one round trip. Numbering
+// the candidates one by one, with a search across the lanes for each, cost
+// twice the time: a 31-base read that a family of documents shares (5,000
+// candidates at K=10,000) 70 us, now 25.
+// Kept documents are collected in an LDS bitset res (W words), which is then
+// written out; or, without (it would take W words of LDS per wave and limit the
+// waves a compute unit holds), by atomic ORs straight in the output row, which
+// is zeroed first (documents of distinct cells are distinct: each bit is set
+// once). With marks (id-list mode) and one batch of slots only the words that
+// are ORed to are zeroed. Returns this lane's number of documents kept.
+constexpr int kSlotsAhead = 6;
 template <class Who>
-__device__ __forceinline__ uint64_t resolve_candidates(const Index &ix, const uint32_t *M, uint64_t *res,
-                                                       uint64_t *out, uint32_t lane, uint64_t *wm, const Who &who) {
-    for (uint32_t w = who.wave * 64 + lane; w < ix.W; w += who.waves * 64) res[w] = 0;
-    who.sync();
-    for (uint32_t c0 = who.wave * 64; c0 < ix.B; c0 += who.waves * 64) {
-        const uint32_t b = c0 + lane;
-        const bool set = b < ix.B && mask_bit(M, b);
-        if (__ballot(set) == 0) continue;
+__device__ __forceinline__ uint64_t resolve_candidates(const Index &ix, const uint32_t *M, const SetCells &cells,
+                                                       uint64_t *res, uint64_t *out, uint32_t lane, uint64_t *wm,
+                                                       const Who &who) {
+    const uint32_t first = who.wave * 64 + lane, step = who.waves * 64;
+    uint64_t kept = 0;
+    bool ready = false;  // the bitset or row is zeroed
+    for (uint32_t c0 = 0; c0 < cells.total; c0 += 64) {
         uint32_t beg = 0, len = 0;
-        if (set) {
+        const uint32_t b = cells.at(ix, M, min(c0 + lane, cells.total - 1));
+        if (c0 + lane < cells.total) {
             beg = ix.boff[b];
             len = ix.boff[b + 1] - beg;
         }
-        uint32_t incl = len;  // inclusive prefix sum of len over the lanes
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-            const uint32_t t = __shfl_up(incl, off);
-            if ((int)lane >= off) incl += t;
+        if (c0 == 0) {
+            // (zeroed while the ranges are loaded)
+            if (res) for (uint32_t w = first; w < ix.W; w += step) res[w] = 0;
+            else if (wm) for (uint32_t k = first; k < (ix.W + 63) / 64; k += step) wm[k] = 0;
         }
-        const uint32_t total = __shfl(incl, 63);
-        const uint32_t excl = incl - len;
-        // a candidate's id and its cell record are loaded together (the
-        // records are also kept in repetition 0's grouping): one round trip
-        // per 64 * U candidates
-        constexpr int U = 4;
-        for (uint32_t k0 = 0; k0 < total; k0 += 64 * U) {
-            uint32_t pos[U];
-            bool has[U];
+        const uint32_t incl = wave_inclusive((len + 63) / 64, lane), excl = incl - (len + 63) / 64;
+        const uint32_t slots = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+        const bool few = !res && wm && cells.total <= 64 && slots <= kSlotsAhead * who.waves;
+        if (!ready) {
+            if (!res && !few) for (uint32_t w = first; w < ix.W; w += step) out[w] = 0;
+            // every member's zeros are performed (acknowledged by L2) before any OR
+            if (!res) __builtin_amdgcn_s_waitcnt(0);
+            who.sync();
+            ready = true;
+        }
+        for (uint32_t s0 = who.wave * kSlotsAhead; s0 < slots || few; s0 += who.waves * kSlotsAhead) {
+            uint32_t d[kSlotsAhead];
+            uint4 cd[kSlotsAhead];
+            bool has[kSlotsAhead];
 #pragma unroll
-            for (int u = 0; u < U; u++) {
-                const uint32_t k = k0 + (uint32_t)u * 64 + lane;
-                has[u] = k < total;
-                // owner: the number of lanes whose inclusive sum is <= k (its
-                // range holds candidate k; all lanes take part in the search)
-                uint32_t lo = 0;
-#pragma unroll
-                for (uint32_t st = 32; st; st >>= 1)
-                    if (__shfl(incl, (int)(lo + st - 1)) <= k) lo += st;
-                const uint32_t ob = __shfl(beg, (int)lo), oe = __shfl(excl, (int)lo);
-                pos[u] = has[u] ? ob + (k - oe) : 0u;
+            for (int u = 0; u < kSlotsAhead; u++) {
+                const uint32_t s = s0 + u;
+                const uint64_t own = __ballot(excl <= s && s < incl);  // the cell that slot s belongs to
+                const int j = own ? __builtin_ctzll(own) : 0;
+                const uint32_t off = (s - (uint32_t)__builtin_amdgcn_readlane((int)excl, j)) * 64 + lane;
+                has[u] = own && off < (uint32_t)__builtin_amdgcn_readlane((int)len, j);
+                const uint32_t pos = has[u] ? (uint32_t)__builtin_amdgcn_readlane((int)beg, j) + off : 0u;
+                d[u] = has[u] ? ix.bdoc[pos] : 0u;
+                cd[u] = has[u] ? ix.cells0[pos] : make_uint4(0u, 0u, 0u, 0u);
             }
-            uint32_t d[U];
-            uint4 cd[U];
+            docs_kept<kSlotsAhead>(ix, M, cd, has);
+            if (few) {
 #pragma unroll
-            for (int u = 0; u < U; u++) {
-                d[u] = has[u] ? ix.bdoc[pos[u]] : 0u;
-                cd[u] = has[u] ? ix.cells0[pos[u]] : make_uint4(0u, 0u, 0u, 0u);
+                for (int u = 0; u < kSlotsAhead; u++)
+                    if (has[u]) out[d[u] >> 6] = 0;
+                __builtin_amdgcn_s_waitcnt(0);
+                who.sync();
             }
 #pragma unroll
-            for (int u = 0; u < U; u++)
-                if (has[u] && doc_kept<1>(ix, M, cd[u]))
+            for (int u = 0; u < kSlotsAhead; u++) {
+                if (!has[u]) continue;
+                if (res) {
                     atomicOr((unsigned long long *)&res[d[u] >> 6], 1ULL << (d[u] & 63));
+                } else {
+                    atomicOr((unsigned long long *)&out[d[u] >> 6], 1ULL << (d[u] & 63));
+                    if (wm) atomicOr((unsigned long long *)&wm[d[u] >> 12], 1ULL << ((d[u] >> 6) & 63));
+                    kept++;
+                }
+            }
+            if (few) break;
         }
     }
+    if (!res) return kept;
     who.sync();
-    uint64_t pc = 0;
     for (uint32_t w0 = who.wave * 64; w0 < ix.W; w0 += who.waves * 64) {
         const uint32_t w = w0 + lane;
         const uint64_t v = w < ix.W ? res[w] : 0;
@@ -1185,84 +1279,9 @@ __device__ __forceinline__ uint64_t resolve_candidates(const Index &ix, const ui
             if (lane == 0) wm[w0 >> 6] = nz;
         }
         if (w < ix.W && (!wm || v)) out[w] = v;
-        pc += (uint64_t)__popcll(v);
-    }
-    return pc;
-}
-
-// As resolve_candidates, with the answer written straight into the output
-// row instead of an LDS bitset (which would take W words of LDS per wave and
-// limit the waves a compute unit holds): the row is zeroed, and once those
-// stores have completed each kept candidate sets its bit with an atomic OR
-// (the documents of distinct cells are distinct, so each bit is set once).
-// Returns this lane's number of documents kept.
-template <class Who>
-__device__ __forceinline__ uint64_t resolve_candidates_out(const Index &ix, const uint32_t *M, uint64_t *out,
-                                                           uint32_t lane, uint64_t *wm, const Who &who) {
-    for (uint32_t w = who.wave * 64 + lane; w < ix.W; w += who.waves * 64) out[w] = 0;
-    if (wm)
-        for (uint32_t k = who.wave * 64 + lane; k < (ix.W + 63) / 64; k += who.waves * 64) wm[k] = 0;
-    // every lane's zeros are performed (acknowledged by L2) before any OR
-    __builtin_amdgcn_s_waitcnt(0);
-    who.sync();
-    uint64_t kept = 0;
-    for (uint32_t c0 = who.wave * 64; c0 < ix.B; c0 += who.waves * 64) {
-        const uint32_t b = c0 + lane;
-        const bool set = b < ix.B && mask_bit(M, b);
-        if (__ballot(set) == 0) continue;
-        uint32_t beg = 0, len = 0;
-        if (set) {
-            beg = ix.boff[b];
-            len = ix.boff[b + 1] - beg;
-        }
-        uint32_t incl = len;  // inclusive prefix sum of len over the lanes
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-            const uint32_t t = __shfl_up(incl, off);
-            if ((int)lane >= off) incl += t;
-        }
-        const uint32_t total = __shfl(incl, 63);
-        const uint32_t excl = incl - len;
-        constexpr int U = 4;  // candidates per lane per round trip
-        for (uint32_t k0 = 0; k0 < total; k0 += 64 * U) {
-            uint32_t pos[U];
-            bool has[U];
-#pragma unroll
-            for (int u = 0; u < U; u++) {
-                const uint32_t k = k0 + (uint32_t)u * 64 + lane;
-                has[u] = k < total;
-                uint32_t lo = 0;  // owner lane of candidate k (all lanes search)
-#pragma unroll
-                for (uint32_t st = 32; st; st >>= 1)
-                    if (__shfl(incl, (int)(lo + st - 1)) <= k) lo += st;
-                const uint32_t ob = __shfl(beg, (int)lo), oe = __shfl(excl, (int)lo);
-                pos[u] = has[u] ? ob + (k - oe) : 0u;
-            }
-            uint32_t d[U];
-            uint4 cd[U];
-#pragma unroll
-            for (int u = 0; u < U; u++) {
-                d[u] = has[u] ? ix.bdoc[pos[u]] : 0u;
-                cd[u] = has[u] ? ix.cells0[pos[u]] : make_uint4(0u, 0u, 0u, 0u);
-            }
-#pragma unroll
-            for (int u = 0; u < U; u++)
-                if (has[u] && doc_kept<1>(ix, M, cd[u])) {
-                    atomicOr((unsigned long long *)&out[d[u] >> 6], 1ULL << (d[u] & 63));
-                    if (wm) atomicOr((unsigned long long *)&wm[d[u] >> 12], 1ULL << ((d[u] >> 6) & 63));
-                    kept++;
-                }
-        }
+        kept += (uint64_t)__popcll(v);
     }
     return kept;
-}
-
-// Number of candidates of the repetition-0 cells set in M, estimated from the
-// number of cells (documents spread evenly over the B cells).
-__device__ __forceinline__ uint64_t estimate_candidates(const Index &ix, const uint32_t *M0) {
-    uint64_t cells = 0;
-    for (uint32_t wi = 0; wi < ix.RW; wi++) cells += __popc(M0[wi] & cell_mask(ix, wi));
-    return cells * ((ix.K + ix.B - 1) / ix.B);
 }
 
 // resolve: 0 auto, 1 dense, 2 candidate (with res, an LDS bitset of W words,
@@ -1271,12 +1290,17 @@ __device__ __forceinline__ uint64_t estimate_candidates(const Index &ix, const u
 template <class Who>
 __device__ __forceinline__ uint64_t resolve(const Index &ix, const uint32_t *M, uint64_t *res, uint64_t *out,
                                             uint32_t lane, int mode, uint64_t *wm, const Who &who) {
-    bool cand = false;
-    if (mode == 2) cand = true;
-    else if (mode == 0) cand = !who.dense(ix.W) && estimate_candidates(ix, M) * (ix.R - 1) * 2 < ix.K * ix.R;
-    uint64_t pc = !cand              ? resolve_dense(ix, M, out, lane, wm, who)
-                  : res != nullptr ? resolve_candidates(ix, M, res, out, lane, wm, who)
-                                   : resolve_candidates_out(ix, M, out, lane, wm, who);
+    // auto: the strategy of fewer round trips (512 documents each, or kSlotsAhead
+    // slots of up to 64; documents spread evenly over the B cells)
+    const SetCells cells(ix, M, lane);
+    bool cand = mode == 2;
+    if (mode == 0) {
+        const uint64_t slots = (uint64_t)cells.total * (((ix.K + ix.B - 1) / ix.B + 63) / 64);
+        cand = !who.dense(ix.W) && slots / kSlotsAhead + 1 < (ix.W + 7) / 8;
+    }
+    if (cells.total == 0) cand = false;
+    uint64_t pc = cand ? resolve_candidates(ix, M, cells, res, out, lane, wm, who)
+                       : resolve_dense(ix, M, out, lane, wm, who);
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) pc += __shfl_xor(pc, off);
     return pc;
