@@ -43,32 +43,38 @@ __global__ void k_batch_reset(BatchBufs bb) {
 // With a scout pass before it (prescout), reads that pass ended are
 // answered already and left out of the queue, and a multi-tile read's
 // running mask starts from its scout AND in repetition 0.
-// Each thread takes kPrepReads reads (256 apart), so a workgroup makes one
-// atomic per size class for 256 x kPrepReads reads: same-address atomics
+// Each thread takes kPrepReads reads (kThreads apart), so a workgroup makes one
+// atomic per size class for kThreads x kPrepReads reads: same-address atomics
 // serialise, and one per 256 reads made the pass over 10^6 reads wait on them
 // (52 -> 23 us with 4); small batches keep one read per thread (100,000
 // reads: 9 us with 1, 19 us with 4, where fewer workgroups wait longer).
-template <uint32_t kPrepReads>
-__global__ __launch_bounds__(256) void k_batch_prep(const InputHdr *in, uint32_t mw, uint32_t rw, uint32_t tile,
-                                                    BatchBufs bb, int prescout) {
+// The workgroup's sum of extra tiles goes to part, for the scan. A batch that
+// one workgroup holds (kOne, up to 4,096 reads) is scanned here too, and needs
+// neither the reset nor the scan's launches (1,999 reads: 24 us in five
+// launches, now one of 7).
+template <uint32_t kPrepReads, uint32_t kThreads, bool kOne>
+__global__ __launch_bounds__(kThreads) void k_batch_prep(const InputHdr *in, uint32_t mw, uint32_t rw, uint32_t tile,
+                                                         BatchBufs bb, int prescout, uint64_t *__restrict__ part) {
+    constexpr uint32_t kWaves = kThreads / 64;
     const uint64_t n = in->n;
     const uint64_t *__restrict__ offs = in->offs;
     const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     bool real[kPrepReads];
     uint32_t cls[kPrepReads];
+    uint64_t extra[kPrepReads];
 #pragma unroll
     for (uint32_t k = 0; k < kPrepReads; k++) {
-        const uint64_t i = ((uint64_t)blockIdx.x * kPrepReads + k) * blockDim.x + threadIdx.x;
+        const uint64_t i = ((uint64_t)blockIdx.x * kPrepReads + k) * kThreads + threadIdx.x;
         real[k] = i < n;
         cls[k] = 0;
+        extra[k] = 0;
         if (real[k] && prescout && !(bb.live[i] & 1u)) {
-            bb.extra[i] = 0;
             real[k] = false;
         } else if (real[k]) {
             const uint64_t beg = offs[i], end = offs[i + 1];
             const uint64_t nw = n_windows(beg, end > beg ? end : beg);
             const uint64_t tiles = nw ? (nw + tile - 1) / tile : 1;
-            bb.extra[i] = tiles - 1;
+            extra[k] = tiles - 1;
             if (tiles > 1) {
                 bb.done[i] = 0;
                 for (uint32_t w = 0; w < mw; w++)
@@ -76,13 +82,14 @@ __global__ __launch_bounds__(256) void k_batch_prep(const InputHdr *in, uint32_t
             }
             cls[k] = (uint32_t)min<uint64_t>(3, min<uint64_t>(nw, tile) * 4 / tile);
         }
+        if (!kOne && i < n) bb.extra[i] = extra[k];
     }
     // slots in the class lists, in read order: ranks within the wave
     // (ballots), offsets of the earlier (read group, wave) pairs of the
     // workgroup (LDS), one atomic per class and workgroup
-    __shared__ uint32_t wcount[kPrepReads][4][4];  // [read group][wave][class]
-    __shared__ unsigned long long bbase[4];
-    uint64_t mine[kPrepReads];
+    __shared__ uint32_t wcount[kPrepReads][kWaves][4];  // [read group][wave][class]
+    __shared__ unsigned long long bbase[4], esum[kPrepReads][kWaves];
+    uint64_t mine[kPrepReads], eincl[kPrepReads];
 #pragma unroll
     for (uint32_t k = 0; k < kPrepReads; k++) {
         mine[k] = 0;
@@ -91,26 +98,54 @@ __global__ __launch_bounds__(256) void k_batch_prep(const InputHdr *in, uint32_t
             if (cls[k] == v) mine[k] = mask;
             if (lane == 0) wcount[k][wave][v] = (uint32_t)__popcll(mask);
         }
+        uint64_t e = extra[k];
+        if (__ballot(e != 0)) {
+#pragma unroll
+            for (int d = 1; d < 64; d <<= 1) {
+                const uint64_t y = __shfl_up(e, d);
+                if ((int)lane >= d) e += y;
+            }
+        }
+        eincl[k] = e;
+        if (lane == 63) esum[k][wave] = e;
     }
     __syncthreads();
-    const uint32_t waves = blockDim.x >> 6;
     if (threadIdx.x < 4) {
         const uint32_t v = threadIdx.x;
         uint32_t tot = 0;
         for (uint32_t k = 0; k < kPrepReads; k++)
-            for (uint32_t w = 0; w < waves; w++) tot += wcount[k][w][v];
-        bbase[v] = tot ? atomicAdd(bb.cls + 16 * v, (unsigned long long)tot) : 0ull;
+            for (uint32_t w = 0; w < kWaves; w++) tot += wcount[k][w][v];
+        if constexpr (kOne) {
+            bbase[v] = 0;
+            bb.cls[16 * v] = tot;
+        } else {
+            bbase[v] = tot ? atomicAdd(bb.cls + 16 * v, (unsigned long long)tot) : 0ull;
+        }
+    }
+    if (kOne && threadIdx.x == 4) *bb.head = 0;
+    if (!kOne && threadIdx.x == 64) {
+        uint64_t sum = 0;
+        for (uint32_t k = 0; k < kPrepReads; k++)
+            for (uint32_t w = 0; w < kWaves; w++) sum += esum[k][w];
+        part[blockIdx.x] = sum;
     }
     __syncthreads();
 #pragma unroll
     for (uint32_t k = 0; k < kPrepReads; k++) {
+        const uint64_t i = ((uint64_t)blockIdx.x * kPrepReads + k) * kThreads + threadIdx.x;
+        if constexpr (kOne) {
+            uint64_t before = 0;
+            for (uint32_t j = 0; j < k * kWaves + wave; j++) before += esum[j / kWaves][j % kWaves];
+            if (i < n) bb.extra_off[i] = before + eincl[k] - extra[k];
+            if (i + 1 == n) bb.extra_off[n] = before + eincl[k];
+            if (n == 0 && i == 0) bb.extra_off[0] = 0;
+        }
         if (!real[k]) continue;
         const uint32_t c = cls[k];
         uint64_t slot = bbase[c] + __popcll(mine[k] & ((1ULL << lane) - 1));
         for (uint32_t kk = 0; kk < k; kk++)
-            for (uint32_t w = 0; w < waves; w++) slot += wcount[kk][w][c];
+            for (uint32_t w = 0; w < kWaves; w++) slot += wcount[kk][w][c];
         for (uint32_t w = 0; w < wave; w++) slot += wcount[k][w][c];
-        const uint64_t i = ((uint64_t)blockIdx.x * kPrepReads + k) * blockDim.x + threadIdx.x;
         bb.order[(uint64_t)c * bb.cap + slot] = (uint32_t)i;
     }
 }
@@ -175,6 +210,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu((NARROW && 
     const uint64_t stride = (uint64_t)gridDim.x * GPB;
     __shared__ unsigned long long blk_issued;
     if (threadIdx.x == 0) blk_issued = 0;
+    // (the queue that is built next starts empty)
+    if (blockIdx.x == 0 && threadIdx.x == 0) *bb.head = 0;
+    if (blockIdx.x == 0 && threadIdx.x < 4) bb.cls[16 * threadIdx.x] = 0;
     __syncthreads();
     uint64_t issued = 0;
 
@@ -476,11 +514,26 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(G == 1 ? 1 
 }
 
 
+// Windows per work item: the tuned tile, or fewer where a batch of cap reads
+// would leave the chip waiting for its last items -- a tile takes about as long
+// as G (lanes that split a row) times its windows, the batch as long as its
+// reads. Best tiles of 64 .. 2,048 measured: G=1 512 at 500 to 8,000 reads,
+// 1,024 at 30,000, 2,048 at 100,000; G=8 64 at 64 to 8,000 reads, 128 at 30,000,
+// 256 at 100,000, 512 at 300,000 (2,000 reads at K=10,000: 111 us with 512,
+// 135 with 1,024; 8,000 at K=101,000: 147 with 64, 239 with 1,024).
+static uint32_t batch_tile(const rambo_s *h, const Tune &tu, uint64_t cap) {
+    const uint64_t G = std::max<uint64_t>(1, h->RW / (uint32_t)tu.seg);
+    uint64_t t = std::max<uint64_t>(64, 512 / G);
+    while (2 * t <= cap / (48 * G)) t *= 2;
+    return (uint32_t)std::min<uint64_t>(t, (uint64_t)tu.tile);
+}
+
 static int enqueue_prep(rambo_s *h, const Tune &tu, BatchGraph &bg, uint64_t *out, const IdsOut &io,
                         hipStream_t s) {
     const uint32_t mw = h->R * h->RW;
     const bool pre = tu.sched == SCHED_SCOUT;
-    hipLaunchKernelGGL(k_batch_reset, dim3(1), dim3(64), 0, s, bg.bb);
+    const bool one = bg.cap <= 4096;
+    if (!pre && !one) hipLaunchKernelGGL(k_batch_reset, dim3(1), dim3(64), 0, s, bg.bb);
     HIP_CHECK(hipGetLastError());
     if (pre) {
         const Index ix = make_index(h);
@@ -509,17 +562,26 @@ static int enqueue_prep(rambo_s *h, const Tune &tu, BatchGraph &bg, uint64_t *ou
 #undef RAMBO_SPLIT_BODY_
         HIP_CHECK(hipGetLastError());
     }
+    const uint32_t tile = batch_tile(h, tu, bg.cap);
+    if (one) {
+        hipLaunchKernelGGL((k_batch_prep<4, 1024, true>), dim3(1), dim3(1024), 0, s, bg.in, mw, h->RW, tile, bg.bb,
+                           pre ? 1 : 0, bg.parts);
+        HIP_CHECK(hipGetLastError());
+        return RAMBO_OK;
+    }
     // four reads per thread once one per thread would take over eight
     // workgroups per compute unit
-    if ((bg.cap + 255) / 256 > 8 * (uint64_t)h->n_cu)
-        hipLaunchKernelGGL(k_batch_prep<4>, dim3((unsigned)((bg.cap + 1023) / 1024)), dim3(256), 0, s, bg.in, mw,
-                           h->RW, (uint32_t)tu.tile, bg.bb, pre ? 1 : 0);
+    const uint32_t per = (bg.cap + 255) / 256 > 8 * (uint64_t)h->n_cu ? 4 : 1;
+    const dim3 grid((unsigned)((bg.cap + 256 * per - 1) / (256 * per)));
+    if (per == 4)
+        hipLaunchKernelGGL((k_batch_prep<4, 256, false>), grid, dim3(256), 0, s, bg.in, mw, h->RW, tile, bg.bb,
+                           pre ? 1 : 0, bg.parts);
     else
-        hipLaunchKernelGGL(k_batch_prep<1>, dim3((unsigned)((bg.cap + 255) / 256)), dim3(256), 0, s, bg.in, mw,
-                           h->RW, (uint32_t)tu.tile, bg.bb, pre ? 1 : 0);
+        hipLaunchKernelGGL((k_batch_prep<1, 256, false>), grid, dim3(256), 0, s, bg.in, mw, h->RW, tile, bg.bb,
+                           pre ? 1 : 0, bg.parts);
     HIP_CHECK(hipGetLastError());
     // the header's first field is n
-    return launch_exclusive_scan(bg.bb.extra, &bg.in->n, bg.cap, bg.bb.extra_off, bg.parts, s);
+    return launch_scan_parts(bg.bb.extra, &bg.in->n, bg.cap, bg.bb.extra_off, bg.parts, per, s);
 }
 
 static int enqueue_main(rambo_s *h, const Tune &tu, BatchGraph &bg, uint64_t *out, hipStream_t s,
@@ -541,7 +603,7 @@ static int enqueue_main(rambo_s *h, const Tune &tu, BatchGraph &bg, uint64_t *ou
         const int per_cu = std::max(1, std::min(fit, tu.waves_per_cu / tu.wpb));                         \
         bg.blocks = (unsigned)(h->n_cu * per_cu);                                                          \
         hipLaunchKernelGGL((k_batch_main<SEG, G>), dim3(bg.blocks), dim3(64 * tu.wpb), lds, s, ix, bg.in, out,  \
-                           bg.bb, opt, use_res, (uint32_t)tu.tile, (uint32_t)tu.grab);                     \
+                           bg.bb, opt, use_res, batch_tile(h, tu, bg.cap), (uint32_t)tu.grab);                     \
     }
     RAMBO_DISPATCH_SPLIT(tu.seg, G)
 #undef RAMBO_SPLIT_BODY_
@@ -587,7 +649,7 @@ static int alloc_graph_state(rambo_s *h, BatchGraph &bg, uint64_t cap, bool batc
         b_done = al(cap * 8);
         b_extra = al(cap * 8);
         b_off = al((cap + 1) * 8);
-        b_parts = al(scan_parts_needed(cap) * 8);
+        b_parts = al(scan_parts_needed(cap, 1) * 8);
         b_order = al(4 * cap * 4);
     }
     HIP_CHECK(hipMalloc(&bg.mem, b_mask + b_done + b_extra + b_off + b_parts + b_order + b_smask + b_live + 640 + 256));

@@ -1,0 +1,66 @@
+"""Batched form at the sizes where its queue is built another way: one workgroup
+that prepares and scans the batch (to 4,096 reads), one read per thread, four
+reads per thread; with tiles that a small batch cuts shorter (several tiles a
+read) and a batch that starts fewer items than the chip has waves; with and
+without the scout pass. Equal to the plain form, whose answers the oracle
+checks at small sizes, and to the oracle on the first reads. The no-allocation
+id lists take as many reads as they are documented to."""
+import numpy as np
+import pytest
+
+import gen
+from paper_1910_04358_amd import rambo as rb
+from tests.gpu_util import build_gpu_seqs, build_oracle, reads_to_dev, to_host_u64
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("B,n", [(100, 1), (100, 4096), (100, 4097), (100, 600_000), (300, 4095), (300, 70_000)])
+def test_batch_sizes_equal_plain_form(B, n):
+    import torch
+    K, R, m, eta, seed = 70, 3, 1 << 18, 2, 8800 + B
+    dm = gen.DocModel(seed=B + 9, n_docs=K, length=3_000, docs_per_anc=7, mu_lo=0.01, mu_hi=0.01)
+    idx = rb.Rambo(K, B, R, m, eta, seed)
+    build_gpu_seqs(idx, dm, 0, K)
+    rm = gen.ReadModel(qseed=n, src_lo=0, src_hi=K, len_kind=0, median=90, sigma=0.9, lo=20, hi=2_900, err_lo=0.0,
+                       err_hi=0.003)
+    r = gen.reads(dm, rm, n)
+    seqs, offs = reads_to_dev(r)
+    idx.set_mode(rb.MODE_PLAIN)
+    want = idx.query_seqs(seqs, offs).clone()
+    k = min(n, 500)
+    o = build_oracle((K, B, R, m, eta, seed), dm)
+    ow, _ = o.query_seqs(r.seqs, r.offsets[:k + 1])
+    assert np.array_equal(to_host_u64(want[:k]), ow)
+    idx.set_mode(rb.MODE_BATCHED)
+    for sched in (2, 1):
+        for tile in (64, 2048):
+            t = idx.get_tune()
+            t.seg, t.tile, t.sched = 4, tile, sched
+            idx.set_tune(t)
+            for _ in range(2):
+                got = idx.query_seqs(seqs, offs, check=False)
+                assert torch.equal(got, want), (sched, tile)
+    ids, off = idx.query_seqs_ids(seqs, offs, ids_cap=80 * n + 64, check=False)
+    bits = np.unpackbits(to_host_u64(want).view(np.uint8), axis=1, bitorder="little")[:, :K]
+    assert np.array_equal(np.diff(off.cpu().numpy()), bits.sum(axis=1))
+    assert np.array_equal(ids.cpu().numpy(), np.nonzero(bits)[1])
+    idx.sync()
+    idx.close()
+
+
+def test_noalloc_takes_its_documented_number_of_reads():
+    import ctypes
+    import torch
+    n = 1 << 20
+    idx = rb.Rambo(40, 8, 2, 1 << 12, 2, 8901)
+    offs = torch.arange(n + 1, dtype=torch.int64, device="cuda")  # reads of one base: no window, every document
+    seqs = torch.full((n,), 65, dtype=torch.uint8, device="cuda")
+    bits = torch.empty((n, idx.W), dtype=torch.int64, device="cuda")
+    ids = torch.empty(40 * n, dtype=torch.int32, device="cuda")
+    off = torch.empty(n + 1, dtype=torch.int64, device="cuda")
+    p = [ctypes.c_void_p(t.data_ptr()) for t in (seqs, offs)] + [n] + [ctypes.c_void_p(t.data_ptr()) for t in (bits, ids, off)]
+    torch.cuda.synchronize()
+    assert rb.lib().rambo_query_seqs_ids_noalloc(idx._h, *p, 40 * n, None) == rb.OK_EMPTYQ
+    assert int(off[-1]) == 40 * n and torch.equal(ids.view(n, 40)[n - 1].cpu(), torch.arange(40, dtype=torch.int32))
+    idx.close()
