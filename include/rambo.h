@@ -38,10 +38,9 @@
  *    queries that hold no term (RAMBO_OK_EMPTYQ, not an error).
  *  - Queries may run concurrently on one handle. Insertions and queries must
  *    be ordered by the caller; a query that overlaps an insertion is
- *    unsupported. Batched-form queries with the same (seqs, offsets, n, out)
- *    share one captured graph and its work-queue state, so calls that
- *    overlap in time need distinct output buffers (they would write the same
- *    output anyway).
+ *    unsupported. Batched-form queries take their work-queue state from the
+ *    handle (up to 16 states, of the size of the batches met, kept until it is
+ *    destroyed or folded): calls that overlap in time take different ones.
  */
 #ifndef RAMBO_H
 #define RAMBO_H
@@ -74,7 +73,7 @@ enum {
 enum {
     RAMBO_MODE_PLAIN = 0,   /* one launch, one wavefront per read */
     RAMBO_MODE_BATCHED = 1, /* persistent launch over (read, k-mer tile) work
-                               items, replayed from a captured HIP graph */
+                               items (the plain form under graph capture) */
 };
 
 /* Resolve strategies (Section 3.3, Algorithm 2: union of the documents of
@@ -424,10 +423,9 @@ int rambo_autotune(rambo_t *h, const uint8_t *seqs, const uint64_t *offsets, uin
 int rambo_get_tune(const rambo_t *h, rambo_tune_t *out);
 
 /* Device time of the most recent batched launch on this handle, from HIP
- * events recorded inside its graph: the whole graph (graph_ms) and its
- * persistent query kernel alone (kernel_ms). Waits for that launch.
- * RAMBO_EINVAL if no batched launch has run or the runtime could not record
- * events inside the graph. */
+ * events around its parts: the whole batch (graph_ms) and its persistent query
+ * kernel alone (kernel_ms). Waits for that launch. RAMBO_EINVAL if no batched
+ * launch has run. */
 int rambo_last_batch_ms(rambo_t *h, float *graph_ms, float *kernel_ms);
 int rambo_set_tune(rambo_t *h, const rambo_tune_t *t);
 

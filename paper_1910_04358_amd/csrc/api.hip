@@ -500,7 +500,6 @@ RAMBO_API int rambo_set_resolve(rambo_t *h, int resolve) {
         return fail(RAMBO_EINVAL, "rambo_set_resolve: bad strategy");
     std::lock_guard<std::mutex> g(h->mu);
     h->resolve = resolve;
-    drop_graphs(h);
     return RAMBO_OK;
 }
 
@@ -508,7 +507,6 @@ RAMBO_API int rambo_set_early_exit(rambo_t *h, int on) {
     if (!h) return fail(RAMBO_EINVAL, "rambo_set_early_exit: null handle");
     std::lock_guard<std::mutex> g(h->mu);
     h->early_exit = on ? 1 : 0;
-    drop_graphs(h);
     return RAMBO_OK;
 }
 
@@ -516,7 +514,6 @@ RAMBO_API int rambo_set_sparse_counter(rambo_t *h, uint64_t *device_counters) {
     if (!h) return fail(RAMBO_EINVAL, "rambo_set_sparse_counter: null handle");
     std::lock_guard<std::mutex> g(h->mu);
     h->sparse_counter = (unsigned long long *)device_counters;
-    drop_graphs(h);
     return RAMBO_OK;
 }
 
@@ -524,7 +521,6 @@ RAMBO_API int rambo_set_probe_counter(rambo_t *h, uint64_t *device_counter) {
     if (!h) return fail(RAMBO_EINVAL, "rambo_set_probe_counter: null handle");
     std::lock_guard<std::mutex> g(h->mu);
     h->probe_counter = (unsigned long long *)device_counter;
-    drop_graphs(h);
     return RAMBO_OK;
 }
 

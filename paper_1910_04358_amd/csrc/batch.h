@@ -22,33 +22,37 @@ struct BatchBufs {
     uint64_t cap;
 };
 
-// Captured graphs for one batch description: prep (per-read tile counts and
-// their scan; absent for the plain form) and the query kernel. The batch is
-// read from the device header `in`, so the graphs serve any batch of up to
-// cap reads placed anywhere the header points.
+// Work-queue state for batches of up to cap reads, with the captured graphs of
+// the server's slots (prep: scout pass and queue; absent for the plain form) or,
+// for the query entry point, without any: its launches are direct. The batch is
+// described by the device header `in`, which the server copies and a direct
+// launch's first kernel writes (own).
 struct BatchGraph {
     uint64_t cap = 0;
     unsigned blocks = 0;  // workgroups of the persistent launch
     Tune tune;
     BatchBufs bb{};
     const InputHdr *in = nullptr;  // device
+    InputHdr *own = nullptr;
     uint64_t *parts = nullptr;     // scan scratch
     void *mem = nullptr;
     hipGraph_t graph_prep = nullptr, graph_main = nullptr;
     hipGraphExec_t exec_prep = nullptr, exec_main = nullptr;
     bool timed = false;
     hipEvent_t ev[3] = {nullptr, nullptr, nullptr};  // before prep, before main, after main
+    hipStream_t stream = nullptr;                    // of the last direct launch
+    bool used = false;                               // there was one
     ~BatchGraph();
 };
 
-// Persistent batched form for batches described by in_dev (device; or, if
-// null, by an owned header set once to *init), up to cap reads.
-int make_batch_graph(rambo_s *h, const Tune &tu, const InputHdr *in_dev, const InputHdr *init, uint64_t cap,
-                     uint64_t *out, std::shared_ptr<BatchGraph> &res, const IdsOut &io = IdsOut());
+// Persistent batched form, captured, for batches described by in_dev (device),
+// up to cap reads.
+int make_batch_graph(rambo_s *h, const Tune &tu, const InputHdr *in_dev, uint64_t cap, uint64_t *out,
+                     std::shared_ptr<BatchGraph> &res);
 // One-node graph of the plain kernel for batches described by in_dev.
 int make_plain_graph(rambo_s *h, const InputHdr *in_dev, uint64_t cap, uint64_t *out,
                      std::shared_ptr<BatchGraph> &res);
-// Enqueue the graphs on s with the timing events between them.
+// Enqueue the graphs on s.
 int launch_batch_graph(rambo_s *h, BatchGraph &bg, hipStream_t s);
 bool tune_valid(const rambo_s *h, const Tune &t);
 int autotune(rambo_s *h, const uint8_t *seqs, const uint64_t *offs, uint64_t n, uint64_t *out, hipStream_t s);

@@ -1,7 +1,6 @@
 // Batched sequence queries: a scout pass over every read (scout schedule),
 // then one persistent launch over a work queue of (read, tile of windows)
-// items of the reads still alive, replayed from captured HIP graphs, with a
-// launch shape chosen by an autotuner.
+// items of the reads still alive, with a launch shape chosen by an autotuner.
 //
 // Most reads end on their scout windows (Section 3.3.1: once a term has
 // emptied the running intersection, no later term can bring a document
@@ -14,7 +13,8 @@
 // that finishes a read's last tile resolves it.
 //
 // The batch size lives in device memory, so one captured graph serves any
-// batch up to its capacity (the serving loop's slots rely on this).
+// batch up to its capacity (the serving loop's slots rely on this). The query
+// entry point launches the same kernels directly.
 #include <algorithm>
 #include <cstdio>
 #include <cstdlib>
@@ -35,8 +35,10 @@ namespace rambo {
 // which may empty the read's masks and let them skip), then classes 2, 1, 0.
 // (the four class counters are 128 bytes apart: their atomics use different
 // cache lines)
-__global__ void k_batch_reset(BatchBufs bb) {
+// A direct launch's header (own): written by its first kernel.
+__global__ void k_batch_reset(BatchBufs bb, InputHdr val, InputHdr *own) {
     if (threadIdx.x == 0) *bb.head = 0;
+    if (threadIdx.x == 0 && own) *own = val;
     if (threadIdx.x < 4) bb.cls[16 * threadIdx.x] = 0;
 }
 
@@ -197,12 +199,14 @@ __device__ __forceinline__ uint32_t scout_pos32(uint32_t nw, uint32_t k) { retur
 // (K=101,000: 0.44 -> 0.39 ms).
 template <int SEG, int G, int NARROW>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu((NARROW && G >= 8) ? 8 : 1))) void k_batch_scout(Index ix, const InputHdr *in, uint64_t *__restrict__ out,
-                                                     BatchBufs bb, QueryOpts opt) {
+                                                     BatchBufs bb, QueryOpts opt, InputHdr val, InputHdr *own) {
     constexpr int GS = scout_group(G, NARROW != 0);  // lanes per read
     constexpr int SLOTS = GS / G;                   // windows per round
-    const uint8_t *__restrict__ seqs = in->seqs;
-    const uint64_t *__restrict__ offs = in->offs;
-    const uint64_t n = in->n;
+    const InputHdr hd = own ? val : *in;
+    const uint8_t *__restrict__ seqs = hd.seqs;
+    const uint64_t *__restrict__ offs = hd.offs;
+    const uint64_t n = hd.n;
+    if (own && blockIdx.x == 0 && threadIdx.x == 0) *own = val;
     const uint32_t lane = threadIdx.x & 63;
     const uint32_t sub = lane % GS, seg = sub % G, slot = sub / G;
     const uint64_t gmask = (GS >= 64) ? ~0ULL : (((1ULL << GS) - 1) << (lane - sub));  // the group's lanes
@@ -528,12 +532,30 @@ static uint32_t batch_tile(const rambo_s *h, const Tune &tu, uint64_t cap) {
     return (uint32_t)std::min<uint64_t>(t, (uint64_t)tu.tile);
 }
 
-static int enqueue_prep(rambo_s *h, const Tune &tu, BatchGraph &bg, uint64_t *out, const IdsOut &io,
-                        hipStream_t s) {
+// Resident workgroups per compute unit of a kernel at a launch shape, asked of
+// the runtime once per shape.
+template <class F>
+static int resident(rambo_s *h, uint64_t key, F kernel, int threads, size_t lds, int *fit) {
+    auto it = h->resident.find(key);
+    if (it == h->resident.end()) {
+        int f = 0;
+        HIP_CHECK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&f, kernel, threads, lds));
+        it = h->resident.emplace(key, std::max(1, f)).first;
+    }
+    *fit = it->second;
+    return RAMBO_OK;
+}
+
+// Scout pass and queue of a batch of up to n reads (n <= bg.cap); with val, a
+// direct launch of that batch.
+static int enqueue_prep(rambo_s *h, const Tune &tu, BatchGraph &bg, uint64_t n, const InputHdr *val, uint64_t *out,
+                        const IdsOut &io, hipStream_t s) {
     const uint32_t mw = h->R * h->RW;
     const bool pre = tu.sched == SCHED_SCOUT;
-    const bool one = bg.cap <= 4096;
-    if (!pre && !one) hipLaunchKernelGGL(k_batch_reset, dim3(1), dim3(64), 0, s, bg.bb);
+    const bool one = n <= 4096;
+    const InputHdr hd = val ? *val : InputHdr{};
+    InputHdr *own = val ? bg.own : nullptr;
+    if (!pre && (!one || own)) hipLaunchKernelGGL(k_batch_reset, dim3(1), dim3(64), 0, s, bg.bb, hd, own);
     HIP_CHECK(hipGetLastError());
     if (pre) {
         const Index ix = make_index(h);
@@ -541,28 +563,30 @@ static int enqueue_prep(rambo_s *h, const Tune &tu, BatchGraph &bg, uint64_t *ou
         // a grid of what fits on the device at once strides over the reads
         const bool narrow = io.counts != nullptr;
         const uint64_t GS = (uint64_t)scout_group(G, narrow);
-        int fit = 0;
+        int fit = 0, st = RAMBO_OK;
+        const uint64_t key = ((uint64_t)G << 16) | ((uint64_t)tu.seg << 8) | (narrow ? 2u : 1u);
 #define RAMBO_SPLIT_BODY_                                                                                    \
-    HIP_CHECK(hipOccupancyMaxActiveBlocksPerMultiprocessor(                                                  \
-        &fit, narrow ? k_batch_scout<SEG, G, 1> : k_batch_scout<SEG, G, 0>, 256, 0))
+    st = narrow ? resident(h, key, k_batch_scout<SEG, G, 1>, 256, 0, &fit)                                   \
+                : resident(h, key, k_batch_scout<SEG, G, 0>, 256, 0, &fit)
         RAMBO_DISPATCH_SPLIT(tu.seg, G)
 #undef RAMBO_SPLIT_BODY_
+        if (st != RAMBO_OK) return st;
         const uint64_t blocks = std::max<uint64_t>(
-            1, std::min<uint64_t>((bg.cap * GS + 255) / 256, (uint64_t)std::max(1, fit) * h->n_cu));
+            1, std::min<uint64_t>((n * GS + 255) / 256, (uint64_t)fit * h->n_cu));
         QueryOpts opt{h->resolve, h->early_exit, h->probe_counter, tu.sched, io.counts,
                       io.counts ? io.noterm : h->d_emptyq};
 #define RAMBO_SPLIT_BODY_                                                                                   \
     if (narrow)                                                                                             \
         hipLaunchKernelGGL((k_batch_scout<SEG, G, 1>), dim3((unsigned)blocks), dim3(256), 0, s, ix, bg.in, out,   \
-                           bg.bb, opt);                                                                      \
+                           bg.bb, opt, hd, own);                                                             \
     else                                                                                                     \
         hipLaunchKernelGGL((k_batch_scout<SEG, G, 0>), dim3((unsigned)blocks), dim3(256), 0, s, ix, bg.in, out,   \
-                           bg.bb, opt)
+                           bg.bb, opt, hd, own)
         RAMBO_DISPATCH_SPLIT(tu.seg, G)
 #undef RAMBO_SPLIT_BODY_
         HIP_CHECK(hipGetLastError());
     }
-    const uint32_t tile = batch_tile(h, tu, bg.cap);
+    const uint32_t tile = batch_tile(h, tu, n);
     if (one) {
         hipLaunchKernelGGL((k_batch_prep<4, 1024, true>), dim3(1), dim3(1024), 0, s, bg.in, mw, h->RW, tile, bg.bb,
                            pre ? 1 : 0, bg.parts);
@@ -571,8 +595,8 @@ static int enqueue_prep(rambo_s *h, const Tune &tu, BatchGraph &bg, uint64_t *ou
     }
     // four reads per thread once one per thread would take over eight
     // workgroups per compute unit
-    const uint32_t per = (bg.cap + 255) / 256 > 8 * (uint64_t)h->n_cu ? 4 : 1;
-    const dim3 grid((unsigned)((bg.cap + 256 * per - 1) / (256 * per)));
+    const uint32_t per = (n + 255) / 256 > 8 * (uint64_t)h->n_cu ? 4 : 1;
+    const dim3 grid((unsigned)((n + 256 * per - 1) / (256 * per)));
     if (per == 4)
         hipLaunchKernelGGL((k_batch_prep<4, 256, false>), grid, dim3(256), 0, s, bg.in, mw, h->RW, tile, bg.bb,
                            pre ? 1 : 0, bg.parts);
@@ -580,11 +604,11 @@ static int enqueue_prep(rambo_s *h, const Tune &tu, BatchGraph &bg, uint64_t *ou
         hipLaunchKernelGGL((k_batch_prep<1, 256, false>), grid, dim3(256), 0, s, bg.in, mw, h->RW, tile, bg.bb,
                            pre ? 1 : 0, bg.parts);
     HIP_CHECK(hipGetLastError());
-    // the header's first field is n
-    return launch_scan_parts(bg.bb.extra, &bg.in->n, bg.cap, bg.bb.extra_off, bg.parts, per, s);
+    // the header's first field is the number of reads
+    return launch_scan_parts(bg.bb.extra, &bg.in->n, n, bg.bb.extra_off, bg.parts, per, s);
 }
 
-static int enqueue_main(rambo_s *h, const Tune &tu, BatchGraph &bg, uint64_t *out, hipStream_t s,
+static int enqueue_main(rambo_s *h, const Tune &tu, BatchGraph &bg, uint64_t n, uint64_t *out, hipStream_t s,
                         const IdsOut &io) {
     const Index ix = make_index(h);
     const uint32_t mw = h->R * h->RW;
@@ -596,14 +620,16 @@ static int enqueue_main(rambo_s *h, const Tune &tu, BatchGraph &bg, uint64_t *ou
     QueryOpts opt{h->resolve, h->early_exit, h->probe_counter, ksched, io.counts,
                   io.counts ? io.noterm : h->d_emptyq, nullptr, io.counts ? io.wm : nullptr};
     // a persistent grid must be resident: never more workgroups than fit
+    const uint64_t key = ((uint64_t)lds << 32) | ((uint64_t)G << 16) | ((uint64_t)tu.seg << 8) | (uint64_t)(4 + tu.wpb);
 #define RAMBO_SPLIT_BODY_                                                                                  \
     {                                                                                                      \
         int fit = 0;                                                                                       \
-        HIP_CHECK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&fit, k_batch_main<SEG, G>, 64 * tu.wpb, lds)); \
+        const int st = resident(h, key, k_batch_main<SEG, G>, 64 * tu.wpb, lds, &fit);                     \
+        if (st != RAMBO_OK) return st;                                                                     \
         const int per_cu = std::max(1, std::min(fit, tu.waves_per_cu / tu.wpb));                         \
         bg.blocks = (unsigned)(h->n_cu * per_cu);                                                          \
         hipLaunchKernelGGL((k_batch_main<SEG, G>), dim3(bg.blocks), dim3(64 * tu.wpb), lds, s, ix, bg.in, out,  \
-                           bg.bb, opt, use_res, batch_tile(h, tu, bg.cap), (uint32_t)tu.grab);                     \
+                           bg.bb, opt, use_res, batch_tile(h, tu, n), (uint32_t)tu.grab);                  \
     }
     RAMBO_DISPATCH_SPLIT(tu.seg, G)
 #undef RAMBO_SPLIT_BODY_
@@ -636,9 +662,8 @@ static int capture(rambo_s *h, hipGraph_t *g, hipGraphExec_t *exec, const std::f
     return RAMBO_OK;
 }
 
-// Graph state and, without an external header, an owned one set to *init.
-static int alloc_graph_state(rambo_s *h, BatchGraph &bg, uint64_t cap, bool batch_bufs, const InputHdr *in_dev,
-                             const InputHdr *init) {
+// Queue state for up to cap reads; without an external header, one of its own.
+static int alloc_state(rambo_s *h, BatchGraph &bg, uint64_t cap, bool batch_bufs, const InputHdr *in_dev) {
     const size_t mw = (size_t)h->R * h->RW;
     auto al = [](size_t x) { return (x + 255) & ~(size_t)255; };
     size_t b_mask = 0, b_done = 0, b_extra = 0, b_off = 0, b_parts = 0, b_order = 0, b_smask = 0, b_live = 0;
@@ -652,7 +677,12 @@ static int alloc_graph_state(rambo_s *h, BatchGraph &bg, uint64_t cap, bool batc
         b_parts = al(scan_parts_needed(cap, 1) * 8);
         b_order = al(4 * cap * 4);
     }
-    HIP_CHECK(hipMalloc(&bg.mem, b_mask + b_done + b_extra + b_off + b_parts + b_order + b_smask + b_live + 640 + 256));
+    const size_t total = b_mask + b_done + b_extra + b_off + b_parts + b_order + b_smask + b_live + 640 + 256;
+    if (hipMalloc(&bg.mem, total) != hipSuccess) {
+        (void)hipGetLastError();
+        bg.mem = nullptr;
+        return fail(RAMBO_ENOMEM, "cannot allocate %llu bytes for a batch's queue", (unsigned long long)total);
+    }
     char *p = (char *)bg.mem;
     bg.bb.smask = b_smask ? (uint32_t *)p : nullptr; p += b_smask;
     bg.bb.live = b_live ? (uint32_t *)p : nullptr; p += b_live;
@@ -666,33 +696,29 @@ static int alloc_graph_state(rambo_s *h, BatchGraph &bg, uint64_t cap, bool batc
     bg.bb.cls = bg.bb.head + 16;           // class v at cls[16 v]: the next four lines
     p += 640;
     bg.bb.cap = cap;
-    if (in_dev) {
-        bg.in = in_dev;
-    } else {
-        InputHdr *own = (InputHdr *)p;
-        HIP_CHECK(hipMemcpy(own, init, sizeof(InputHdr), hipMemcpyHostToDevice));
-        bg.in = own;
-    }
-    // graphs of the query entry point are timed (rambo_last_batch_ms); the
-    // server's are not (three fewer operations per batch)
+    bg.cap = cap;
+    bg.own = in_dev ? nullptr : (InputHdr *)p;
+    bg.in = in_dev ? in_dev : bg.own;
+    // launches of the query entry point are timed (rambo_last_batch_ms); the
+    // server's graphs are not (three fewer operations per batch)
     bg.timed = in_dev == nullptr;
     if (bg.timed)
         for (auto &e : bg.ev) HIP_CHECK(hipEventCreate(&e));
     return RAMBO_OK;
 }
 
-int make_batch_graph(rambo_s *h, const Tune &tu, const InputHdr *in_dev, const InputHdr *init, uint64_t cap,
-                     uint64_t *out, std::shared_ptr<BatchGraph> &res, const IdsOut &io) {
+int make_batch_graph(rambo_s *h, const Tune &tu, const InputHdr *in_dev, uint64_t cap, uint64_t *out,
+                     std::shared_ptr<BatchGraph> &res) {
     auto bg = std::make_shared<BatchGraph>();
-    bg->cap = cap;
     bg->tune = tu;
-    int st = alloc_graph_state(h, *bg, cap, true, in_dev, init);
+    std::lock_guard<std::mutex> g(h->mu);
+    int st = alloc_state(h, *bg, cap, true, in_dev);
     if (st == RAMBO_OK)
         st = capture(h, &bg->graph_prep, &bg->exec_prep,
-                     [&](hipStream_t s) { return enqueue_prep(h, tu, *bg, out, io, s); });
+                     [&](hipStream_t s) { return enqueue_prep(h, tu, *bg, cap, nullptr, out, IdsOut(), s); });
     if (st == RAMBO_OK)
         st = capture(h, &bg->graph_main, &bg->exec_main,
-                     [&](hipStream_t s) { return enqueue_main(h, tu, *bg, out, s, io); });
+                     [&](hipStream_t s) { return enqueue_main(h, tu, *bg, cap, out, s, IdsOut()); });
     if (st != RAMBO_OK) return st;
     res = bg;
     return RAMBO_OK;
@@ -701,8 +727,7 @@ int make_batch_graph(rambo_s *h, const Tune &tu, const InputHdr *in_dev, const I
 int make_plain_graph(rambo_s *h, const InputHdr *in_dev, uint64_t cap, uint64_t *out,
                      std::shared_ptr<BatchGraph> &res) {
     auto bg = std::make_shared<BatchGraph>();
-    bg->cap = cap;
-    int st = alloc_graph_state(h, *bg, cap, false, in_dev, nullptr);
+    int st = alloc_state(h, *bg, cap, false, in_dev);
     if (st == RAMBO_OK)
         st = capture(h, &bg->graph_main, &bg->exec_main, [&](hipStream_t s) {
             return launch_query_seqs_plain(h, nullptr, nullptr, cap, out, s, default_seg(h->RW), bg->in);
@@ -714,45 +739,80 @@ int make_plain_graph(rambo_s *h, const InputHdr *in_dev, uint64_t cap, uint64_t 
 
 int launch_batch_graph(rambo_s *h, BatchGraph &bg, hipStream_t s) {
     (void)h;
-    if (bg.timed) HIP_CHECK(hipEventRecord(bg.ev[0], s));
     if (bg.exec_prep) HIP_CHECK(hipGraphLaunch(bg.exec_prep, s));
-    if (bg.timed) HIP_CHECK(hipEventRecord(bg.ev[1], s));
     HIP_CHECK(hipGraphLaunch(bg.exec_main, s));
-    if (bg.timed) HIP_CHECK(hipEventRecord(bg.ev[2], s));
     return RAMBO_OK;
 }
 
-static std::string graph_key(const Tune &tu, const uint8_t *seqs, const uint64_t *offs, uint64_t n, uint64_t *out,
-                             const IdsOut &io) {
-    char buf[320];
-    snprintf(buf, sizeof buf, "%p/%p/%llu/%p/%p/%p/%d.%d.%d.%d.%d.%d", (const void *)seqs, (const void *)offs,
-             (unsigned long long)n, (void *)out, (const void *)io.counts, (const void *)io.wm, tu.seg, tu.tile,
-             tu.waves_per_cu, tu.wpb, tu.grab, tu.sched);
-    return buf;
+// Queue state for a call of n reads on stream s, from the handle's pool: one
+// whose last call was on s (the new call follows it) or has ended, of the fewest
+// reads that hold n; otherwise a new one, up to kPool of them (the ended ones
+// that are too small are freed first); otherwise the one that has waited
+// longest, which s then waits for. Called with h->mu held.
+constexpr size_t kPool = 16;
+static int take_state(rambo_s *h, uint64_t n, hipStream_t s, std::shared_ptr<BatchGraph> &res) {
+    auto &pool = h->batch_pool;
+    auto ended = [](const BatchGraph &b) { return hipEventQuery(b.ev[2]) == hipSuccess; };
+    size_t best = pool.size();
+    for (size_t k = 0; k < pool.size(); k++)
+        if (pool[k]->cap >= n && (best == pool.size() || pool[k]->cap < pool[best]->cap) &&
+            (!pool[k]->used || pool[k]->stream == s || ended(*pool[k])))
+            best = k;
+    if (best == pool.size()) {
+        (void)hipGetLastError();  // (a query that found work still running)
+        for (size_t k = 0; k < pool.size();)
+            if (pool[k]->cap < n && ended(*pool[k])) pool.erase(pool.begin() + k);
+            else k++;
+        (void)hipGetLastError();
+        if (pool.size() < kPool) {
+            auto bg = std::make_shared<BatchGraph>();
+            const int st = alloc_state(h, *bg, std::max<uint64_t>(n, 4096), true, nullptr);
+            if (st != RAMBO_OK) return st;
+            pool.push_back(bg);
+            best = pool.size() - 1;
+        } else {
+            best = 0;
+            for (size_t k = 1; k < pool.size(); k++)
+                if (pool[k]->cap > pool[best]->cap) best = k;
+            if (pool[best]->cap < n) {
+                HIP_CHECK(hipEventSynchronize(pool[best]->ev[2]));
+                auto bg = std::make_shared<BatchGraph>();
+                const int st = alloc_state(h, *bg, n, true, nullptr);
+                if (st != RAMBO_OK) return st;
+                pool[best] = bg;
+            }
+        }
+    }
+    (void)hipGetLastError();
+    res = pool[best];
+    if (res->used) HIP_CHECK(hipStreamWaitEvent(s, res->ev[2], 0));
+    return RAMBO_OK;
 }
 
-static int run_graph(rambo_s *h, const Tune &tu, const uint8_t *seqs, const uint64_t *offs, uint64_t n,
-                     uint64_t *out, hipStream_t s, const IdsOut &io = IdsOut()) {
-    std::shared_ptr<BatchGraph> bg;
+// One batch: its kernels launched directly, whatever buffers it comes in.
+static int run_batch(rambo_s *h, const Tune &tu, const uint8_t *seqs, const uint64_t *offs, uint64_t n, uint64_t *out,
+                     hipStream_t s, const IdsOut &io = IdsOut()) {
     std::lock_guard<std::mutex> g(h->mu);
-    const std::string key = graph_key(tu, seqs, offs, n, out, io);
-    auto it = h->graphs.find(key);
-    if (it != h->graphs.end()) {
-        bg = it->second;
-    } else {
-        if (h->graphs.size() >= 16) h->graphs.clear();
-        const InputHdr init{n, offs, seqs, 0};
-        int st = make_batch_graph(h, tu, nullptr, &init, n, out, bg, io);
-        if (st != RAMBO_OK) return st;
-        h->graphs[key] = bg;
+    std::shared_ptr<BatchGraph> bg;
+    int st = take_state(h, n, s, bg);
+    if (st != RAMBO_OK) return st;
+    const InputHdr val{n, offs, seqs, 0};
+    HIP_CHECK(hipEventRecord(bg->ev[0], s));
+    st = enqueue_prep(h, tu, *bg, n, &val, out, io, s);
+    if (st == RAMBO_OK) {
+        HIP_CHECK(hipEventRecord(bg->ev[1], s));
+        st = enqueue_main(h, tu, *bg, n, out, s, io);
     }
-    int st = launch_batch_graph(h, *bg, s);
+    HIP_CHECK(hipEventRecord(bg->ev[2], s));
+    bg->stream = s;
+    bg->used = true;
     if (st == RAMBO_OK) h->last_graph = bg;
     return st;
 }
 
 void drop_graphs(rambo_s *h) {
-    h->graphs.clear();
+    h->batch_pool.clear();
+    h->resident.clear();
     h->last_graph.reset();
 }
 
@@ -812,12 +872,12 @@ static int time_candidate(rambo_s *h, const Tune &tu, const uint8_t *seqs, const
     hipEvent_t a, b;
     HIP_CHECK(hipEventCreate(&a));
     HIP_CHECK(hipEventCreate(&b));
-    int st = run_graph(h, tu, seqs, offs, n, out, s);  // warm-up (and graph build)
-    if (st == RAMBO_OK) st = run_graph(h, tu, seqs, offs, n, out, s);
+    int st = run_batch(h, tu, seqs, offs, n, out, s);  // warm-up (and graph build)
+    if (st == RAMBO_OK) st = run_batch(h, tu, seqs, offs, n, out, s);
     float best = 1e30f;
     for (int rep = 0; rep < 5 && st == RAMBO_OK; rep++) {
         (void)hipEventRecord(a, s);
-        st = run_graph(h, tu, seqs, offs, n, out, s);
+        st = run_batch(h, tu, seqs, offs, n, out, s);
         (void)hipEventRecord(b, s);
         if (hipEventSynchronize(b) != hipSuccess) st = fail(RAMBO_EDEVICE, "autotune: run failed");
         float ms = 0;
@@ -881,12 +941,15 @@ int autotune(rambo_s *h, const uint8_t *seqs, const uint64_t *offs, uint64_t n, 
     }
     std::lock_guard<std::mutex> g(h->mu);
     h->tune = best;
-    drop_graphs(h);  // keep only graphs of the chosen shape
     return RAMBO_OK;
 }
 
 int query_seqs_batched(rambo_s *h, const uint8_t *seqs, const uint64_t *offs, uint64_t n, uint64_t *out,
                        hipStream_t s, const IdsOut &io) {
+    // under capture the plain kernel, which needs no state of the handle
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &cap) == hipSuccess && cap != hipStreamCaptureStatusNone)
+        return launch_query_seqs_plain(h, seqs, offs, n, out, s, default_seg(h->RW), nullptr, io);
     if (!h->tuned) {
         h->tune.seg = default_seg(h->RW);
         const char *mode = getenv("RAMBO_TUNE");
@@ -903,7 +966,7 @@ int query_seqs_batched(rambo_s *h, const uint8_t *seqs, const uint64_t *offs, ui
         std::lock_guard<std::mutex> g(h->mu);
         tu = h->tune;
     }
-    return run_graph(h, tu, seqs, offs, n, out, s, io);
+    return run_batch(h, tu, seqs, offs, n, out, s, io);
 }
 
 }  // namespace rambo
@@ -957,6 +1020,5 @@ RAMBO_API int rambo_set_tune(rambo_t *h, const rambo_tune_t *t) {
     std::lock_guard<std::mutex> g(h->mu);
     h->tune = tu;
     h->tuned = true;
-    drop_graphs(h);
     return RAMBO_OK;
 }

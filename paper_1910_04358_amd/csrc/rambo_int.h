@@ -97,8 +97,9 @@ struct rambo_s {
     bool tuned = false;
     rambo::Tune tune;
     hipStream_t aux = nullptr;  // internal stream (graph capture, sync helpers)
-    std::mutex mu;              // guards the graph cache and tuner
-    std::map<std::string, std::shared_ptr<rambo::BatchGraph>> graphs;
+    std::mutex mu;              // guards the batched form's states and tuner
+    std::vector<std::shared_ptr<rambo::BatchGraph>> batch_pool;  // queue states of the query entry point
+    std::map<uint64_t, int> resident;               // workgroups a compute unit holds, by kernel and shape
     std::shared_ptr<rambo::BatchGraph> last_graph;  // most recently launched
 };
 

@@ -430,7 +430,7 @@ static int setup_slot(rambo_server_s *s, Slot &sl) {
         int st = make_plain_graph(h, (const InputHdr *)sl.hd_stage, small_cap, sl.hd_out, sl.small);
         if (st == RAMBO_OK) st = make_plain_graph(h, (const InputHdr *)sl.d_stage, mid_cap, sl.d_out, sl.mid);
         if (st == RAMBO_OK)
-            st = make_batch_graph(h, large, (const InputHdr *)sl.d_stage, nullptr, R, sl.d_out, sl.large);
+            st = make_batch_graph(h, large, (const InputHdr *)sl.d_stage, R, sl.d_out, sl.large);
         if (st != RAMBO_OK) return st;
         // replay both graphs once on an empty batch, so that the first real
         // batch does not pay for loading their kernels

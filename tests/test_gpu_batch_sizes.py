@@ -64,3 +64,64 @@ def test_noalloc_takes_its_documented_number_of_reads():
     assert rb.lib().rambo_query_seqs_ids_noalloc(idx._h, *p, 40 * n, None) == rb.OK_EMPTYQ
     assert int(off[-1]) == 40 * n and torch.equal(ids.view(n, 40)[n - 1].cpu(), torch.arange(40, dtype=torch.int32))
     idx.close()
+
+
+def test_streams_threads_buffers_and_capture():
+    """Batches on two streams and from two threads at once, on buffers that
+    change from call to call, growing and shrinking; and a batch captured in a
+    graph and replayed."""
+    import threading
+    import torch
+    K, B, R, m, eta, seed = 70, 100, 3, 1 << 18, 2, 8950
+    dm = gen.DocModel(seed=77, n_docs=K, length=3_000, docs_per_anc=7, mu_lo=0.01, mu_hi=0.01)
+    idx = rb.Rambo(K, B, R, m, eta, seed)
+    build_gpu_seqs(idx, dm, 0, K)
+    rm = gen.ReadModel(qseed=5, src_lo=0, src_hi=K, len_kind=0, median=90, sigma=0.9, lo=20, hi=2_900, err_hi=0.003)
+    sets = [reads_to_dev(gen.reads(dm, rm, n, i0=n)) for n in (3_000, 20_000, 500, 9_000)]
+    idx.set_mode(rb.MODE_PLAIN)
+    want = [idx.query_seqs(*s).clone() for s in sets]
+    idx.set_mode(rb.MODE_BATCHED)
+    t = idx.get_tune()
+    t.seg = 4
+    idx.set_tune(t)
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    torch.cuda.synchronize()
+    got = []
+    for rep in range(12):
+        k, st = rep % 4, streams[rep % 2]
+        out = torch.full_like(want[k], -1)
+        torch.cuda.current_stream().synchronize()
+        got.append((k, idx.query_seqs(*sets[k], out=out, stream=st, check=False)))
+    torch.cuda.synchronize()
+    assert all(torch.equal(o, want[k]) for k, o in got)
+    bad = []
+
+    def work(j):
+        torch.cuda.set_device(0)
+        st = torch.cuda.Stream()
+        for rep in range(8):
+            k = (j + rep) % 4
+            out = torch.empty_like(want[k])
+            idx.query_seqs(*sets[k], out=out, stream=st, check=False)
+            st.synchronize()
+            if not torch.equal(out, want[k]):
+                bad.append((j, rep))
+
+    ts = [threading.Thread(target=work, args=(j,)) for j in range(3)]
+    for t in ts:
+        t.start()
+    for t in ts:
+        t.join()
+    assert not bad
+    g = torch.cuda.CUDAGraph()
+    out = torch.empty_like(want[1])
+    torch.cuda.synchronize()
+    with torch.cuda.graph(g):
+        idx.query_seqs(*sets[1], out=out, check=False)
+    for _ in range(3):
+        out.fill_(-1)
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, want[1])
+    idx.sync()
+    idx.close()
