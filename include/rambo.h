@@ -71,7 +71,10 @@ enum {
 
 /* Query execution forms for rambo_query_seqs. */
 enum {
-    RAMBO_MODE_PLAIN = 0,   /* one launch, one wavefront per read */
+    RAMBO_MODE_PLAIN = 0,   /* one launch, one to 16 wavefronts per read; batches
+                               of thousands of reads take the batched form's
+                               launches in their default shape, unless the
+                               stream is being captured */
     RAMBO_MODE_BATCHED = 1, /* persistent launch over (read, k-mer tile) work
                                items (the plain form under graph capture) */
 };

@@ -437,7 +437,7 @@ RAMBO_API int rambo_query_seqs(rambo_t *h, const uint8_t *seqs, const uint64_t *
     if (!seqs || !offsets || !out) return fail(RAMBO_EINVAL, "rambo_query_seqs: null array");
     if (h->opaque) return fail(RAMBO_EINVAL, "rambo_query_seqs: the index holds opaque terms, not 31-mers");
     if (h->mode == RAMBO_MODE_BATCHED) return query_seqs_batched(h, seqs, offsets, n, out, (hipStream_t)stream);
-    return launch_query_seqs_plain(h, seqs, offsets, n, out, (hipStream_t)stream, default_seg(h->RW));
+    return query_seqs_plain(h, seqs, offsets, n, out, (hipStream_t)stream);
 }
 
 RAMBO_API int rambo_query_term_sets(rambo_t *h, const uint64_t *terms, const uint64_t *offsets, uint64_t n,
@@ -484,7 +484,7 @@ RAMBO_API int rambo_query_seqs_ids(rambo_t *h, const uint8_t *seqs, const uint64
     io.noterm = h->d_invalid + 2;
     const int st = h->mode == RAMBO_MODE_BATCHED
                        ? query_seqs_batched(h, seqs, offsets, n, scratch, s, io)
-                       : launch_query_seqs_plain(h, seqs, offsets, n, scratch, s, default_seg(h->RW), nullptr, io);
+                       : query_seqs_plain(h, seqs, offsets, n, scratch, s, io);
     if (st != RAMBO_OK) return st;
     return launch_ids(h, scratch, n, ids, id_offsets, ids_cap, s, io, h->d_ids_aux, h->ids_host);
 }

@@ -51,7 +51,7 @@ __global__ void k_batch_reset(BatchBufs bb, InputHdr val, InputHdr *own) {
 // (52 -> 23 us with 4); small batches keep one read per thread (100,000
 // reads: 9 us with 1, 19 us with 4, where fewer workgroups wait longer).
 // The workgroup's sum of extra tiles goes to part, for the scan. A batch that
-// one workgroup holds (kOne, up to 4,096 reads) is scanned here too, and needs
+// one workgroup holds (kOne, up to 2,048 reads) is scanned here too, and needs
 // neither the reset nor the scan's launches (1,999 reads: 24 us in five
 // launches, now one of 7).
 template <uint32_t kPrepReads, uint32_t kThreads, bool kOne>
@@ -66,7 +66,7 @@ __global__ __launch_bounds__(kThreads) void k_batch_prep(const InputHdr *in, uin
     uint64_t extra[kPrepReads];
 #pragma unroll
     for (uint32_t k = 0; k < kPrepReads; k++) {
-        const uint64_t i = ((uint64_t)blockIdx.x * kPrepReads + k) * kThreads + threadIdx.x;
+        const uint64_t i0 = ((uint64_t)blockIdx.x * kPrepReads + k) * kThreads, i = i0 + threadIdx.x;
         real[k] = i < n;
         cls[k] = 0;
         extra[k] = 0;
@@ -77,14 +77,19 @@ __global__ __launch_bounds__(kThreads) void k_batch_prep(const InputHdr *in, uin
             const uint64_t nw = n_windows(beg, end > beg ? end : beg);
             const uint64_t tiles = nw ? (nw + tile - 1) / tile : 1;
             extra[k] = tiles - 1;
-            if (tiles > 1) {
-                bb.done[i] = 0;
-                for (uint32_t w = 0; w < mw; w++)
-                    bb.rmask[i * mw + w] = (prescout && w < rw) ? bb.smask[i * rw + w] : 0xFFFFFFFFu;
-            }
             cls[k] = (uint32_t)min<uint64_t>(3, min<uint64_t>(nw, tile) * 4 / tile);
         }
         if (!kOne && i < n) bb.extra[i] = extra[k];
+        // the multi-tile reads' masks, a wave per read (192 words each at R=6,
+        // B=1,000)
+        if (extra[k]) bb.done[i] = 0;
+        uint64_t multi = __ballot(extra[k] != 0);
+        while (multi) {
+            const uint64_t j = i0 + wave * 64 + (uint64_t)__builtin_ctzll(multi);
+            multi &= multi - 1;
+            for (uint32_t w = lane; w < mw; w += 64)
+                bb.rmask[j * mw + w] = (prescout && w < rw) ? bb.smask[j * rw + w] : 0xFFFFFFFFu;
+        }
     }
     // slots in the class lists, in read order: ranks within the wave
     // (ballots), offsets of the earlier (read group, wave) pairs of the
@@ -552,7 +557,7 @@ static int enqueue_prep(rambo_s *h, const Tune &tu, BatchGraph &bg, uint64_t n, 
                         const IdsOut &io, hipStream_t s) {
     const uint32_t mw = h->R * h->RW;
     const bool pre = tu.sched == SCHED_SCOUT;
-    const bool one = n <= 4096;
+    const bool one = n <= 2048;
     const InputHdr hd = val ? *val : InputHdr{};
     InputHdr *own = val ? bg.own : nullptr;
     if (!pre && (!one || own)) hipLaunchKernelGGL(k_batch_reset, dim3(1), dim3(64), 0, s, bg.bb, hd, own);
@@ -588,7 +593,7 @@ static int enqueue_prep(rambo_s *h, const Tune &tu, BatchGraph &bg, uint64_t n, 
     }
     const uint32_t tile = batch_tile(h, tu, n);
     if (one) {
-        hipLaunchKernelGGL((k_batch_prep<4, 1024, true>), dim3(1), dim3(1024), 0, s, bg.in, mw, h->RW, tile, bg.bb,
+        hipLaunchKernelGGL((k_batch_prep<2, 1024, true>), dim3(1), dim3(1024), 0, s, bg.in, mw, h->RW, tile, bg.bb,
                            pre ? 1 : 0, bg.parts);
         HIP_CHECK(hipGetLastError());
         return RAMBO_OK;
@@ -791,7 +796,7 @@ static int take_state(rambo_s *h, uint64_t n, hipStream_t s, std::shared_ptr<Bat
 
 // One batch: its kernels launched directly, whatever buffers it comes in.
 static int run_batch(rambo_s *h, const Tune &tu, const uint8_t *seqs, const uint64_t *offs, uint64_t n, uint64_t *out,
-                     hipStream_t s, const IdsOut &io = IdsOut()) {
+                     hipStream_t s, const IdsOut &io = IdsOut(), bool note = true) {
     std::lock_guard<std::mutex> g(h->mu);
     std::shared_ptr<BatchGraph> bg;
     int st = take_state(h, n, s, bg);
@@ -806,7 +811,7 @@ static int run_batch(rambo_s *h, const Tune &tu, const uint8_t *seqs, const uint
     HIP_CHECK(hipEventRecord(bg->ev[2], s));
     bg->stream = s;
     bg->used = true;
-    if (st == RAMBO_OK) h->last_graph = bg;
+    if (st == RAMBO_OK && note) h->last_graph = bg;
     return st;
 }
 
@@ -967,6 +972,29 @@ int query_seqs_batched(rambo_s *h, const uint8_t *seqs, const uint64_t *offs, ui
         tu = h->tune;
     }
     return run_batch(h, tu, seqs, offs, n, out, s, io);
+}
+
+// Plain-form queries: the plain kernels, or, from the size on where they no
+// longer keep the chip busy, the batched form's in their default shape -- a
+// long read is one wave's (or one workgroup's) work in the plain kernels, which
+// the others' end waits for. Measured, plain kernels against batched launches,
+// us: K=10,000 (a lane a term) 1,000 reads 62 / 86, 2,000 109 / 95, 4,000 167 /
+// 121, 16,000 554 / 290, 100,000 1,775 / 1,353; K=101,000 (8 lanes) 2,000 63 / 93,
+// 4,000 104 / 105, 8,000 203 / 106, 100,000 895 / 588. Under capture, with the
+// RAMBO+ tallies and without memory for the queue the plain kernels run.
+int query_seqs_plain(rambo_s *h, const uint8_t *seqs, const uint64_t *offs, uint64_t n, uint64_t *out, hipStream_t s,
+                     const IdsOut &io) {
+    Tune tu;
+    tu.seg = default_seg(h->RW);
+    tu.sched = h->tune.sched;
+    const bool lane_rows = h->RW <= 4;  // a lane holds a whole row
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (n > (lane_rows ? 6 : 16) * (uint64_t)h->n_cu && !h->sparse_counter &&
+        hipStreamIsCapturing(s, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone) {
+        const int st = run_batch(h, tu, seqs, offs, n, out, s, io, false);
+        if (st != RAMBO_ENOMEM) return st;
+    }
+    return launch_query_seqs_plain(h, seqs, offs, n, out, s, tu.seg, nullptr, io);
 }
 
 }  // namespace rambo

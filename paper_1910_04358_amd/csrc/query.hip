@@ -150,7 +150,7 @@ static size_t team_lds(const rambo_s *h, uint32_t waves, bool use_res) {
 // at 4,000 172-187 and 118-124, at 8,000 293-315 and 197-218.
 static uint32_t team_waves(const rambo_s *h, uint64_t n) {
     const uint64_t cu = (uint64_t)h->n_cu;
-    uint32_t t = n <= cu + cu / 8 ? 16 : n <= 2 * cu ? 8 : n <= 16 * cu ? 4 : 1;
+    uint32_t t = n <= cu + cu / 8 ? 16 : n <= 2 * cu ? 8 : n <= 16 * cu ? 4 : 1;  // (past that only under capture and the like)
     while (t > 1 && team_lds(h, t, seq_lds_result(h->W)) + 64 > h->lds_max) t /= 2;
     return t;
 }

@@ -176,6 +176,8 @@ int launch_store_u64(uint64_t *p, uint64_t v, hipStream_t s);
 // batch.hip
 int query_seqs_batched(rambo_s *h, const uint8_t *seqs, const uint64_t *offs, uint64_t n, uint64_t *out,
                        hipStream_t s, const IdsOut &io = IdsOut());
+int query_seqs_plain(rambo_s *h, const uint8_t *seqs, const uint64_t *offs, uint64_t n, uint64_t *out, hipStream_t s,
+                     const IdsOut &io = IdsOut());
 void drop_graphs(rambo_s *h);
 
 // Row split: a lane reads SEG words of a row, G = row_words / SEG lanes share
