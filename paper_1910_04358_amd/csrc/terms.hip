@@ -136,6 +136,10 @@ __device__ __forceinline__ void resolve_chunk(const TermIndex &ix, const uint64_
         for (int k = 0; k < 8; k += 2) {
             // (two words at a time, so that only their reads are in registers)
             __builtin_amdgcn_sched_barrier(0);
+            if (rec * 8 + k >= ix.W) {  // no such words
+                w[16 * h + 2 * k] = w[16 * h + 2 * k + 1] = w[16 * h + 2 * k + 2] = w[16 * h + 2 * k + 3] = 0;
+                continue;
+            }
 #pragma unroll
             for (int j = 0; j < 2; j++) {
                 uint64_t q = ~0ULL;
@@ -219,13 +223,13 @@ __device__ __forceinline__ void fill_masks(Seg<SEG> (&cm)[COUNT], uint32_t v) {
 // Rows of at most 4 words (B <= 128): a lane holds a term's whole masks, and
 // a wave resolves its own 64 terms, with T in its own LDS area.
 // Bound by random row reads (one 128-byte line each): repetition 0's rows are
-// read first, and a term that no document of the index holds (half of a
-// typical batch) mostly stops there: with B = 32 three quarters of those have
-// no positive cell left. K=1,000 (B=32, R=4, eta=3, rows of 1 GiB), 10^7
+// read first, then repetition 1's, then the others', and a term that no document
+// of the index holds (half of a typical batch) mostly stops early: with B = 32
+// three quarters of those have no positive cell left after each. K=1,000 (B=32, R=4, eta=3, rows of 1 GiB), 10^7
 // terms: 3.17 ms with all 12 rows read at once, one ballot per cell and 8-byte
 // stores; 2.35 ms in this form with 16-byte stores 128 bytes apart; 2.02 ms with
 // 64-byte, 1.83 ms with 128-byte stores (1.44 ms with none: the 1.28 GB of
-// results and the row reads share HBM).
+// results and the row reads share HBM); 1.76 ms with repetition 1 apart.
 template <int SEG>
 __global__ __launch_bounds__(256) void k_terms_lane(TermIndex ix, const uint64_t *__restrict__ terms, uint64_t n,
                                                     uint64_t *__restrict__ out, unsigned long long *invalid) {
@@ -256,7 +260,9 @@ __global__ __launch_bounds__(256) void k_terms_lane(TermIndex ix, const uint64_t
     if (go) {
         probe_reps<SEG, 0, 1>(ix, ix.hp->h, x, 0, acc);
         go = some(0);
-        if (go) probe_reps<SEG, 1, 4, 1>(ix, ix.hp->h, x, 0, acc);
+        if (go) probe_reps<SEG, 1, 1, 1>(ix, ix.hp->h, x, 0, acc);
+        go = go && some(1);
+        if (go) probe_reps<SEG, 2, 3, 2>(ix, ix.hp->h, x, 0, acc);
         if (go && ix.R > 5) probe_reps<SEG, 5, MAXR - 5, 5>(ix, ix.hp->h, x, 0, acc);
     } else {
 #pragma unroll
@@ -283,8 +289,8 @@ __global__ __launch_bounds__(256) void k_terms_lane(TermIndex ix, const uint64_t
 // resolves 64 terms; all rows of up to four repetitions are in flight at once.
 // Bound by the result stores where the index is cached (ClueWeb-like, 50,000
 // documents, R=3, B=5,000, 200,000 terms, 1.25 GB of results: 14.7 ms with a
-// candidate resolve per term, 0.66 ms now, 0.45 ms without the stores, of
-// which the probes take 0.14 ms; T is 123 KB there, one workgroup a CU).
+// candidate resolve per term, 0.64 ms now, 0.45 ms without the stores, of
+// which the probes take 0.13 ms; T is 123 KB there, one workgroup a CU).
 __global__ __launch_bounds__(1024) void k_terms_group(TermIndex ix, const uint64_t *__restrict__ terms, uint64_t n,
                                                       uint64_t *__restrict__ out, unsigned long long *invalid,
                                                       uint32_t lg) {
@@ -306,7 +312,8 @@ __global__ __launch_bounds__(1024) void k_terms_group(TermIndex ix, const uint64
     for (uint32_t t0 = wave * per; t0 < 64; t0 += waves * per) {
         const uint32_t t = t0 + g;
         const uint64_t x = __shfl(mine, (int)t);
-        const bool ok = (oks >> t) & 1;
+        // (lanes past the last cell's word have nothing to read: at B=5,000 24 of 64)
+        const bool ok = ((oks >> t) & 1) && seg * 128 < ix.B;
         {
             Seg<4> cm[4];
             fill_masks(cm, ok ? 0xFFFFFFFFu : 0u);
@@ -357,7 +364,7 @@ __device__ __forceinline__ void and_sets(const Index &ix, const uint64_t *__rest
             for (uint32_t st = 32; st; st >>= 1)
                 if (__shfl(incl, (int)(t + st - 1)) <= i) t += st;
             const uint64_t from = __shfl(src, (int)(t & 63));
-            if (i >= total) continue;
+            if (i >= total || seg * (SEG * 32) >= ix.B) continue;
             uint64_t x = terms[from + i];
             if (!ix.opaque) x = canonical(x);
             Seg<SEG> cm[COUNT];
