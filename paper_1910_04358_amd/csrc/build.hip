@@ -156,12 +156,13 @@ __global__ __launch_bounds__(256) void k_build(Index ix, Docs in, uint64_t from,
 // put together in LDS and ORed into the rows in order (k_part_apply), which
 // costs 0.8 ms a GiB. 1,000 documents of 200 kbp, R=4, eta=3 into 1 GiB of rows
 // (2.4 x 10^9 bits): 116 ms by atomics alone, 79 ms by direct insertion
-// as above, 14.6 ms partitioned.
+// as above, 14.2 ms partitioned.
 // ---------------------------------------------------------------------------
 constexpr uint32_t kBuckets = 1024;    // regions of the scatter, at most
 constexpr uint32_t kStage = 32768;     // bits staged by a scatter workgroup (128 KB of LDS), over all buckets
 constexpr uint32_t kFlush = 16;        // bits written together (64 bytes)
-constexpr uint32_t kGroupAdds = 6;     // bits a thread adds between flushes: six a bucket of 32 places, with 1,024
+constexpr uint32_t kGroupAdds = 9;     // bits a thread adds between flushes: nine a bucket of 32 places, with 1,024
+                                       // (14.2 ms for the genomes above; 14.7 with 6, 14.4 with 12, which overflow more)
 constexpr uint32_t kUnroll = 4;        // positions of a thread whose loads go together
 constexpr uint32_t kTileBits = 19;     // an apply tile: 64 KB of rows
 
