@@ -15,7 +15,7 @@ from tests.gpu_util import cuda, to_dev
 
 pytestmark = pytest.mark.gpu
 
-# (K, B, R, m, eta): documents of 60 kbp, 1.8 million positions
+# (K, B, R, m, eta): documents of 80 kbp, 2.4 million positions
 SHAPES = [
     (30, 1, 1, 1 << 17, 4),       # one-word rows, one cell
     (30, 100, 2, 100_003, 2),     # a bucket past the last row
@@ -29,7 +29,7 @@ SHAPES = [
 def test_bulk_insert_equals_oracle(shape):
     K, B, R, m, eta = shape
     seed = 8500 + B
-    dm = gen.DocModel(seed=B, n_docs=K, length=60_000, docs_per_anc=5, mu_lo=0.02, mu_hi=0.02)
+    dm = gen.DocModel(seed=B, n_docs=K, length=80_000, docs_per_anc=5, mu_lo=0.02, mu_hi=0.02)
     docs = dm.docs(0, K)
     o = oracle.Oracle(K, B, R, m, eta, seed)
     o.build_docs(docs, dm.length, 0, K)
@@ -99,7 +99,7 @@ def test_several_passes_and_ragged_documents():
 def test_two_streams_and_capture():
     import torch
     K, B, R, m, eta, seed = 64, 20, 2, 1 << 16, 3, 8602
-    parts = [ragged(s, 40, K, 60_000) for s in (2, 3, 4)]
+    parts = [ragged(s, 40, K, 80_000) for s in (2, 3, 4)]
     a, b = (rb.Rambo(K, B, R, m, eta, seed) for _ in range(2))
     dev = [tuple(to_dev(x) for x in p) for p in parts]
     streams = [torch.cuda.Stream(), torch.cuda.Stream()]
