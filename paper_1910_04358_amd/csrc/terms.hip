@@ -78,6 +78,8 @@ __device__ __forceinline__ uint64_t transpose64(uint64_t x, const Transpose &t) 
 // banks). Block k of repetition r first holds the queries' mask words (word t:
 // bits 64 k .. 64 k + 63 of query t's mask), then, transposed, its cells' query
 // sets. ix.docslot holds the documents' cells as slots c + c / 64 of this array.
+// A group of 32 queries has words of 32 bits instead: a block first holds the low
+// halves of its 32 mask words, then the high halves.
 constexpr uint32_t kBlockWords = 65;
 __host__ __device__ inline uint32_t t_blocks(uint32_t B) { return (B + 63) / 64; }
 __host__ __device__ inline uint32_t t_words(uint32_t R, uint32_t B) { return R * t_blocks(B) * kBlockWords; }
@@ -87,6 +89,13 @@ __device__ __forceinline__ void transpose_blocks(uint64_t *T, uint32_t blocks, u
     for (uint32_t k = wave; k < blocks; k += waves) {
         const uint64_t x = T[k * kBlockWords + lane];
         if (__ballot(x != 0)) T[k * kBlockWords + lane] = transpose64(x, tp);
+    }
+}
+__device__ __forceinline__ void transpose_blocks(uint32_t *T, uint32_t blocks, uint32_t wave, uint32_t waves,
+                                                 uint32_t lane, const Transpose &tp) {
+    for (uint32_t k = wave; k < blocks; k += waves) {
+        const uint32_t x = T[k * kBlockWords + lane];
+        if (__ballot(x != 0)) T[k * kBlockWords + lane] = transpose32(x, tp);
     }
 }
 
@@ -170,11 +179,73 @@ __device__ __forceinline__ void resolve_chunk(const TermIndex &ix, const uint64_
     }
 }
 
+// The same for a group of 32 queries and N = 16: the transpose takes word k of both
+// halves of the chunk at a time, so that lanes t and 32 + t end with words 0 to 7
+// and 8 to 15 of query t; the pieces' exchange has two more stages, which bring
+// the halves of a row eight lanes together again.
+template <int R, int N>
+__device__ __forceinline__ void resolve_chunk(const TermIndex &ix, const uint32_t *T, uint64_t *__restrict__ out,
+                                              uint64_t base, uint32_t nq, uint32_t c, uint32_t lane,
+                                              const Transpose &tp) {
+    static_assert(N == 16, "two records of eight words");
+    const uint32_t records = (ix.W + 7) / 8, stride = t_blocks(ix.B) * kBlockWords;
+    uint32_t slot[2][R][4], w[16];
+#pragma unroll
+    for (int h = 0; h < 2; h++)
+#pragma unroll
+        for (int r = 0; r < R; r++) {
+            const uint4 v = ix.docslot[((uint64_t)r * records + min(2 * c + h, records - 1)) * 64 + lane];
+            slot[h][r][0] = v.x; slot[h][r][1] = v.y; slot[h][r][2] = v.z; slot[h][r][3] = v.w;
+        }
+#pragma unroll
+    for (int k = 0; k < 8; k++) {
+        if (k % 2 == 0) __builtin_amdgcn_sched_barrier(0);
+        uint32_t q[2];
+#pragma unroll
+        for (int h = 0; h < 2; h++) {
+            q[h] = ~0u;
+#pragma unroll
+            for (int r = 0; r < R; r++) {
+                const uint32_t s = k % 2 ? slot[h][r][k >> 1] >> 16 : slot[h][r][k >> 1] & 0xFFFFu;
+                q[h] &= T[r * stride + s];
+            }
+            if (((uint64_t)c * 16 + 8 * h + k) * 64 + lane >= ix.K) q[h] = 0;  // (the slots past K are 0, a real cell)
+        }
+        const uint64_t v = transpose64((uint64_t)q[1] << 32 | q[0], tp);
+        w[2 * k] = (uint32_t)v;
+        w[2 * k + 1] = (uint32_t)(v >> 32);
+    }
+    transpose_pieces<4>(w, lane);  // piece i: words 8 h + 2 (lane % 4) of query (lane % 32 & ~3) + i
+    // pieces 2, 3 change places with the other half's 0, 1; then 2, 3 with lane ^ 4's 0, 1
+    const bool up = lane & 4;
+#pragma unroll
+    for (int p = 0; p < 2; p++)
+#pragma unroll
+        for (int k = 0; k < 4; k++) {
+            const auto x = __builtin_amdgcn_permlane32_swap(w[4 * p + k], w[4 * (p + 2) + k], false, false);
+            const uint32_t a = x[0], b = x[1];
+            const uint32_t o = dpp<0x141>(dpp<0x1B>(up ? a : b));
+            w[4 * p + k] = up ? o : a;
+            w[4 * (p + 2) + k] = up ? b : o;
+        }
+    const uint32_t k = c * 16 + 2 * (lane & 7);
+    const uint32_t q0 = (lane & 24) | (lane >> 5) << 1;
+#pragma unroll
+    for (uint32_t i = 0; i < 4; i++) {
+        const uint32_t q = q0 | (i & 2) << 1 | (i & 1);
+        if (q < nq) {
+            uint64_t *o = out + (base + q) * ix.W + k;
+            if (k + 1 < ix.W) __builtin_memcpy(o, w + 4 * i, 16);
+            else if (k < ix.W) __builtin_memcpy(o, w + 4 * i, 8);
+        }
+    }
+}
+
 // The documents of slice blockIdx.y, in chunks of N words, every waves-th one
 // from the wave-th: a batch of few groups is cut into slices so that it fills
 // the chip, each slice probing its group's terms again.
-template <int R, int N>
-__device__ __forceinline__ void resolve_chunks(const TermIndex &ix, const uint64_t *T, uint64_t *__restrict__ out,
+template <int R, int N, typename Q>
+__device__ __forceinline__ void resolve_chunks(const TermIndex &ix, const Q *T, uint64_t *__restrict__ out,
                                                uint64_t base, uint32_t nq, uint32_t wave, uint32_t waves,
                                                uint32_t lane, const Transpose &tp) {
     const uint32_t chunks = (ix.W + N - 1) / N, per = (chunks + gridDim.y - 1) / gridDim.y;
@@ -182,8 +253,8 @@ __device__ __forceinline__ void resolve_chunks(const TermIndex &ix, const uint64
     for (uint32_t c = c0 + wave; c < c1; c += waves) resolve_chunk<R, N>(ix, T, out, base, nq, c, lane, tp);
 }
 
-template <int N>
-__device__ __forceinline__ void resolve_group(const TermIndex &ix, const uint64_t *T, uint64_t *__restrict__ out,
+template <int N, typename Q>
+__device__ __forceinline__ void resolve_group(const TermIndex &ix, const Q *T, uint64_t *__restrict__ out,
                                               uint64_t base, uint32_t nq, uint32_t wave, uint32_t waves,
                                               uint32_t lane, const Transpose &tp) {
     switch (ix.R) {
@@ -195,9 +266,9 @@ __device__ __forceinline__ void resolve_group(const TermIndex &ix, const uint64_
 
 // Query t's masks of repetitions FIRST .. FIRST + COUNT - 1 (those below R) into
 // the blocks: this lane holds SEG consecutive row words from word seg * SEG.
-template <int SEG, int FIRST, int COUNT>
+template <int SEG, int FIRST, int COUNT, typename Q>
 __device__ __forceinline__ void store_masks(const Index &ix, const Seg<SEG> (&cm)[COUNT], uint32_t seg, uint32_t t,
-                                            uint64_t *T) {
+                                            Q *T) {
     const uint32_t nb = t_blocks(ix.B);
 #pragma unroll
     for (int i = 0; i < COUNT; i++) {
@@ -207,7 +278,10 @@ __device__ __forceinline__ void store_masks(const Index &ix, const Seg<SEG> (&cm
             const uint32_t k = (seg * SEG + s) / 2;
             uint64_t v = cm[i].w[s];
             if constexpr (SEG > 1) v |= (uint64_t)cm[i].w[s + 1] << 32;
-            if (k < nb) T[((FIRST + i) * nb + k) * kBlockWords + t] = v;
+            if (k >= nb) continue;
+            Q *b = T + ((FIRST + i) * nb + k) * kBlockWords + t;
+            b[0] = (Q)v;
+            if constexpr (sizeof(Q) == 4) b[32] = (Q)(v >> 32);
         }
     }
 }
@@ -286,22 +360,28 @@ __global__ __launch_bounds__(256) void k_terms_lane(TermIndex ix, const uint64_t
 }
 
 // Wider rows: G = 2^lg lanes share a term's row (4 words each) and a workgroup
-// resolves 64 terms; all rows of up to four repetitions are in flight at once.
-// Bound by the result stores where the index is cached (ClueWeb-like, 50,000
-// documents, R=3, B=5,000, 200,000 terms, 1.25 GB of results: 14.7 ms with a
-// candidate resolve per term, 0.64 ms now, 0.45 ms without the stores, of
-// which the probes take 0.13 ms; T is 123 KB there, one workgroup a CU).
+// resolves 64 or 32 terms (of the type Q: a bit a term); all rows of up to four
+// repetitions are in flight at once.
+// Bound by the result stores and the resolve's LDS reads where the index is cached
+// (ClueWeb-like, 50,000 documents, R=3, B=5,000, 200,000 terms, 1.25 GB of
+// results: 14.7 ms with a candidate resolve per term; 0.64 ms in groups of 64,
+// whose T of 123 KB leaves one workgroup a CU, 0.45 ms of it without the stores,
+// the probes 0.13 ms; 0.55 ms in groups of 32, two workgroups a CU, one of which
+// probes while the other stores; 0.58 ms with 24 waves a CU instead of 16, for
+// which registers are spilled).
+template <typename Q>
 __global__ __launch_bounds__(1024) void k_terms_group(TermIndex ix, const uint64_t *__restrict__ terms, uint64_t n,
                                                       uint64_t *__restrict__ out, unsigned long long *invalid,
                                                       uint32_t lg) {
     extern __shared__ uint64_t smem64[];
-    uint64_t *T = smem64;
+    constexpr uint32_t kQ = 8 * sizeof(Q);  // queries of a group
+    Q *T = (Q *)smem64;
     const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6, waves = blockDim.x >> 6;
-    const uint64_t base = (uint64_t)blockIdx.x * 64;
+    const uint64_t base = (uint64_t)blockIdx.x * kQ;
     const Transpose tp(lane);
     const uint32_t per = 64u >> lg, g = lane >> lg, seg = lane & ((1u << lg) - 1);
     uint64_t mine = 0;  // term base + lane
-    bool mine_ok = base + lane < n;
+    bool mine_ok = lane < kQ && base + lane < n;
     if (mine_ok) mine = terms[base + lane];
     if (mine_ok && !ix.opaque && (mine >> 62)) {
         mine_ok = false;
@@ -309,7 +389,7 @@ __global__ __launch_bounds__(1024) void k_terms_group(TermIndex ix, const uint64
     }
     if (!ix.opaque) mine = canonical(mine);
     const uint64_t oks = __ballot(mine_ok);
-    for (uint32_t t0 = wave * per; t0 < 64; t0 += waves * per) {
+    for (uint32_t t0 = wave * per; t0 < kQ; t0 += waves * per) {
         const uint32_t t = t0 + g;
         const uint64_t x = __shfl(mine, (int)t);
         // (lanes past the last cell's word have nothing to read: at B=5,000 24 of 64)
@@ -330,7 +410,7 @@ __global__ __launch_bounds__(1024) void k_terms_group(TermIndex ix, const uint64
     __syncthreads();
     transpose_blocks(T, ix.R * t_blocks(ix.B), wave, waves, lane, tp);
     __syncthreads();
-    resolve_group<16>(ix, T, out, base, (uint32_t)min<uint64_t>(64, n - base), wave, waves, lane, tp);
+    resolve_group<16>(ix, T, out, base, (uint32_t)min<uint64_t>(kQ, n - base), wave, waves, lane, tp);
 }
 
 // ANDs repetitions FIRST .. FIRST + COUNT - 1 of the rows of the group's sets
@@ -607,7 +687,8 @@ static TermIndex term_index(const rambo_s *h) {
 }
 
 // Launch shape of the group kernels: waves of a workgroup and slices of the
-// documents.
+// documents, for groups of tq queries, chunks of `chunk` result words and words of
+// `word` bytes in T.
 struct GroupShape {
     uint32_t lds, waves, groups, slices;
 };
@@ -623,9 +704,9 @@ static bool group_resolve(const rambo_s *h) {
 // takes the unit's 16 waves; smaller ones share it. Few groups are cut into
 // slices of the documents until the chip has a workgroup of its own for each
 // place, down to one chunk of result words a wave.
-static GroupShape group_shape(const rambo_s *h, uint64_t n, uint32_t tq, uint32_t chunk) {
+static GroupShape group_shape(const rambo_s *h, uint64_t n, uint32_t tq, uint32_t chunk, uint32_t word) {
     GroupShape g;
-    g.lds = t_words(h->R, h->B) * 8;
+    g.lds = t_words(h->R, h->B) * word;
     g.waves = g.lds > h->lds_max / 2 ? 16 : g.lds > h->lds_max / 4 ? 8 : 4;
     const uint64_t groups = (n + tq - 1) / tq, places = (uint64_t)h->n_cu * (16 / g.waves);
     const uint64_t chunks = (h->W + chunk - 1) / chunk, most = (chunks + g.waves - 1) / g.waves;
@@ -674,10 +755,19 @@ int launch_query_kmers(rambo_s *h, const uint64_t *kmers, uint64_t n, uint64_t *
         else if (h->RW == 2) hipLaunchKernelGGL(k_terms_lane<2>, grid, block, lds, s, ix, kmers, n, out, h->d_invalid);
         else hipLaunchKernelGGL(k_terms_lane<4>, grid, block, lds, s, ix, kmers, n, out, h->d_invalid);
     } else {
-        const GroupShape g = group_shape(h, n, 64, 16);
+        // where a T of 64 terms would take more than half the LDS, and so leave one
+        // workgroup a compute unit, groups of 32 (0.64 -> 0.55 ms, see the kernel);
+        // elsewhere they would only read the documents' cells twice as often
+        const bool half = t_words(h->R, h->B) * 8 > h->lds_max / 2;
+        const GroupShape g = group_shape(h, n, half ? 32 : 64, 16, half ? 4 : 8);
         if (g.groups > 0x7FFFFFFFu) return fail(RAMBO_EINVAL, "rambo_query_kmers: batch too large");
-        hipLaunchKernelGGL(k_terms_group, dim3(g.groups, g.slices), dim3(64 * g.waves), g.lds, s, ix, kmers, n, out,
-                           h->d_invalid, h->log2RW - 2);
+        const dim3 grid(g.groups, g.slices), block(64 * g.waves);
+        if (half)
+            hipLaunchKernelGGL(k_terms_group<uint32_t>, grid, block, g.lds, s, ix, kmers, n, out, h->d_invalid,
+                               h->log2RW - 2);
+        else
+            hipLaunchKernelGGL(k_terms_group<uint64_t>, grid, block, g.lds, s, ix, kmers, n, out, h->d_invalid,
+                               h->log2RW - 2);
     }
     HIP_CHECK(hipGetLastError());
     return RAMBO_OK;
@@ -716,7 +806,7 @@ int launch_query_termsets(rambo_s *h, const uint64_t *terms, const uint64_t *off
     // in groups of 16, whose transposes are as many each)
     uint32_t tq = 64;
     while (tq > 4 && n < (uint64_t)h->n_cu * 4 * tq) tq >>= 1;
-    const GroupShape g = group_shape(h, n, tq, 8);
+    const GroupShape g = group_shape(h, n, tq, 8, 8);
     if (g.groups > 0x7FFFFFFFu) return fail(RAMBO_EINVAL, "rambo_query_term_sets: batch too large");
     QueryOpts opt{h->resolve, h->early_exit, h->probe_counter, SCHED_SWEEP, nullptr, h->d_emptyq};
     const dim3 grid(g.groups, g.slices), block(64 * g.waves);

@@ -72,3 +72,17 @@ def test_batches_that_fill_the_chip(B):
     want, _ = o.query_termsets(pt, po, oracle.MODE_ALG2, early_exit=True)
     assert np.array_equal(to_host_u64(idx.query_term_sets(to_dev(pt), to_dev(po))), want)
     idx.close()
+
+
+@pytest.mark.parametrize("shape", [(1, 5000, 3, 1 << 11, 2), (1500, 2048, 8, 1 << 11, 1), (2049, 4950, 4, 1 << 11, 2),
+                                   (1030, 8192, 2, 1 << 11, 2)], ids=lambda s: "K%d-B%d-R%d" % s[:3])
+def test_half_groups_equal_oracle(shape):
+    """Groups of 32 terms: masks of 64 terms would take more than half the LDS.
+    Batches around multiples of 32; answers of one word, of half a chunk more
+    than one, of one word more than two; every number of probed repetitions."""
+    idx, o, dm, terms, offs = build(shape, 8400 + shape[1])
+    q, _ = dm.term_queries(9, 20_003, 0.7)
+    want = o.query_terms(q, oracle.MODE_ALG2)
+    for n in (1, 31, 32, 33, 95, 20_003):
+        assert np.array_equal(to_host_u64(idx.query_kmers(to_dev(q[:n]))), want[:n]), n
+    idx.close()
