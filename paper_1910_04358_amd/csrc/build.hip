@@ -413,9 +413,10 @@ static int launch_parts(rambo_s *h, const Docs &in, uint64_t most, hipStream_t s
     pt.slots = kStage / kBuckets;
     while (pt.slots * 2 * pt.buckets <= kStage && pt.slots < 4096) pt.slots *= 2;
     const uint32_t bucket_bits = pt.lg + h->log2RW + 5;
-    // (every tile of a bucket reads the bucket's bits: 17 ps a bit at 128 tiles, a
-    // repetition of 8 GiB; past 256 direct insertion is as fast)
-    if (bucket_bits > kTileBits + 8) return RAMBO_OK;
+    // (every tile of a bucket reads the bucket's bits: 128 tiles, a repetition of
+    // 8 GiB, 5 x 10^10 bits in 1.53 s, 2.57 before; 256 tiles, 16 GiB, 1.2 x 10^11
+    // bits in 6.4 s, 5.1 directly)
+    if (bucket_bits > kTileBits + 7) return RAMBO_OK;
     // segments of the mean number of bits and eight deviations more
     const uint64_t segs = (uint64_t)pt.buckets * pt.groups;
     const uint64_t room = std::max<uint64_t>(256ull << 20, std::min<uint64_t>(h->rows_bytes, 4ull << 30));
