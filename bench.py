@@ -11,9 +11,9 @@ synthetic (the paper's ENA archive is not available).
 
 A step is one query batch of all 100,000 reads (every k-mer of every read
 counted, including those early exit skips), with the index and the reads
-resident in HBM. The batched form (persistent launch replayed from a HIP
-graph, autotuned shape) gives `value`; the plain one-launch kernel and the
-build are reported beside it, with the served form's latency when run.
+resident in HBM. The batched form (a scout pass, then a persistent launch,
+autotuned shape) gives `value`; the plain form and the build are reported
+beside it, with the served form's latency when run.
 
 Prints one JSON line on stdout; progress goes to stderr.
 """
@@ -294,8 +294,7 @@ def time_steps(fn, steps, warmup):
 
 def pipelined_run(idx, seqs, offs, ref, steps, warmup):
     """The same batch passes, consecutive ones alternating between two streams
-    (each with its own output buffer, so its own captured graphs and queue
-    state): a batch's scout pass and queue building can run while the
+    (each with its own output buffer and queue state): a batch's scout pass and queue building can run while the
     previous batch's persistent kernel drains. Each step is still one whole
     pass over one batch; the answers are checked against the single-stream
     ones. Timed with events: the two streams wait for a start event on the
@@ -326,7 +325,7 @@ def pipelined_run(idx, seqs, offs, ref, steps, warmup):
     if not (torch.equal(outs[0], ref) and torch.equal(outs[1], ref)):
         raise SystemExit("two-stream batched results differ")
     return {"ms_per_step": ms, "streams": 2,
-            "note": "consecutive batches alternate between two streams (own output buffers and graphs); "
+            "note": "consecutive batches alternate between two streams (own output buffers and queue state); "
                     "each step is one whole pass over one batch"}
 
 
@@ -482,7 +481,7 @@ def main():
         batched_ms = time_steps(step, args.steps, args.warmup)
         if args.only is None and not torch.equal(out, ref):
             raise SystemExit("batched results differ from the plain kernel")
-        # the main kernel's own device time from events inside the graph, and
+        # the main kernel's own device time from events between the launches, and
         # the probes of the pass (scout and main kernels), per launch
         idx.set_probe_counter(probes)
         probes.zero_()

@@ -1,5 +1,5 @@
 """Batched form at the sizes where its queue is built another way: one workgroup
-that prepares and scans the batch (to 4,096 reads), one read per thread, four
+that prepares and scans the batch (to 2,048 reads), one read per thread, four
 reads per thread; with tiles that a small batch cuts shorter (several tiles a
 read) and a batch that starts fewer items than the chip has waves; with and
 without the scout pass. Equal to the plain form, whose answers the oracle
@@ -15,7 +15,8 @@ from tests.gpu_util import build_gpu_seqs, build_oracle, reads_to_dev, to_host_u
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("B,n", [(100, 1), (100, 4096), (100, 4097), (100, 600_000), (300, 4095), (300, 70_000)])
+@pytest.mark.parametrize("B,n", [(100, 1), (100, 2048), (100, 2049), (100, 4096), (100, 4097), (100, 600_000),
+                                 (300, 2048), (300, 4095), (300, 70_000)])
 def test_batch_sizes_equal_plain_form(B, n):
     import torch
     K, R, m, eta, seed = 70, 3, 1 << 18, 2, 8800 + B
