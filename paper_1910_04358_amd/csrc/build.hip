@@ -169,7 +169,7 @@ __global__ __launch_bounds__(256) void k_build(Index ix, Docs in, uint64_t from,
 // put together in LDS and ORed into the rows in order (k_part_apply), which
 // costs 0.8 ms a GiB. 1,000 documents of 200 kbp, R=4, eta=3 into 1 GiB of rows
 // (2.4 x 10^9 bits): 116 ms by atomics alone, 79 ms by direct insertion
-// as above, 14.2 ms partitioned.
+// as above, 14.0 ms partitioned.
 // ---------------------------------------------------------------------------
 constexpr uint32_t kBuckets = 1024;    // regions of the scatter, at most
 constexpr uint32_t kStage = 32768;     // bits staged by a scatter workgroup (128 KB of LDS), over all buckets
@@ -177,7 +177,8 @@ constexpr uint32_t kFlush = 16;        // bits written together (64 bytes)
 constexpr uint32_t kGroupAdds = 9;     // bits a thread adds between flushes: nine a bucket of 32 places, with 1,024
                                        // (14.2 ms for the genomes above; 14.7 with 6, 14.4 with 12, which overflow more)
 constexpr uint32_t kUnroll = 4;        // positions of a thread whose loads go together
-constexpr uint32_t kTileBits = 19;     // an apply tile: 64 KB of rows
+constexpr uint32_t kTileBits = 20;     // an apply tile, at most: 128 KB of rows
+constexpr uint32_t kBucketBits = 19;   // a bucket, at least
 
 // Where a partitioned insertion keeps its bits: segment (b, g) holds those of
 // bucket b that workgroup g found, at most cap of them (a multiple of 16), as
@@ -305,13 +306,17 @@ __global__ __launch_bounds__(1024) void k_part_scatter(Index ix, Docs in, Parts 
     flush(true);
 }
 
-// ORs the segments' bits of one tile of the rows (64 KB, or a smaller bucket)
+// ORs the segments' bits of one tile of the rows (128 KB, or a smaller bucket)
 // into the rows: a workgroup collects them in LDS, reading all of its bucket's
 // segments, four lanes a segment. A bucket's tiles are eight workgroups apart, so
 // they run on one XCD, whose L2 then reads the segments once. The rows are
 // changed by atomics (in order, at more than half the rate of plain loads and
 // stores), so insertions on other streams may run at the same time.
-__global__ __launch_bounds__(512) void k_part_apply(Index ix, Docs in, Parts pt, uint32_t r, uint32_t pass,
+// Bound by the reads of the bits, each by every tile of its bucket, where there
+// are many tiles, and by the atomics where there are few: tiles of 128 KB, one
+// workgroup a compute unit, against 64 KB, two: 5 x 10^10 bits at 64 / 128 tiles a
+// bucket, scatter included, 1.10 / 1.53 s; 2.4 x 10^9 at 2 / 4, 14.0 / 14.2 ms.
+__global__ __launch_bounds__(1024) void k_part_apply(Index ix, Docs in, Parts pt, uint32_t r, uint32_t pass,
                                                     uint32_t tiles, uint32_t lgt) {
     extern __shared__ __align__(16) uint32_t smem32[];
     const uint64_t first = in.off[0], all = in.off[in.n];
@@ -407,15 +412,15 @@ static int launch_parts(rambo_s *h, const Docs &in, uint64_t most, hipStream_t s
     Parts pt;
     pt.groups = (uint32_t)h->n_cu;
     // buckets of a tile at least, and not more than there are places for
-    pt.lg = kTileBits - 5 - std::min<uint32_t>(h->log2RW, kTileBits - 5);
+    pt.lg = kBucketBits - 5 - std::min<uint32_t>(h->log2RW, kBucketBits - 5);
     while ((((h->m - 1) >> pt.lg) + 1) > kBuckets) pt.lg++;
     pt.buckets = (uint32_t)(((h->m - 1) >> pt.lg) + 1);
     pt.slots = kStage / kBuckets;
     while (pt.slots * 2 * pt.buckets <= kStage && pt.slots < 4096) pt.slots *= 2;
     const uint32_t bucket_bits = pt.lg + h->log2RW + 5;
-    // (every tile of a bucket reads the bucket's bits: 128 tiles, a repetition of
-    // 8 GiB, 5 x 10^10 bits in 1.53 s, 2.57 before; 256 tiles, 16 GiB, 1.2 x 10^11
-    // bits in 6.4 s, 5.1 directly)
+    // (every tile of a bucket reads the bucket's bits: at 64 tiles, a repetition of
+    // 8 GiB, 5 x 10^10 bits in 1.10 s, 2.57 directly; at 128, 16 GiB, 1.2 x 10^11
+    // bits in 4.1 s, 5.1 directly; at 256 it would take longer)
     if (bucket_bits > kTileBits + 7) return RAMBO_OK;
     // segments of the mean number of bits and eight deviations more
     const uint64_t segs = (uint64_t)pt.buckets * pt.groups;
@@ -454,7 +459,7 @@ static int launch_parts(rambo_s *h, const Docs &in, uint64_t most, hipStream_t s
         for (uint32_t r = 0; r < h->R; r++) {
             hipLaunchKernelGGL(k_part_scatter<SEQS>, dim3(pt.groups), dim3(1024), lds, s, ix, in, pt, r, (uint32_t)c,
                                h->d_invalid);
-            hipLaunchKernelGGL(k_part_apply, dim3(apply), dim3(512), (size_t)1 << (lgt - 3), s, ix, in, pt, r,
+            hipLaunchKernelGGL(k_part_apply, dim3(apply), dim3(lgt > kBucketBits ? 1024 : 512), (size_t)1 << (lgt - 3), s, ix, in, pt, r,
                                (uint32_t)c, tiles, lgt);
         }
     // positions past `most`, if there are any (the allocation goes on in another

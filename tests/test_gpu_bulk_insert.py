@@ -15,13 +15,15 @@ from tests.gpu_util import cuda, to_dev
 
 pytestmark = pytest.mark.gpu
 
-# (K, B, R, m, eta): documents of 80 kbp, 2.4 million positions
+# (K, B, R, m, eta): documents of 80 kbp, 2.4 million positions or more
 SHAPES = [
     (30, 1, 1, 1 << 17, 4),       # one-word rows, one cell
     (30, 100, 2, 100_003, 2),     # a bucket past the last row
     (30, 40, 3, 65_537, 3),       # two-word rows
     (30, 1100, 2, 9_001, 2),      # rows of 64 words, few regions
     (30, 32, 2, 3_000_017, 16),   # many regions, many hash functions
+    (40, 1000, 1, 1 << 20, 2),    # regions of one full tile of the rows
+    (40, 1000, 1, (1 << 20) + 5, 2),  # of two tiles
 ]
 
 
