@@ -192,19 +192,21 @@ __device__ __forceinline__ uint32_t scout_pos32(uint32_t nw, uint32_t k) { retur
 // the bytes of its read's next round and of its next read's first round, and
 // the offsets two reads ahead. A round then costs one memory round trip,
 // whichever way the read goes. The grid is what fits on the device at once.
-// NARROW (id-list mode, where an ended read costs no output) gives rows split
+// NARROW (where an ended read costs no output here: id lists, and large batches of
+// bitsets) gives rows split
 // over 8 or more lanes one window per round (a group of G lanes per read)
 // instead of 8: the read ends at its first empty window, with no probes of
 // the windows after it, and a wave holds as many rows in flight as with wider
-// groups, as it walks 8 reads at once; with bitsets the wider groups write the
-// zero bitsets faster.
+// groups, as it walks 8 reads at once; where this pass writes the zero bitsets
+// (zero), the wider groups write them faster.
 // In id-list mode with split rows a wave keeps only 8 reads' rounds in
 // flight and the pass waits on their round trips: 8 waves per SIMD instead of
 // the 7 its 71 VGPRs allow (two values spilled to scratch) make it 12 % faster
 // (K=101,000: 0.44 -> 0.39 ms).
 template <int SEG, int G, int NARROW>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu((NARROW && G >= 8) ? 8 : 1))) void k_batch_scout(Index ix, const InputHdr *in, uint64_t *__restrict__ out,
-                                                     BatchBufs bb, QueryOpts opt, InputHdr val, InputHdr *own) {
+                                                     BatchBufs bb, QueryOpts opt, InputHdr val, InputHdr *own,
+                                                     bool zero) {
     constexpr int GS = scout_group(G, NARROW != 0);  // lanes per read
     constexpr int SLOTS = GS / G;                   // windows per round
     const InputHdr hd = own ? val : *in;
@@ -330,7 +332,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu((NARROW && 
             if (!live) {
                 if (opt.counts) {
                     if (sub == 0) opt.counts[i] = 0;
-                } else {
+                } else if (zero) {  // (otherwise k_batch_zero's work)
                     for (uint32_t w = sub; w < ix.W; w += GS) out[i * ix.W + w] = 0;
                 }
             }
@@ -357,6 +359,27 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu((NARROW && 
         if (lane == 0 && issued) atomicAdd(&blk_issued, (unsigned long long)issued);
         __syncthreads();
         if (threadIdx.x == 0 && blk_issued) atomicAdd(opt.probes, blk_issued * ix.eta);
+    }
+}
+
+// The zero bitsets of the reads that the scout pass ended, where it leaves them to
+// this kernel: a wave takes eight consecutive reads and writes their rows 1 KB a
+// store, and waits for none (K=101,000, 10^5 reads, 1.2 GB: the pass and this
+// kernel 80 and 195 us, 298 in one).
+__global__ __launch_bounds__(256) void k_batch_zero(const InputHdr *in, const uint32_t *__restrict__ live,
+                                                    uint64_t *__restrict__ out, uint64_t W) {
+    const uint64_t n = in->n;
+    const uint32_t lane = threadIdx.x & 63;
+    const uint64_t stride = (uint64_t)gridDim.x * (blockDim.x >> 6) * 8;
+    const uint64_t zero[2] = {0, 0};
+    for (uint64_t i0 = (((uint64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6) * 8; i0 < n; i0 += stride) {
+        uint64_t ended = __ballot(lane < 8 && i0 + lane < n && !(live[min(i0 + lane, n - 1)] & 1u));
+        while (ended) {
+            uint64_t *row = out + (i0 + (uint64_t)__builtin_ctzll(ended)) * W;
+            ended &= ended - 1;
+            for (uint64_t w = 2 * lane; w + 1 < W; w += 128) __builtin_memcpy(row + w, zero, 16);
+            if ((W & 1) && lane == 0) row[W - 1] = 0;
+        }
     }
 }
 
@@ -551,6 +574,14 @@ static int resident(rambo_s *h, uint64_t key, F kernel, int threads, size_t lds,
     return RAMBO_OK;
 }
 
+// Result words of a batch, with rows split over 8 or more lanes, from which the
+// zero bitsets of the reads that the scout pass ends are left to k_batch_zero: in
+// the scout pass a wave waits for the rows it writes, from here on that costs more
+// than the launch (K=101,000, 12.6 KB a read, whole calls, us: 1,200 reads 88
+// without and 94 with it, 5,000 96 / 100, 10,000 121 / 118, 20,000 185 / 178,
+// 100,000 574-598 / 530, 10^6 5,057 / 4,429).
+static constexpr uint64_t kZeroApart = 1 << 24;
+
 // Scout pass and queue of a batch of up to n reads (n <= bg.cap); with val, a
 // direct launch of that batch.
 static int enqueue_prep(rambo_s *h, const Tune &tu, BatchGraph &bg, uint64_t n, const InputHdr *val, uint64_t *out,
@@ -566,7 +597,12 @@ static int enqueue_prep(rambo_s *h, const Tune &tu, BatchGraph &bg, uint64_t n, 
         const Index ix = make_index(h);
         const int G = (int)h->RW / tu.seg;
         // a grid of what fits on the device at once strides over the reads
-        const bool narrow = io.counts != nullptr;
+        const bool apart = !io.counts && G >= 8 && n * h->W >= kZeroApart;
+        // without rows to write, narrow groups, where each has two reads or more
+        // (in the setting above 20,000 reads 178 with wide groups and 197 with narrow
+        // ones, 100,000 530 / 529, 200,000 987 / 956, 10^6 4,429 / 4,233)
+        const bool narrow =
+            io.counts != nullptr || (apart && n * (uint64_t)G >= 2 * (uint64_t)h->n_cu * 2048);
         const uint64_t GS = (uint64_t)scout_group(G, narrow);
         int fit = 0, st = RAMBO_OK;
         const uint64_t key = ((uint64_t)G << 16) | ((uint64_t)tu.seg << 8) | (narrow ? 2u : 1u);
@@ -583,13 +619,18 @@ static int enqueue_prep(rambo_s *h, const Tune &tu, BatchGraph &bg, uint64_t n, 
 #define RAMBO_SPLIT_BODY_                                                                                   \
     if (narrow)                                                                                             \
         hipLaunchKernelGGL((k_batch_scout<SEG, G, 1>), dim3((unsigned)blocks), dim3(256), 0, s, ix, bg.in, out,   \
-                           bg.bb, opt, hd, own);                                                             \
+                           bg.bb, opt, hd, own, !apart);                                                             \
     else                                                                                                     \
         hipLaunchKernelGGL((k_batch_scout<SEG, G, 0>), dim3((unsigned)blocks), dim3(256), 0, s, ix, bg.in, out,   \
-                           bg.bb, opt, hd, own)
+                           bg.bb, opt, hd, own, !apart)
         RAMBO_DISPATCH_SPLIT(tu.seg, G)
 #undef RAMBO_SPLIT_BODY_
         HIP_CHECK(hipGetLastError());
+        if (apart) {
+            hipLaunchKernelGGL(k_batch_zero, dim3((unsigned)std::min<uint64_t>((n + 31) / 32, (uint64_t)h->n_cu * 8)),
+                               dim3(256), 0, s, bg.in, bg.bb.live, out, (uint64_t)h->W);
+            HIP_CHECK(hipGetLastError());
+        }
     }
     const uint32_t tile = batch_tile(h, tu, n);
     if (one) {

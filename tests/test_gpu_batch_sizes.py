@@ -126,3 +126,38 @@ def test_streams_threads_buffers_and_capture():
         assert torch.equal(out, want[1])
     idx.sync()
     idx.close()
+
+
+def test_zero_bitsets_written_apart():
+    """Wide rows and batches past the size from which a kernel of its own writes the
+    ended reads' zero bitsets, with wide and narrow scout groups, into buffers that
+    hold other values; W odd and even, early exit on and off."""
+    import torch
+    for K, n in ((6_400, 170_001), (33_050, 33_001), (33_000, 132_000)):
+        B, R, m, eta, seed = 300, 2, 1 << 18, 2, 8970
+        dm = gen.DocModel(seed=78, n_docs=K, length=100, docs_per_anc=1_000, mu_lo=0.01, mu_hi=0.01)
+        idx = rb.Rambo(K, B, R, m, eta, seed)
+        build_gpu_seqs(idx, dm, 0, K)
+        rm = gen.ReadModel(qseed=n, src_lo=0, src_hi=K, len_kind=0, median=60, sigma=0.3, lo=20, hi=99, err_lo=0.0,
+                           err_hi=0.003)
+        seqs, offs = reads_to_dev(gen.reads(dm, rm, n))
+        idx.set_mode(rb.MODE_BATCHED)
+        t = idx.get_tune()
+        t.sched = 1
+        for seg in (1, 2):
+            t.seg = seg
+            idx.set_tune(t)
+            want = torch.empty((n, idx.W), dtype=torch.int64, device="cuda")
+            idx.query_seqs(seqs, offs, out=want, check=False)
+            t.sched = 2
+            idx.set_tune(t)
+            got = torch.full_like(want, -1)
+            for ee in (True, False):
+                idx.set_early_exit(ee)
+                got.fill_(-1)
+                idx.query_seqs(seqs, offs, out=got, check=False)
+                assert torch.equal(got, want), (K, n, seg, ee)
+            idx.set_early_exit(True)
+            t.sched = 1
+        idx.sync()
+        idx.close()
