@@ -597,7 +597,8 @@ static int enqueue_prep(rambo_s *h, const Tune &tu, BatchGraph &bg, uint64_t n, 
         const Index ix = make_index(h);
         const int G = (int)h->RW / tu.seg;
         // a grid of what fits on the device at once strides over the reads
-        const bool apart = !io.counts && G >= 8 && n * h->W >= kZeroApart;
+        // (a captured graph, whose batches are mostly smaller than n, keeps one kernel)
+        const bool apart = val && !io.counts && G >= 8 && n * h->W >= kZeroApart;
         // without rows to write, narrow groups, where each has two reads or more
         // (in the setting above 20,000 reads 178 with wide groups and 197 with narrow
         // ones, 100,000 530 / 529, 200,000 987 / 956, 10^6 4,429 / 4,233)
