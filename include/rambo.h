@@ -266,11 +266,15 @@ int rambo_insert_batch(rambo_t *h, const uint64_t *doc_ids, const uint64_t *kmer
  * valid 31-windows (Figure 1). Extraction runs on the GPU. Enqueued on
  * `stream`.
  * Large batches of k-mers or sequences (several bits of each 32 bytes of a
- * repetition's rows) are sorted by region first, in scratch memory that the
- * handle allocates when it first meets one and keeps: at most the size of the
- * index, or 256 MiB if that is more, and never over 4 GiB. Insertions that use
- * it follow one another whatever their streams. Without that memory, and under
- * graph capture, bits are set one at a time, with the same result. */
+ * repetition's rows) are sorted by region first. A call may be such a batch if
+ * the memory at seqs goes on for that many positions and n_docs documents that
+ * together with others fill the index (or of 2^17 positions, if that is more)
+ * hold as many; positions past that estimate are set one bit at a time. Sorting
+ * takes scratch memory that the handle allocates when it first meets such a call
+ * and keeps: at most the size of the index, or 256 MiB if that is more, and never
+ * over 4 GiB. Insertions that use it follow one another whatever their streams.
+ * Without that memory, and under graph capture, bits are set one at a time, with
+ * the same result. */
 int rambo_insert_seqs(rambo_t *h, const uint64_t *doc_ids, const uint8_t *seqs,
                       const uint64_t *offsets, uint64_t n_docs, void *stream);
 

@@ -364,7 +364,7 @@ RAMBO_API int rambo_insert(rambo_t *h, uint64_t doc_id, const uint64_t *kmers, u
     if (hipMemcpyAsync(d, kmers, n * 8, hipMemcpyHostToDevice, h->aux) != hipSuccess ||
         hipMemcpyAsync(d + n, meta, sizeof meta, hipMemcpyHostToDevice, h->aux) != hipSuccess)
         st = fail(RAMBO_EDEVICE, "rambo_insert: copy failed");
-    if (st == RAMBO_OK) st = launch_build_kmers(h, d, d + n + 1, d + n, 1, h->aux);
+    if (st == RAMBO_OK) st = launch_build_kmers(h, d, d + n + 1, d + n, 1, h->aux, n);
     if (hipStreamSynchronize(h->aux) != hipSuccess && st == RAMBO_OK) st = fail(RAMBO_EDEVICE, "rambo_insert: kernel failed");
     (void)hipFree(d);
     return st;

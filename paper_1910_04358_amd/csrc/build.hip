@@ -156,9 +156,14 @@ __device__ __forceinline__ void build_share(const Index &ix, const Docs &in, uin
         if (t.ok) scatter_term(ix, t.x, t.d);
     }
 }
+// All positions of an insertion of fewer than least; those from the from-th on of
+// a larger one.
 template <bool SEQS>
-__global__ __launch_bounds__(256) void k_build(Index ix, Docs in, uint64_t from, unsigned long long *invalid) {
-    build_share<SEQS>(ix, in, in.off[0] + from, in.off[in.n], invalid);
+__global__ __launch_bounds__(256) void k_build(Index ix, Docs in, uint64_t from, uint64_t least,
+                                               unsigned long long *invalid) {
+    const uint64_t first = in.off[0], last = in.off[in.n];
+    if (last <= first) return;
+    build_share<SEQS>(ix, in, last - first < least ? first : first + from, last, invalid);
 }
 
 // ---------------------------------------------------------------------------
@@ -191,7 +196,15 @@ struct Parts {
     uint32_t slots;    // staged bits of a bucket: kStage / buckets, a power of two
     uint64_t chunk;    // positions of the concatenated documents a pass takes
     uint64_t least;    // positions below which the whole insertion is direct
+    uint64_t rep;      // words from a repetition's segments to the next one's (0: one set of segments)
 };
+
+// Repetition blockIdx.y of a launch that takes several has segments of its own.
+__device__ __forceinline__ uint32_t part_rep(Parts &pt, uint32_t r) {
+    pt.bits += blockIdx.y * pt.rep;
+    pt.count += blockIdx.y * pt.rep;
+    return r + blockIdx.y;
+}
 
 __device__ __forceinline__ uint32_t *part_base(const Index &ix, const Parts &pt, uint32_t r, uint32_t b) {
     return ix.rows + (((uint64_t)r * ix.m + ((uint64_t)b << pt.lg)) << ix.log2RW);
@@ -208,27 +221,24 @@ __device__ __forceinline__ void part_direct(uint32_t *base, uint32_t v) {
 // segments. A workgroup a compute unit; it takes a contiguous share of the
 // positions and stages bits in LDS, so that they leave 16 of a bucket at a time.
 // A bit that finds its bucket's places taken is set directly. An insertion of
-// fewer than least positions sets all its bits directly (the host does not know
-// the number of positions).
+// fewer than least positions is left to k_build (the host does not know the number
+// of positions).
 // Bound by vector instructions (the hashes' 64-bit products; 300 a 64 positions
 // and eta = 3): 6.7 x 10^7 positions of one repetition in 0.91 ms.
 template <bool SEQS>
 __global__ __launch_bounds__(1024) void k_part_scatter(Index ix, Docs in, Parts pt, uint32_t r, uint32_t pass,
                                                        unsigned long long *invalid) {
     extern __shared__ __align__(16) uint32_t smem32[];
+    r = part_rep(pt, r);
     uint32_t *stage = smem32;            // [buckets][slots]
     uint32_t *fill = stage + kStage;     // [kBuckets] staged
     uint32_t *sent = fill + kBuckets;    // [kBuckets] written to the segment
     const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const uint64_t first = in.off[0], all = in.off[in.n];
-    if (all <= first) return;
+    if (all <= first || all - first < pt.least) return;
     const uint64_t lo = first + (uint64_t)pass * pt.chunk;
     if (lo >= all) return;
     const uint64_t hi = min(all, lo + pt.chunk);
-    if (all - first < pt.least) {  // direct: all repetitions at once, in the first launch
-        if (r == 0 && pass == 0) build_share<SEQS>(ix, in, first, all, invalid);
-        return;
-    }
     for (uint32_t b = threadIdx.x; b < kBuckets; b += blockDim.x) fill[b] = sent[b] = 0;
     __syncthreads();
     // this workgroup's share, in steps of 1,024 * kUnroll positions
@@ -306,8 +316,8 @@ __global__ __launch_bounds__(1024) void k_part_scatter(Index ix, Docs in, Parts 
     flush(true);
 }
 
-// ORs the segments' bits of one tile of the rows (128 KB, or a smaller bucket)
-// into the rows: a workgroup collects them in LDS, reading all of its bucket's
+// ORs the segments' bits into the rows, tile by tile (128 KB of rows, or a smaller
+// bucket): a workgroup collects a tile's in LDS, reading all of its bucket's
 // segments, four lanes a segment. A bucket's tiles are eight workgroups apart, so
 // they run on one XCD, whose L2 then reads the segments once. The rows are
 // changed by atomics (in order, at more than half the rate of plain loads and
@@ -316,46 +326,54 @@ __global__ __launch_bounds__(1024) void k_part_scatter(Index ix, Docs in, Parts 
 // are many tiles, and by the atomics where there are few: tiles of 128 KB, one
 // workgroup a compute unit, against 64 KB, two: 5 x 10^10 bits at 64 / 128 tiles a
 // bucket, scatter included, 1.10 / 1.53 s; 2.4 x 10^9 at 2 / 4, 14.0 / 14.2 ms.
+// The grid is what is resident and strides over the tiles (a multiple of eight
+// workgroups, so that each stays on its tiles' XCD): with a workgroup a tile a
+// launch that found nothing to do took 130 us at 131,072 tiles.
 __global__ __launch_bounds__(1024) void k_part_apply(Index ix, Docs in, Parts pt, uint32_t r, uint32_t pass,
                                                     uint32_t tiles, uint32_t lgt) {
     extern __shared__ __align__(16) uint32_t smem32[];
+    r = part_rep(pt, r);
     const uint64_t first = in.off[0], all = in.off[in.n];
     if (all <= first || first + (uint64_t)pass * pt.chunk >= all || all - first < pt.least) return;
-    const uint32_t b = (blockIdx.x / (8 * tiles)) * 8 + blockIdx.x % 8, tile = (blockIdx.x / 8) % tiles;
-    if (b >= pt.buckets) return;
     const uint32_t words = 1u << (lgt - 5), part = threadIdx.x & 3;
-    for (uint32_t i = threadIdx.x; i < words; i += blockDim.x) smem32[i] = 0;
-    __syncthreads();
-    auto put = [&](uint32_t v) {
-        if (v >> lgt == tile) atomicOr(&smem32[(v & ((1u << lgt) - 1)) >> 5], 1u << (v & 31));
-    };
-    constexpr uint32_t U = 8;  // loads of a lane in flight
-    const uint32_t *counts = pt.count + (uint64_t)b * pt.groups;
-    const uint32_t g0 = threadIdx.x >> 2, gs = blockDim.x >> 2;
-    uint32_t next = g0 < pt.groups ? counts[g0] : 0;
-    for (uint32_t g = g0; g < pt.groups; g += gs) {
-        const uint32_t n = next;
-        next = g + gs < pt.groups ? counts[g + gs] : 0;
-        const uint32_t *seg = pt.bits + ((uint64_t)b * pt.groups + g) * pt.cap;
-        const uint4 *seg4 = reinterpret_cast<const uint4 *>(seg);
-        const uint32_t n4 = n / 4;
-        for (uint32_t i0 = part; i0 < n4; i0 += 4 * U) {
-            uint4 v[U];
+    const uint32_t end = ((pt.buckets + 7) / 8) * 8 * tiles;
+    for (uint32_t w = blockIdx.x; w < end; w += gridDim.x) {
+        const uint32_t b = (w / (8 * tiles)) * 8 + w % 8, tile = (w / 8) % tiles;
+        if (b >= pt.buckets) continue;
+        // (a thread clears the words that it wrote out itself: no barrier before)
+        for (uint32_t i = threadIdx.x; i < words; i += blockDim.x) smem32[i] = 0;
+        __syncthreads();
+        auto put = [&](uint32_t v) {
+            if (v >> lgt == tile) atomicOr(&smem32[(v & ((1u << lgt) - 1)) >> 5], 1u << (v & 31));
+        };
+        constexpr uint32_t U = 8;  // loads of a lane in flight
+        const uint32_t *counts = pt.count + (uint64_t)b * pt.groups;
+        const uint32_t g0 = threadIdx.x >> 2, gs = blockDim.x >> 2;
+        uint32_t next = g0 < pt.groups ? counts[g0] : 0;
+        for (uint32_t g = g0; g < pt.groups; g += gs) {
+            const uint32_t n = next;
+            next = g + gs < pt.groups ? counts[g + gs] : 0;
+            const uint32_t *seg = pt.bits + ((uint64_t)b * pt.groups + g) * pt.cap;
+            const uint4 *seg4 = reinterpret_cast<const uint4 *>(seg);
+            const uint32_t n4 = n / 4;
+            for (uint32_t i0 = part; i0 < n4; i0 += 4 * U) {
+                uint4 v[U];
 #pragma unroll
-            for (uint32_t u = 0; u < U; u++) v[u] = seg4[min(i0 + 4 * u, n4 - 1)];
+                for (uint32_t u = 0; u < U; u++) v[u] = seg4[min(i0 + 4 * u, n4 - 1)];
 #pragma unroll
-            for (uint32_t u = 0; u < U; u++) {
-                if (i0 + 4 * u >= n4) break;
-                put(v[u].x); put(v[u].y); put(v[u].z); put(v[u].w);
+                for (uint32_t u = 0; u < U; u++) {
+                    if (i0 + 4 * u >= n4) break;
+                    put(v[u].x); put(v[u].y); put(v[u].z); put(v[u].w);
+                }
             }
+            if (part < n % 4) put(seg[n4 * 4 + part]);
         }
-        if (part < n % 4) put(seg[n4 * 4 + part]);
-    }
-    __syncthreads();
-    uint32_t *rows = part_base(ix, pt, r, b) + (uint64_t)tile * words;
-    for (uint32_t i = threadIdx.x; i < words; i += blockDim.x) {
-        const uint32_t v = smem32[i];
-        if (v) atomicOr(rows + i, v);
+        __syncthreads();
+        uint32_t *rows = part_base(ix, pt, r, b) + (uint64_t)tile * words;
+        for (uint32_t i = threadIdx.x; i < words; i += blockDim.x) {
+            const uint32_t v = smem32[i];
+            if (v) atomicOr(rows + i, v);
+        }
     }
 }
 
@@ -391,6 +409,19 @@ static uint64_t bytes_from(const void *p) {
     return (uint64_t)((const char *)base + size - (const char *)p);
 }
 
+// Positions that an insertion of n_docs documents is taken to hold, where the
+// buffer does not say: the index's K documents fill its filters to three quarters
+// at most (2 m ln 2 / eta terms a filter, B of them for the K documents), or 2^17
+// positions a document if that is more. The buffer may be a store of documents,
+// of which the call inserts a few: without this bound a document of 100 kbp out
+// of 10 GB went through 132 rounds of launches that found nothing to do (17.4 ms,
+// K=101,000; 0.04 ms out of a buffer of its own).
+static uint64_t likely_positions(const rambo_s *h, uint64_t n_docs) {
+    const double full = 2 * 0.6931 * (double)h->m * h->B / h->eta;  // of all K
+    const double docs = (double)n_docs * std::max(full / (double)h->K, 131072.0);
+    return (uint64_t)std::min(docs, std::max(full, 4194304.0));
+}
+
 // The partitioned insertion of at most `most` positions, if it pays; *taken says
 // whether it was enqueued. Word terms stay direct: most of a document's bits are
 // words that others have set already, and a load shows that sooner than the
@@ -403,7 +434,7 @@ static int launch_parts(rambo_s *h, const Docs &in, uint64_t most, hipStream_t s
     // direct 33 to 50 ps a bit, partitioned 5.3 ps a bit, 0.9 ms a GiB of rows and
     // 45 us a repetition: equal near 1.6 million bits and one per 32 bytes of rows
     const uint64_t least_bits = 1600000 + rep_bytes / 32;
-    // (more than two million positions: the bound is an allocation's, and small
+    // (more than two million positions: the bound may be an allocation's, and small
     // tensors share one of 2 MB)
     const uint64_t least = std::max<uint64_t>((2 << 20) + 1, (least_bits + h->eta - 1) / h->eta);
     if (h->opaque || most < least) return RAMBO_OK;
@@ -429,12 +460,18 @@ static int launch_parts(rambo_s *h, const Docs &in, uint64_t most, hipStream_t s
         const double mean = (double)positions * h->eta / (double)segs;
         return ((uint64_t)(mean + 8 * std::sqrt(mean)) + 16 + 15) & ~15ull;
     };
+    auto chunk_of = [&](uint64_t passes) { return ((most + passes - 1) / passes + 1023) & ~1023ull; };
+    auto words_of = [&](uint64_t chunk) { return (segs * (seg_cap(chunk) + 1) + 3) & ~3ull; };  // of a repetition
     uint64_t passes = 1;
     while (seg_cap((most + passes - 1) / passes) * segs * 4 > room) passes++;
-    pt.chunk = ((most + passes - 1) / passes + 1023) & ~1023ull;
+    pt.chunk = chunk_of(passes);
     pt.cap = (uint32_t)seg_cap(pt.chunk);
     pt.least = least;
-    const uint64_t need = segs * pt.cap * 4 + segs * 4;
+    // all repetitions in one launch where their segments fit together (the launches
+    // are then few, should the documents turn out to be small)
+    const bool together = passes == 1 && h->R * words_of(pt.chunk) * 4 <= room;
+    pt.rep = together ? words_of(pt.chunk) : 0;
+    const uint64_t need = (together ? h->R : 1) * words_of(pt.chunk) * 4;
     std::lock_guard<std::mutex> g(h->parts_mu);
     if (h->parts_bytes < need) {
         if (h->d_parts) (void)hipFree(h->d_parts);  // (waits for the work that uses it)
@@ -454,17 +491,20 @@ static int launch_parts(rambo_s *h, const Docs &in, uint64_t most, hipStream_t s
     const Index ix = make_index(h);
     const size_t lds = (size_t)(kStage + kBuckets * 2) * 4;
     const uint32_t lgt = std::min<uint32_t>(bucket_bits, kTileBits), tiles = 1u << (bucket_bits - lgt);
-    const unsigned apply = ((pt.buckets + 7) / 8) * 8 * tiles;
+    // (64 KB of LDS a workgroup of 512 threads: two a compute unit, else one)
+    const unsigned per_cu = lgt > kBucketBits ? 1 : 2;
+    const unsigned apply = std::min<unsigned>(((pt.buckets + 7) / 8) * 8 * tiles, ((unsigned)h->n_cu * per_cu + 7) / 8 * 8);
+    const unsigned reps = together ? h->R : 1;
     for (uint64_t c = 0; c < passes; c++)
-        for (uint32_t r = 0; r < h->R; r++) {
-            hipLaunchKernelGGL(k_part_scatter<SEQS>, dim3(pt.groups), dim3(1024), lds, s, ix, in, pt, r, (uint32_t)c,
+        for (uint32_t r = 0; r < h->R; r += reps) {
+            hipLaunchKernelGGL(k_part_scatter<SEQS>, dim3(pt.groups, reps), dim3(1024), lds, s, ix, in, pt, r, (uint32_t)c,
                                h->d_invalid);
-            hipLaunchKernelGGL(k_part_apply, dim3(apply), dim3(lgt > kBucketBits ? 1024 : 512), (size_t)1 << (lgt - 3), s, ix, in, pt, r,
-                               (uint32_t)c, tiles, lgt);
+            hipLaunchKernelGGL(k_part_apply, dim3(apply, reps), dim3(lgt > kBucketBits ? 1024 : 512),
+                               (size_t)1 << (lgt - 3), s, ix, in, pt, r, (uint32_t)c, tiles, lgt);
         }
-    // positions past `most`, if there are any (the allocation goes on in another
-    // mapping): nothing, usually
-    hipLaunchKernelGGL(k_build<SEQS>, dim3((unsigned)h->n_cu), dim3(256), 0, s, ix, in, passes * pt.chunk, h->d_invalid);
+    // an insertion that turns out to be small, or the positions past `most`
+    hipLaunchKernelGGL(k_build<SEQS>, dim3((unsigned)h->n_cu * 16), dim3(256), 0, s, ix, in, passes * pt.chunk, least,
+                       h->d_invalid);
     HIP_CHECK(hipGetLastError());
     HIP_CHECK(hipEventRecord(h->parts_done, s));
     *taken = true;
@@ -478,19 +518,21 @@ static int launch_build(rambo_s *h, const Docs &in, uint64_t most, hipStream_t s
     if (st != RAMBO_OK || taken) return st;
     // the grid is persistent (grid-stride); the number of positions is only known on the device
     hipLaunchKernelGGL(k_build<SEQS>, dim3((unsigned)h->n_cu * 16), dim3(256), 0, s, make_index(h), in, (uint64_t)0,
-                       h->d_invalid);
+                       (uint64_t)0, h->d_invalid);
     HIP_CHECK(hipGetLastError());
     return RAMBO_OK;
 }
 
 int launch_build_kmers(rambo_s *h, const uint64_t *kmers, const uint64_t *koff, const uint64_t *doc_ids,
-                       uint64_t n_docs, hipStream_t s) {
-    return launch_build<false>(h, Docs{kmers, nullptr, koff, doc_ids, n_docs}, bytes_from(kmers) / 8, s);
+                       uint64_t n_docs, hipStream_t s, uint64_t positions) {
+    const uint64_t most = positions ? positions : std::min(bytes_from(kmers) / 8, likely_positions(h, n_docs));
+    return launch_build<false>(h, Docs{kmers, nullptr, koff, doc_ids, n_docs}, most, s);
 }
 
 int launch_build_seqs(rambo_s *h, const uint8_t *seqs, const uint64_t *offs, const uint64_t *doc_ids,
                       uint64_t n_docs, hipStream_t s) {
-    return launch_build<true>(h, Docs{nullptr, seqs, offs, doc_ids, n_docs}, bytes_from(seqs), s);
+    return launch_build<true>(h, Docs{nullptr, seqs, offs, doc_ids, n_docs},
+                              std::min(bytes_from(seqs), likely_positions(h, n_docs)), s);
 }
 
 int launch_dump_bfu(rambo_s *h, uint32_t r, uint32_t b, uint64_t *d_out, hipStream_t s) {

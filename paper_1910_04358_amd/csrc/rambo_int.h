@@ -142,8 +142,9 @@ rambo_s *create_index(uint64_t K, uint32_t B, uint32_t R, uint64_t m, uint32_t e
                       const uint64_t *gids);
 
 // build.hip
+// (positions: k-mers of all the documents where the caller knows, else 0)
 int launch_build_kmers(rambo_s *h, const uint64_t *kmers, const uint64_t *koff, const uint64_t *doc_ids,
-                       uint64_t n_docs, hipStream_t s);
+                       uint64_t n_docs, hipStream_t s, uint64_t positions = 0);
 int launch_build_seqs(rambo_s *h, const uint8_t *seqs, const uint64_t *offs, const uint64_t *doc_ids,
                       uint64_t n_docs, hipStream_t s);
 int launch_dump_bfu(rambo_s *h, uint32_t r, uint32_t b, uint64_t *d_out, hipStream_t s);
