@@ -453,7 +453,7 @@ static int launch_parts(rambo_s *h, const Docs &in, uint64_t most, hipStream_t s
     // 8 GiB, 5 x 10^10 bits in 1.10 s, 2.57 directly; at 128, 16 GiB, 1.2 x 10^11
     // bits in 4.1 s, 5.1 directly; at 256 it would take longer)
     if (bucket_bits > kTileBits + 7) return RAMBO_OK;
-    // segments of the mean number of bits and eight deviations more
+    // segments of the mean number of bits and eight deviations more, and their counts
     const uint64_t segs = (uint64_t)pt.buckets * pt.groups;
     const uint64_t room = std::max<uint64_t>(256ull << 20, std::min<uint64_t>(h->rows_bytes, 4ull << 30));
     auto seg_cap = [&](uint64_t positions) {
@@ -463,7 +463,7 @@ static int launch_parts(rambo_s *h, const Docs &in, uint64_t most, hipStream_t s
     auto chunk_of = [&](uint64_t passes) { return ((most + passes - 1) / passes + 1023) & ~1023ull; };
     auto words_of = [&](uint64_t chunk) { return (segs * (seg_cap(chunk) + 1) + 3) & ~3ull; };  // of a repetition
     uint64_t passes = 1;
-    while (seg_cap((most + passes - 1) / passes) * segs * 4 > room) passes++;
+    while (words_of(chunk_of(passes)) * 4 > room && chunk_of(passes) > 1024) passes++;
     pt.chunk = chunk_of(passes);
     pt.cap = (uint32_t)seg_cap(pt.chunk);
     pt.least = least;
@@ -472,6 +472,7 @@ static int launch_parts(rambo_s *h, const Docs &in, uint64_t most, hipStream_t s
     const bool together = passes == 1 && h->R * words_of(pt.chunk) * 4 <= room;
     pt.rep = together ? words_of(pt.chunk) : 0;
     const uint64_t need = (together ? h->R : 1) * words_of(pt.chunk) * 4;
+    if (need > room) return RAMBO_OK;
     std::lock_guard<std::mutex> g(h->parts_mu);
     if (h->parts_bytes < need) {
         if (h->d_parts) (void)hipFree(h->d_parts);  // (waits for the work that uses it)

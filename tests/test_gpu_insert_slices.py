@@ -1,7 +1,7 @@
 """Insertions of a few documents out of a large buffer cost what the documents
-cost, in time and in memory; documents that turn out shorter than the estimate
-that chooses the bulk path are inserted all the same (against the same documents
-one by one)."""
+cost, in time and in memory, and the scratch of a bulk insertion stays within its
+documented size; documents that turn out shorter than the estimate that chooses
+the bulk path are inserted all the same (against the same documents one by one)."""
 import time
 
 import numpy as np
@@ -59,6 +59,21 @@ def test_one_document_of_a_large_buffer():
     assert part < 4 * own + 100e-6, (part, own)
     idx.sync()
     idx.close()
+
+
+def test_scratch_stays_within_its_documented_size():
+    K, B, R, m, eta, L = 740, 20, 2, 1 << 21, 3, 124_600
+    offs = to_dev(np.arange(K + 1, dtype=np.uint64) * np.uint64(L))
+    ids = to_dev(np.arange(K, dtype=np.uint64))
+    docs = bases(K * L)
+    for _ in range(2):  # (the first loads the kernels)
+        idx = rb.Rambo(K, B, R, m, eta, 8702)
+        before = free_bytes()
+        idx.insert_seqs(ids, docs, offs)
+        taken = before - free_bytes()
+        idx.sync()
+        idx.close()
+    assert 64 * MIB < taken <= 256 * MIB, taken  # (the rows are smaller)
 
 
 @pytest.mark.parametrize("n,L", [(40, 1_000), (64, 50), (17, 30)])
