@@ -60,6 +60,16 @@ __global__ __launch_bounds__(256) void k_query_seqs_plain(Index ix, const uint8_
 // other repetitions' rows, the resolve): with one wave per read a read of
 // 1,500 bases took 24 steps of 64 windows one after the other, here two (16
 // reads at K=10,000: 53 us a call, now 21).
+//
+// With early exit the waves first scout (repetition 0 on 64 windows 31 apart, then
+// on the rest of those) where the parts take several steps, or where the batch's
+// rows are what it waits for (kTeamScout bases, about 8 us of rows): most reads
+// that no document holds end there. Without, 4,000 reads of 10 kbp with an error
+// in a thousand bases took 789 us at K=101,000, now 60 (55 with one wave per read,
+// which scouts), 257 of 1 kbp with one in a hundred 41, now 27. Elsewhere the
+// scouts' round trip would only make the reads that live wait (id lists of 257
+// reads of median 300: 83 us without, 86 with scouts in the longer reads).
+constexpr uint64_t kTeamScout = 3 << 16;
 template <int SEG, int G>
 __global__ __launch_bounds__(1024) void k_query_seqs_team(Index ix, const uint8_t *__restrict__ seqs,
                                                           const uint64_t *__restrict__ offs, uint64_t n,
@@ -84,29 +94,71 @@ __global__ __launch_bounds__(1024) void k_query_seqs_team(Index ix, const uint8_
     const uint64_t nwin = n_windows(beg, end);
     constexpr uint32_t kGrain = 64 / G;  // terms that the wave's lanes take together
     const uint64_t part = ((nwin + kGrain - 1) / kGrain + waves - 1) / waves * kGrain;  // windows per wave
-    const uint32_t used = part ? (uint32_t)((nwin + part - 1) / part) : 0;  // waves that have any
+    const bool ee = opt.early_exit != 0;
+    const bool scouts = ee && nwin > 0 && (part > 64 || offs[n] - offs[0] >= kTeamScout);
+    // waves that probe anything
+    const uint32_t used = scouts ? waves : part ? (uint32_t)((nwin + part - 1) / part) : 0;
     if (threadIdx.x == 0) issued = kept = 0;
     init_masks(ix, M, lane);
     __syncthreads();
     const uint64_t w_lo = min(nwin, wave * part), w_hi = min(nwin, w_lo + part);
-    const bool ee = opt.early_exit != 0;
     bool live = true;
     uint64_t got = 0;
-    if (w_lo < w_hi)
-        got = sweep_rep0<SEG, G>(ix, seqs, beg, end, w_lo, w_hi, lane, M, ee, false, 0, 0, live);
-    __syncthreads();
-    if (ee && used) {
-        // the read ends here if the parts' AND is empty
+    uint64_t *o = out + read * ix.W;
+    // the AND of the waves' repetition-0 masks is not empty (the same in every wave)
+    auto rep0_live = [&]() -> bool {
         uint32_t any = 0;
         for (uint32_t w = lane; w < ix.RW; w += 64) {
             uint32_t v = 0xFFFFFFFFu;
             for (uint32_t k = 0; k < used; k++) v &= M0[k * pitch + w];
             any |= v;
         }
-        live = __ballot(any != 0) != 0;
+        return __ballot(any != 0) != 0;
+    };
+    // the answer of a read that repetition 0 has ended
+    auto ended = [&]() {
+        if (opt.probes && lane == 0 && got) atomicAdd(opt.probes, (unsigned long long)(got * ix.eta));
+        if (!opt.counts)
+            for (uint32_t w = threadIdx.x; w < ix.W; w += blockDim.x) o[w] = 0;
+        else if (threadIdx.x == 0) opt.counts[read] = 0;
+    };
+    if (scouts) {
+        const uint64_t ns = scout_count(0, nwin);
+        for (uint64_t s0 = 0, s1; s0 < ns; s0 = s1) {
+            s1 = s0 ? ns : min<uint64_t>(ns, 64);
+            const uint64_t per = ((s1 - s0 + kGrain - 1) / kGrain + waves - 1) / waves * kGrain;
+            const uint64_t hi = min(s1, s0 + (wave + 1) * per);
+            for (uint64_t i0 = s0 + wave * per; i0 < hi; i0 += 64) {
+                Window wv{0, false};
+                if (i0 + lane < hi) {
+                    WinBytes wb;
+                    load_window_bytes(wb, seqs + beg + scout_pos(0, nwin, i0 + lane));
+                    wv = decode_window(wb);
+                }
+                (void)probe_group<SEG, G, 0, 1>(ix, step_params(ix), wv, wv.valid, lane, M);
+                got += (uint64_t)__popcll(__ballot(wv.valid));
+            }
+            __syncthreads();
+            live = rep0_live();
+            if (!live) {
+                ended();
+                return;
+            }
+            __syncthreads();  // (the masks change again)
+        }
     }
-    if (w_lo < w_hi && ix.R > 1 && (live || !ee))
-        got += sweep_rest<SEG, G>(ix, seqs, beg, end, w_lo, w_hi, lane, M, ee);
+    if (w_lo < w_hi)
+        got += sweep_rep0<SEG, G>(ix, seqs, beg, end, w_lo, w_hi, lane, M, ee, scouts, 0, nwin, live);
+    __syncthreads();
+    if (ee && used) {
+        // the read ends here if the parts' AND is empty
+        live = rep0_live();
+        if (!live) {
+            ended();
+            return;
+        }
+    }
+    if (w_lo < w_hi && ix.R > 1) got += sweep_rest<SEG, G>(ix, seqs, beg, end, w_lo, w_hi, lane, M, ee);
     if (lane == 0 && got) atomicAdd(&issued, (unsigned long long)got);
     __syncthreads();
     for (uint32_t w = threadIdx.x; w < mw; w += blockDim.x) {
@@ -119,7 +171,6 @@ __global__ __launch_bounds__(1024) void k_query_seqs_team(Index ix, const uint8_
         if (opt.probes && issued) atomicAdd(opt.probes, issued * ix.eta);
         if (issued == 0) atomicAdd(opt.emptyq, 1ULL);
     }
-    uint64_t *o = out + read * ix.W;
     if (masks_some_rep_empty(ix, M0, lane)) {
         if (!opt.counts)
             for (uint32_t w = threadIdx.x; w < ix.W; w += blockDim.x) o[w] = 0;
