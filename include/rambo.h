@@ -323,8 +323,8 @@ int rambo_query_seqs(rambo_t *h, const uint8_t *seqs, const uint64_t *offsets, u
  * term. An empty set answers every document (counted for rambo_sync as
  * RAMBO_OK_EMPTYQ). Device arrays (offsets n + 1
  * words, non-decreasing; out n * W words as rambo_query_kmers), asynchronous
- * on `stream`; one wave per set, repetition 0 over all terms before the
- * others; the resolve and early exit settings apply. */
+ * on `stream`; repetition 0 over all terms before the others; the resolve and
+ * early exit settings apply. */
 int rambo_query_term_sets(rambo_t *h, const uint64_t *terms, const uint64_t *offsets, uint64_t n, uint64_t *out,
                           void *stream);
 

@@ -187,7 +187,7 @@ __global__ __launch_bounds__(1024) void k_query_seqs_team(Index ix, const uint8_
 }
 
 // LDS of a team of waves: their masks and one candidate bitset.
-static size_t team_lds(const rambo_s *h, uint32_t waves, bool use_res) {
+size_t team_lds(const rambo_s *h, uint32_t waves, bool use_res) {
     return (size_t)waves * wave_lds(h->R * h->RW, h->W, false, false).total * 4 + (use_res ? (size_t)h->W * 8 : 0);
 }
 
@@ -199,7 +199,7 @@ static size_t team_lds(const rambo_s *h, uint32_t waves, bool use_res) {
 // 8,000 261-272 and 217-241; with 16 waves at 257 reads 49-60 and 47-52 (4: 55-66
 // and 57-62); with 8 at 512 57-65 and 49-53; with 4 at 2,000 114-135 and 77-85,
 // at 4,000 172-187 and 118-124, at 8,000 293-315 and 197-218.
-static uint32_t team_waves(const rambo_s *h, uint64_t n) {
+uint32_t team_waves(const rambo_s *h, uint64_t n) {
     const uint64_t cu = (uint64_t)h->n_cu;
     uint32_t t = n <= cu + cu / 8 ? 16 : n <= 2 * cu ? 8 : n <= 16 * cu ? 4 : 1;  // (past that only under capture and the like)
     while (t > 1 && team_lds(h, t, seq_lds_result(h->W)) + 64 > h->lds_max) t /= 2;

@@ -429,10 +429,11 @@ __device__ __forceinline__ bool masks_some_rep_empty(const Index &ix, const uint
 
 // Probe repetitions FIRST .. FIRST+COUNT-1 (those below R) with all their
 // loads in flight together and AND them into the running masks; returns
-// whether every one of those running masks is still non-empty.
+// whether every one of those running masks is still non-empty. Lanes from upto on
+// hold no term.
 template <int SEG, int G, int FIRST, int COUNT>
 __device__ __forceinline__ bool probe_group(const Index &ix, const HashRec *hp, const Window &wv, bool valid,
-                                            uint32_t lane, uint32_t *M) {
+                                            uint32_t lane, uint32_t *M, uint32_t upto = 64) {
     static_assert(FIRST + COUNT <= MAXR, "repetition group past MAXR");
     Seg<SEG> cm[COUNT];
 #pragma unroll
@@ -452,7 +453,7 @@ __device__ __forceinline__ bool probe_group(const Index &ix, const HashRec *hp, 
         if ((COUNT == 1 || (int)ix.R == FIRST + 1) && (ix.eta == 1 || ix.eta == 2)) {
             // one repetition, the rows of U sub-steps in flight together
 #pragma unroll 1
-            for (int s0 = 0; s0 < G; s0 += U) {
+            for (int s0 = 0; s0 < G && s0 * KPW < (int)upto; s0 += U) {
                 uint64_t xs[U];
                 bool vs[U];
                 bool any = false;
@@ -469,7 +470,7 @@ __device__ __forceinline__ bool probe_group(const Index &ix, const HashRec *hp, 
             }
         } else {
 #pragma unroll 1
-            for (int sub = 0; sub < G; sub++) {
+            for (int sub = 0; sub < G && sub * KPW < (int)upto; sub++) {
                 const int src = sub * KPW + (int)(lane / G);
                 const uint64_t x = __shfl(wv.canon, src);
                 const int v = __shfl((int)valid, src);

@@ -159,6 +159,9 @@ int launch_query_termsets(rambo_s *h, const uint64_t *terms, const uint64_t *off
                           hipStream_t s);
 
 // query.hip
+// Waves a read (or term set) of a batch of n gets, and the LDS of such a team.
+uint32_t team_waves(const rambo_s *h, uint64_t n);
+size_t team_lds(const rambo_s *h, uint32_t waves, bool use_res);
 // With hdr (device), the batch is read from it on the device and n is only
 // the capacity the grid is sized for. With counts, id-list mode (QueryOpts).
 int launch_query_seqs_plain(rambo_s *h, const uint8_t *seqs, const uint64_t *offs, uint64_t n,

@@ -241,24 +241,27 @@ __device__ __forceinline__ void resolve_chunk(const TermIndex &ix, const uint32_
     }
 }
 
-// The documents of slice blockIdx.y, in chunks of N words, every waves-th one
+// The documents of one of the slices, in chunks of N words, every waves-th one
 // from the wave-th: a batch of few groups is cut into slices so that it fills
 // the chip, each slice probing its group's terms again.
+struct Slice {
+    uint32_t at, of;
+};
 template <int R, int N, typename Q>
 __device__ __forceinline__ void resolve_chunks(const TermIndex &ix, const Q *T, uint64_t *__restrict__ out,
                                                uint64_t base, uint32_t nq, uint32_t wave, uint32_t waves,
-                                               uint32_t lane, const Transpose &tp) {
-    const uint32_t chunks = (ix.W + N - 1) / N, per = (chunks + gridDim.y - 1) / gridDim.y;
-    const uint32_t c0 = min(chunks, blockIdx.y * per), c1 = min(chunks, c0 + per);
+                                               uint32_t lane, const Transpose &tp, Slice sl) {
+    const uint32_t chunks = (ix.W + N - 1) / N, per = (chunks + sl.of - 1) / sl.of;
+    const uint32_t c0 = min(chunks, sl.at * per), c1 = min(chunks, c0 + per);
     for (uint32_t c = c0 + wave; c < c1; c += waves) resolve_chunk<R, N>(ix, T, out, base, nq, c, lane, tp);
 }
 
 template <int N, typename Q>
 __device__ __forceinline__ void resolve_group(const TermIndex &ix, const Q *T, uint64_t *__restrict__ out,
                                               uint64_t base, uint32_t nq, uint32_t wave, uint32_t waves,
-                                              uint32_t lane, const Transpose &tp) {
+                                              uint32_t lane, const Transpose &tp, Slice sl) {
     switch (ix.R) {
-#define RAMBO_R_(R_) case R_: resolve_chunks<R_, N>(ix, T, out, base, nq, wave, waves, lane, tp); break;
+#define RAMBO_R_(R_) case R_: resolve_chunks<R_, N>(ix, T, out, base, nq, wave, waves, lane, tp, sl); break;
     RAMBO_R_(1) RAMBO_R_(2) RAMBO_R_(3) RAMBO_R_(4) RAMBO_R_(5) RAMBO_R_(6) RAMBO_R_(7) RAMBO_R_(8)
 #undef RAMBO_R_
     }
@@ -356,7 +359,7 @@ __global__ __launch_bounds__(256) void k_terms_lane(TermIndex ix, const uint64_t
     }
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
-    resolve_group<16>(ix, T, out, base, (uint32_t)min<uint64_t>(64, n - base), 0, 1, lane, tp);
+    resolve_group<16>(ix, T, out, base, (uint32_t)min<uint64_t>(64, n - base), 0, 1, lane, tp, Slice{blockIdx.y, gridDim.y});
 }
 
 // Wider rows: G = 2^lg lanes share a term's row (4 words each) and a workgroup
@@ -410,109 +413,220 @@ __global__ __launch_bounds__(1024) void k_terms_group(TermIndex ix, const uint64
     __syncthreads();
     transpose_blocks(T, ix.R * t_blocks(ix.B), wave, waves, lane, tp);
     __syncthreads();
-    resolve_group<16>(ix, T, out, base, (uint32_t)min<uint64_t>(kQ, n - base), wave, waves, lane, tp);
+    resolve_group<16>(ix, T, out, base, (uint32_t)min<uint64_t>(kQ, n - base), wave, waves, lane, tp,
+                      Slice{blockIdx.y, gridDim.y});
 }
+
+// Rows of U terms in repetitions FIRST .. FIRST + COUNT - 1 (those below R), all
+// loads before any use; a term that there is not reads row 0 of the repetition.
+template <int SEG, int FIRST, int COUNT, int U, int ETA>
+__device__ __forceinline__ void probe_steps_eta(const Index &ix, const HashRec *hp, const uint64_t (&x)[U],
+                                                const bool (&has)[U], uint32_t seg, Seg<SEG> (&cm)[U][COUNT]) {
+    Seg<SEG> v[U][COUNT][ETA];
+#pragma unroll
+    for (int u = 0; u < U; u++)
+#pragma unroll
+        for (int k = 0; k < COUNT; k++)
+            if (FIRST + k < (int)ix.R)
+#pragma unroll
+                for (int j = 0; j < ETA; j++) {
+                    const uint64_t pos = has[u] ? bloom_pos(hash_rec(hp, (FIRST + k) * ETA + j), ix.m, x[u]) : 0;
+                    v[u][k][j] = load_seg<SEG>(row_ptr(ix, FIRST + k, pos) + seg * SEG);
+                }
+#pragma unroll
+    for (int u = 0; u < U; u++)
+#pragma unroll
+        for (int k = 0; k < COUNT; k++)
+            if (FIRST + k < (int)ix.R)
+#pragma unroll
+                for (int j = 0; j < ETA; j++)
+#pragma unroll
+                    for (int s = 0; s < SEG; s++) cm[u][k].w[s] &= v[u][k][j].w[s];
+}
+template <int SEG, int FIRST, int COUNT, int U>
+__device__ __forceinline__ void probe_steps(const Index &ix, const HashRec *hp, const uint64_t (&x)[U],
+                                            const bool (&has)[U], uint32_t seg, Seg<SEG> (&cm)[U][COUNT]) {
+    if (ix.eta == 2) probe_steps_eta<SEG, FIRST, COUNT, U, 2>(ix, hp, x, has, seg, cm);
+    else if (ix.eta == 1) probe_steps_eta<SEG, FIRST, COUNT, U, 1>(ix, hp, x, has, seg, cm);
+    else
+#pragma unroll
+        for (int u = 0; u < U; u++)
+            if (has[u]) probe_reps<SEG, FIRST, COUNT>(ix, hp, x[u], seg, cm[u]);
+}
+
+// A group's term sets on their way through the repetitions: lane t of every wave
+// holds set t (terms[beg .. beg + len)), alive the sets that no mask has ended.
+struct SetGroup {
+    const uint64_t *terms;
+    uint64_t beg, len, alive;
+    uint64_t *T;
+    uint32_t lane, wave, waves, lg;  // 2^lg lanes share a row
+    bool early_exit;
+    uint64_t issued;  // probes of the group
+};
 
 // ANDs repetitions FIRST .. FIRST + COUNT - 1 of the rows of the group's sets
 // into their masks in T. The sets' terms are taken in rounds, of up to 64 of
-// each set at first and twice as many (to 1,024) each time; a round's terms are one flat list, 64 / G of them a wave at a time,
-// so that sets of a few terms keep every wave's loads in flight. After a round
-// (with early exit) a set one of whose masks is empty is done: alive holds the
-// others, the same in every wave. Called by the whole workgroup.
-template <int SEG, int FIRST, int COUNT>
-__device__ __forceinline__ void and_sets(const Index &ix, const uint64_t *__restrict__ terms, uint64_t beg,
-                                         uint64_t len, bool early_exit, uint32_t lg, uint32_t wave, uint32_t waves,
-                                         uint32_t lane, uint64_t *T, uint64_t &alive, uint64_t &issued) {
-    const uint32_t per = 64u >> lg, g = lane >> lg, seg = lane & ((1u << lg) - 1), nb = t_blocks(ix.B);
-    const uint32_t reps = min(ix.R - FIRST, (uint32_t)COUNT);
+// each set at first and twice as many (to 1,024) each time; a round's terms are
+// one flat list, 64 >> lg of them a wave at a time and U such steps in flight, so
+// that sets of a few terms keep every wave's loads in flight. After a round
+// (with early exit) a set one of whose masks is empty is done. Called by the whole
+// workgroup.
+template <int SEG, int FIRST, int COUNT, int U>
+__device__ __forceinline__ void and_sets(const Index &ix, SetGroup &g) {
+    const uint32_t lane = g.lane, per = 64u >> g.lg, in = lane >> g.lg, seg = lane & ((1u << g.lg) - 1);
+    const uint32_t nb = t_blocks(ix.B), reps = min(ix.R - FIRST, (uint32_t)COUNT);
     uint32_t step = 64;
     for (uint64_t at = 0;; at += step, step = min(2 * step, 1024u)) {
-        const uint32_t cnt = ((alive >> lane) & 1) && len > at ? (uint32_t)min<uint64_t>(step, len - at) : 0;
-        uint32_t incl = cnt;
-#pragma unroll
-        for (int d = 1; d < 64; d <<= 1) {
-            const uint32_t v = __shfl_up(incl, d);
-            if ((int)lane >= d) incl += v;
-        }
+        const uint32_t cnt = ((g.alive >> lane) & 1) && g.len > at ? (uint32_t)min<uint64_t>(step, g.len - at) : 0;
+        const uint32_t incl = wave_inclusive(cnt, lane);
         const uint32_t total = __shfl(incl, 63);
         if (total == 0) return;
-        const uint64_t src = beg + at - (incl - cnt);  // item i of this lane's set is terms[src + i]
-        for (uint32_t i0 = wave * per; i0 < total; i0 += waves * per) {
-            const uint32_t i = i0 + g;
-            uint32_t t = 0;  // owner of item i: the number of sets whose inclusive sum is <= i
+        const uint64_t src = g.beg + at - (incl - cnt);  // item i of this lane's set is terms[src + i]
+        for (uint32_t i0 = g.wave * per; i0 < total; i0 += U * g.waves * per) {
+            uint32_t own[U];
+            uint64_t x[U];
+            bool has[U];
 #pragma unroll
-            for (uint32_t st = 32; st; st >>= 1)
-                if (__shfl(incl, (int)(t + st - 1)) <= i) t += st;
-            const uint64_t from = __shfl(src, (int)(t & 63));
-            if (i >= total || seg * (SEG * 32) >= ix.B) continue;
-            uint64_t x = terms[from + i];
-            if (!ix.opaque) x = canonical(x);
-            Seg<SEG> cm[COUNT];
-            fill_masks(cm, 0xFFFFFFFFu);
-            probe_reps<SEG, FIRST, COUNT>(ix, step_params(ix), x, seg, cm);
+            for (int u = 0; u < U; u++) {
+                const uint32_t i = i0 + u * g.waves * per + in;
+                uint32_t t = 0;  // owner of item i: the number of sets whose inclusive sum is <= i
 #pragma unroll
-            for (int r = 0; r < COUNT; r++) {
-                if (FIRST + r >= (int)ix.R) continue;
+                for (uint32_t st = 32; st; st >>= 1)
+                    if (__shfl(incl, (int)(t + st - 1)) <= i) t += st;
+                own[u] = t;
+                const uint64_t from = __shfl(src, (int)(t & 63));
+                has[u] = i < total && seg * (SEG * 32) < ix.B;
+                x[u] = has[u] ? g.terms[from + i] : 0;
+            }
+            Seg<SEG> cm[U][COUNT];
 #pragma unroll
-                for (int s = 0; s < SEG; s += 2) {
-                    const uint32_t k = (seg * SEG + s) / 2;
-                    uint64_t v = cm[r].w[s];
-                    if constexpr (SEG > 1) v |= (uint64_t)cm[r].w[s + 1] << 32;
-                    if (k < nb)
-                        __hip_atomic_fetch_and(&T[((FIRST + r) * nb + k) * kBlockWords + t], v, __ATOMIC_RELAXED,
-                                               __HIP_MEMORY_SCOPE_WORKGROUP);
+            for (int u = 0; u < U; u++) {
+                if (!ix.opaque) x[u] = canonical(x[u]);
+                fill_masks(cm[u], 0xFFFFFFFFu);
+            }
+            if constexpr (U == 1) {
+                if (has[0]) probe_reps<SEG, FIRST, COUNT>(ix, step_params(ix), x[0], seg, cm[0]);
+            } else {
+                // (rows of terms that there are not: row 0, in range, unused)
+                probe_steps<SEG, FIRST, COUNT, U>(ix, step_params(ix), x, has, seg, cm);
+            }
+#pragma unroll
+            for (int u = 0; u < U; u++) {
+                if (!has[u]) continue;
+#pragma unroll
+                for (int r = 0; r < COUNT; r++) {
+                    if (FIRST + r >= (int)ix.R) continue;
+#pragma unroll
+                    for (int s = 0; s < SEG; s += 2) {
+                        const uint32_t k = (seg * SEG + s) / 2;
+                        uint64_t v = cm[u][r].w[s];
+                        if constexpr (SEG > 1) v |= (uint64_t)cm[u][r].w[s + 1] << 32;
+                        if (k < nb)
+                            __hip_atomic_fetch_and(&g.T[((FIRST + r) * nb + k) * kBlockWords + own[u]], v,
+                                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                    }
                 }
             }
         }
-        issued += (uint64_t)total * reps;
+        g.issued += (uint64_t)total * reps;
         __syncthreads();
-        if (early_exit) {
-            bool live = (alive >> lane) & 1;
+        if (g.early_exit) {
+            bool live = (g.alive >> lane) & 1;
             for (uint32_t r = FIRST; r < FIRST + reps; r++) {
                 uint64_t o = 0;
-                for (uint32_t k = 0; k < nb; k++) o |= T[(r * nb + k) * kBlockWords + lane];
+                for (uint32_t k = 0; k < nb; k++) o |= g.T[(r * nb + k) * kBlockWords + lane];
                 live = live && o != 0;
             }
-            alive = __ballot(live);
+            g.alive = __ballot(live);
             __syncthreads();
         }
     }
 }
 
-// Term sets: a workgroup resolves tq <= 64 sets, repetition 0 over all their
+// The answers of a group with few positive cells, a wave a set: the sets that
+// have ended get zeros, the others are resolved from their own masks (in M; only
+// the first mwaves waves have room for them).
+__device__ __forceinline__ void resolve_sets(const TermIndex &ix, const SetGroup &g, uint64_t *__restrict__ out,
+                                             uint64_t base, uint32_t nq, uint32_t *M, uint32_t mwaves, int rmode,
+                                             Slice sl) {
+    const uint32_t lane = g.lane, nb = t_blocks(ix.B);
+    uint32_t live = 0, ended = 0;
+    for (uint32_t t = 0; t < nq; t++) {
+        uint64_t *o = out + (base + t) * ix.W;
+        if (!((g.alive >> t) & 1)) {
+            if (ended++ % (g.waves * sl.of) == g.wave * sl.of + sl.at) write_zeros(o, ix.W, lane);
+            continue;
+        }
+        if (live++ % (mwaves * sl.of) != g.wave * sl.of + sl.at) continue;
+        for (uint32_t w = lane; w < ix.R * ix.RW; w += 64) {
+            const uint32_t r = w / ix.RW, k = (w % ix.RW) / 2;
+            const uint64_t v = k < nb ? g.T[(r * nb + k) * kBlockWords + t] : 0;
+            M[w] = (uint32_t)(w % ix.RW & 1 ? v >> 32 : v);
+        }
+        OneWave().sync();
+        (void)resolve(ix, M, nullptr, o, lane, rmode);
+        OneWave().sync();
+    }
+}
+
+// Groups of term sets that are short on average (up to kShortSet terms) take
+// k_sets_group, the others k_sets_long, which both find out from the offsets: a
+// batch launches both. Past that the flat list's LDS atomic a term costs more than
+// a wave a set (ClueWeb-like, 30,000 sets of 64 words 1.73 ms flat, 0.99 a wave
+// each; of 4 words 0.43 and 1.85).
+constexpr uint32_t kShortSet = 16;
+__device__ __forceinline__ bool short_sets(uint64_t len, uint32_t nq) {
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) len += __shfl_xor(len, d);
+    return len <= (uint64_t)kShortSet * nq;
+}
+
+// Term sets: a workgroup answers tq <= 64 sets, repetition 0 over all their
 // terms first, then the others (Section 3.3.1). Bound by round trips: the
 // offsets, the terms, two rounds of rows, and the result stores (Wiki-like,
 // 17,618 documents, R=2, B=1,000, 100,000 sets of 2 to 8 terms, 0.22 GB of
 // results: 1.44 ms with a wave and a resolve per set, 0.21 ms with a wave per
 // set and the group's resolve, 0.14 ms with the flat list of terms).
+// The group's resolve costs the same whatever its masks hold (K=101,000, 8 sets:
+// 75 us). Where the sets' own resolves are estimated to take fewer round trips (512
+// documents, or kSlotsAhead slots of 64) they are resolved one by one, and those
+// that have ended cost their zeros (30,000 sets of 4 random 31-mers at K=101,000:
+// 440 us with the group's resolve, 118 without).
 template <int SEG>
 __global__ __launch_bounds__(1024) void k_sets_group(TermIndex ix, const uint64_t *__restrict__ terms,
                                                      const uint64_t *__restrict__ offs, uint64_t n,
                                                      uint64_t *__restrict__ out, QueryOpts opt,
-                                                     unsigned long long *invalid, uint32_t lg, uint32_t tq) {
+                                                     unsigned long long *invalid, uint32_t lg, uint32_t tq,
+                                                     uint32_t mwaves) {
     extern __shared__ uint64_t smem64[];
-    uint64_t *T = smem64;
     __shared__ unsigned long long bad_sets;
     const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6, waves = blockDim.x >> 6;
     const uint64_t base = (uint64_t)blockIdx.x * tq;
     const uint32_t nq = (uint32_t)min<uint64_t>(tq, n - base);
-    const Transpose tp(lane);
-    const bool counts = blockIdx.y == 0 && wave == 0;  // once per set, whatever the slices
-    uint64_t beg = 0, len = 0;
+    const Slice sl{blockIdx.y, gridDim.y};
+    SetGroup g;
+    g.terms = terms;
+    g.T = smem64;
+    g.lane = lane; g.wave = wave; g.waves = waves; g.lg = lg;
+    g.early_exit = opt.early_exit != 0;
+    g.beg = g.len = g.issued = 0;
     if (lane < nq) {
-        beg = offs[base + lane];
+        g.beg = offs[base + lane];
         const uint64_t end = offs[base + lane + 1];
-        len = end > beg ? end - beg : 0;
+        g.len = end > g.beg ? end - g.beg : 0;
     }
-    if (counts && lane < nq && len == 0) atomicAdd(opt.emptyq, 1ULL);
-    uint64_t alive = __ballot(lane < nq);
+    if (!short_sets(g.len, nq)) return;
+    const bool counts = sl.at == 0 && wave == 0;  // once per set, whatever the slices
+    if (counts && lane < nq && g.len == 0) atomicAdd(opt.emptyq, 1ULL);
+    g.alive = __ballot(lane < nq);
     if (!ix.opaque) {
         // a k-mer index takes 31-mer codes only: a set holding another value
         // answers no document
         if (threadIdx.x == 0) bad_sets = 0;
         __syncthreads();
         for (uint32_t t = wave; t < nq; t += waves) {
-            const uint64_t b = __shfl(beg, (int)t), l = __shfl(len, (int)t);
+            const uint64_t b = __shfl(g.beg, (int)t), l = __shfl(g.len, (int)t);
             bool bad = false;
             for (uint64_t w = 0; w < l && !bad; w += 64)
                 bad = __ballot(w + lane < l && (terms[b + w + lane] >> 62)) != 0;
@@ -521,20 +635,130 @@ __global__ __launch_bounds__(1024) void k_sets_group(TermIndex ix, const uint64_
         __syncthreads();
         const uint64_t bad = bad_sets;
         if (counts && lane == 0 && bad) atomicAdd(invalid, (unsigned long long)__popcll(bad));
-        alive &= ~bad;
+        g.alive &= ~bad;
     }
-    const uint32_t blocks = ix.R * t_blocks(ix.B);
-    for (uint32_t k = wave; k < blocks; k += waves) T[k * kBlockWords + lane] = (alive >> lane) & 1 ? ~0ULL : 0;
+    const uint32_t nb = t_blocks(ix.B), blocks = ix.R * nb;
+    for (uint32_t k = wave; k < blocks; k += waves) g.T[k * kBlockWords + lane] = (g.alive >> lane) & 1 ? ~0ULL : 0;
     __syncthreads();
-    uint64_t issued = 0;
+    // (few repetitions: several steps in flight instead)
+    and_sets<SEG, 0, 1, 4>(ix, g);
+    if (ix.R == 2) and_sets<SEG, 1, 1, 4>(ix, g);
+    else if (ix.R == 3) and_sets<SEG, 1, 2, 2>(ix, g);
+    else if (ix.R > 3) and_sets<SEG, 1, 4, 1>(ix, g);
+    if (ix.R > 5) and_sets<SEG, 5, 3, 1>(ix, g);
+    if (opt.probes && wave == 0 && lane == 0 && g.issued) atomicAdd(opt.probes, (unsigned long long)(g.issued * ix.eta));
+    const uint32_t live = (uint32_t)__popcll(g.alive);
+    uint64_t cells = 0;  // positive repetition-0 cells of the sets alive
+    if (live) {
+        for (uint32_t k = 0; k < nb; k++) cells += (uint32_t)__popcll(g.T[k * kBlockWords + lane]);
+        if (!((g.alive >> lane) & 1)) cells = 0;
+#pragma unroll
+        for (int d = 32; d > 0; d >>= 1) cells += __shfl_xor(cells, d);
+    }
+    const uint64_t slots = cells * (((ix.K + ix.B - 1) / ix.B + 63) / 64);
+    const uint64_t own = (slots / kSlotsAhead + 2 * live) / max(1u, min(live, mwaves * sl.of));
+    if (live == 0 || own < (ix.W + 7) / 8 / (waves * sl.of)) {
+        uint32_t *M = reinterpret_cast<uint32_t *>(g.T + t_words(ix.R, ix.B)) + wave * ix.R * ix.RW;
+        resolve_sets(ix, g, out, base, nq, M, mwaves, opt.rmode, sl);
+        return;
+    }
+    const Transpose tp(lane);
+    __syncthreads();  // (every wave has read T for its choice)
+    transpose_blocks(g.T, blocks, wave, waves, lane, tp);
+    __syncthreads();
+    resolve_group<8>(ix, g.T, out, base, nq, wave, waves, lane, tp, sl);
+}
+
+// A small batch of term sets of any length: a workgroup of up to 16 waves per set,
+// as k_query_seqs_team for reads, the waves sharing the set's terms. Bound by the
+// chain of round trips. One launch: two would cost the smallest batches 4 us of 20.
+template <int SEG, int G>
+__global__ __launch_bounds__(1024) void k_sets_team(Index ix, const uint64_t *__restrict__ terms,
+                                                    const uint64_t *__restrict__ offs, uint64_t *__restrict__ out,
+                                                    QueryOpts opt, unsigned long long *invalid, int use_res) {
+    extern __shared__ __align__(16) uint64_t smem64[];
+    __shared__ unsigned long long issued;
+    __shared__ uint32_t bad;
+    const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6, waves = blockDim.x >> 6;
+    const uint32_t mw = ix.R * ix.RW, pitch = wave_lds(mw, ix.W, false, false).total;
+    uint32_t *M0 = reinterpret_cast<uint32_t *>(smem64), *M = M0 + wave * pitch;
+    uint64_t *res = use_res ? reinterpret_cast<uint64_t *>(M0 + waves * pitch) : nullptr;
+    const uint64_t beg = offs[blockIdx.x], end = offs[blockIdx.x + 1], len = end > beg ? end - beg : 0;
+    constexpr uint32_t kGrain = 64 / G;
+    const uint64_t part = ((len + kGrain - 1) / kGrain + waves - 1) / waves * kGrain;  // terms per wave
+    const uint32_t used = part ? (uint32_t)((len + part - 1) / part) : 0;            // waves that have any
+    const uint64_t lo = min(len, wave * part), hi = min(len, lo + part);
     const bool ee = opt.early_exit != 0;
-    and_sets<SEG, 0, 1>(ix, terms, beg, len, ee, lg, wave, waves, lane, T, alive, issued);
-    if (ix.R > 1) and_sets<SEG, 1, 4>(ix, terms, beg, len, ee, lg, wave, waves, lane, T, alive, issued);
-    if (ix.R > 5) and_sets<SEG, 5, 3>(ix, terms, beg, len, ee, lg, wave, waves, lane, T, alive, issued);
-    if (opt.probes && counts && lane == 0 && issued) atomicAdd(opt.probes, (unsigned long long)(issued * ix.eta));
-    transpose_blocks(T, blocks, wave, waves, lane, tp);
+    uint64_t *o = out + (uint64_t)blockIdx.x * ix.W;
+    if (threadIdx.x == 0) {
+        issued = 0;
+        bad = 0;
+        if (len == 0) atomicAdd(opt.emptyq, 1ULL);
+    }
+    init_masks(ix, M, lane);
     __syncthreads();
-    resolve_group<8>(ix, T, out, base, nq, wave, waves, lane, tp);
+    auto load = [&](uint64_t w) -> Window {
+        Window wv;
+        wv.valid = w + lane < hi;
+        wv.canon = wv.valid ? terms[beg + w + lane] : 0;
+        return wv;
+    };
+    uint64_t got = 0;
+    bool odd = false;  // a value that is no 31-mer: the set answers no document
+    bool alive = true;
+    for (uint64_t w = lo; w < hi; w += 64) {
+        Window wv = load(w);
+        if (!ix.opaque) {
+            odd |= (wv.canon >> 62) != 0;
+            wv.canon = canonical(wv.canon & MASK62);
+        }
+        if (ee && !alive) continue;  // (the rest is looked through for such values)
+        alive = probe_group<SEG, G, 0, 1>(ix, step_params(ix), wv, wv.valid, lane, M, (uint32_t)min<uint64_t>(64, hi - w));
+        got += min<uint64_t>(64, hi - w);
+        if (ee && !alive && ix.opaque) break;
+    }
+    if (odd) bad = 1;
+    if (opt.probes && lane == 0 && got) atomicAdd(&issued, (unsigned long long)got);
+    __syncthreads();
+    uint32_t any = 0;  // the parts' AND in repetition 0
+    for (uint32_t w = lane; w < ix.RW; w += 64) {
+        uint32_t v = 0xFFFFFFFFu;
+        for (uint32_t k = 0; k < used; k++) v &= M0[k * pitch + w];
+        any |= v;
+    }
+    const bool live = !bad && (!ee || __ballot(any != 0) != 0);
+    if (bad && threadIdx.x == 0) atomicAdd(invalid, 1ULL);
+    if (live && ix.R > 1) {
+        got = 0;
+        for (uint64_t w = lo; w < hi; w += 64) {
+            Window wv = load(w);
+            if (!ix.opaque) wv.canon = canonical(wv.canon);
+            const uint32_t nv = (uint32_t)min<uint64_t>(64, hi - w);
+            alive = probe_group<SEG, G, 1, 4>(ix, step_params(ix), wv, wv.valid, lane, M, nv);
+            got += nv * (min(ix.R, 5u) - 1);
+            if ((int)ix.R > 5 && (alive || !ee)) {
+                alive &= probe_group<SEG, G, 5, MAXR - 5>(ix, step_params(ix), wv, wv.valid, lane, M, nv);
+                got += nv * (ix.R - 5);
+            }
+            if (ee && !alive) break;
+        }
+        if (opt.probes && lane == 0 && got) atomicAdd(&issued, (unsigned long long)got);
+        __syncthreads();
+    }
+    if (opt.probes && threadIdx.x == 0 && issued) atomicAdd(opt.probes, issued * ix.eta);
+    if (live) {
+        for (uint32_t w = threadIdx.x; w < mw; w += blockDim.x) {
+            uint32_t v = M0[w];
+            for (uint32_t k = 1; k < used; k++) v &= M0[k * pitch + w];
+            M0[w] = v;
+        }
+        __syncthreads();
+    }
+    if (!live || masks_some_rep_empty(ix, M0, lane)) {
+        for (uint32_t w = threadIdx.x; w < ix.W; w += blockDim.x) o[w] = 0;
+        return;
+    }
+    (void)resolve(ix, M0, res, o, lane, opt.rmode, nullptr, WholeGroup{wave, waves});
 }
 
 // ---------------------------------------------------------------------------
@@ -602,23 +826,14 @@ __global__ __launch_bounds__(256) void k_query_kmers(Index ix, const uint64_t *_
     }
 }
 
-// -------------------------------------------------------------------------
-// term-set queries: one wave per set, 64 terms per step; repetition 0 over
-// every term first, then the other repetitions (Section 3.3.1 order)
-// -------------------------------------------------------------------------
+// One term set by one wave (M: its masks in LDS; res: LDS bitset of W words, or
+// null), 64 terms per step; repetition 0 over every term first, then the other
+// repetitions (Section 3.3.1 order).
 template <int SEG, int G>
-__global__ __launch_bounds__(256) void k_query_termsets(Index ix, const uint64_t *__restrict__ terms,
-                                                        const uint64_t *__restrict__ offs, uint64_t n,
-                                                        uint64_t *__restrict__ out, QueryOpts opt, int use_res,
-                                                        unsigned long long *invalid) {
-    extern __shared__ __align__(16) uint64_t smem64[];
-    const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const WaveLds L = wave_lds(ix.R * ix.RW, ix.W, use_res != 0, false);
-    uint32_t *M = reinterpret_cast<uint32_t *>(smem64) + wave * L.total;
-    uint64_t *res = use_res ? reinterpret_cast<uint64_t *>(M + L.res) : nullptr;
-
-    const uint64_t q = (uint64_t)blockIdx.x * (blockDim.x >> 6) + wave;
-    if (q >= n) return;
+__device__ __forceinline__ void answer_set(const Index &ix, const uint64_t *__restrict__ terms,
+                                           const uint64_t *__restrict__ offs, uint64_t q, uint64_t *__restrict__ out,
+                                           const QueryOpts &opt, uint32_t *M, uint64_t *res,
+                                           unsigned long long *invalid, uint32_t lane) {
     const uint64_t beg = offs[q];
     uint64_t end = offs[q + 1];
     if (end < beg) end = beg;
@@ -648,16 +863,16 @@ __global__ __launch_bounds__(256) void k_query_termsets(Index ix, const uint64_t
             Window wv;
             wv.canon = ix.opaque ? x : canonical(x);
             wv.valid = valid;
-            const uint64_t nv = (uint64_t)__popcll(__ballot(valid));
+            const uint32_t nv = (uint32_t)min<uint64_t>(64, len - w);
             bool alive;
             if (pass == 0) {
-                alive = probe_group<SEG, G, 0, 1>(ix, step_params(ix), wv, valid, lane, M);
+                alive = probe_group<SEG, G, 0, 1>(ix, step_params(ix), wv, valid, lane, M, nv);
                 issued += nv;
             } else {
-                alive = probe_group<SEG, G, 1, 4>(ix, step_params(ix), wv, valid, lane, M);
+                alive = probe_group<SEG, G, 1, 4>(ix, step_params(ix), wv, valid, lane, M, nv);
                 issued += nv * (min(ix.R, 5u) - 1);
                 if ((int)ix.R > 5 && (alive || !opt.early_exit)) {
-                    alive &= probe_group<SEG, G, 5, MAXR - 5>(ix, step_params(ix), wv, valid, lane, M);
+                    alive &= probe_group<SEG, G, 5, MAXR - 5>(ix, step_params(ix), wv, valid, lane, M, nv);
                     issued += nv * (ix.R - 5);
                 }
             }
@@ -675,6 +890,39 @@ __global__ __launch_bounds__(256) void k_query_termsets(Index ix, const uint64_t
         return;
     }
     resolve(ix, M, res, o, lane, opt.rmode);
+}
+
+// A wave takes `take` consecutive sets. With tq (a multiple of take), only the sets
+// of groups of tq that k_sets_group leaves (short_sets): the grid is then one of
+// 64 to 128 waves a compute unit, so that a batch without such groups costs a launch
+// and one look at the offsets (a wave a set: 14 us for 100,000 sets).
+template <int SEG, int G>
+__global__ __launch_bounds__(256) void k_sets_long(Index ix, const uint64_t *__restrict__ terms,
+                                                   const uint64_t *__restrict__ offs, uint64_t n,
+                                                   uint64_t *__restrict__ out, QueryOpts opt, int use_res,
+                                                   unsigned long long *invalid, uint32_t tq, uint32_t take) {
+    extern __shared__ __align__(16) uint64_t smem64[];
+    const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const WaveLds L = wave_lds(ix.R * ix.RW, ix.W, use_res != 0, false);
+    uint32_t *M = reinterpret_cast<uint32_t *>(smem64) + wave * L.total;
+    uint64_t *res = use_res ? reinterpret_cast<uint64_t *>(M + L.res) : nullptr;
+
+    const uint64_t q0 = ((uint64_t)blockIdx.x * (blockDim.x >> 6) + wave) * take;
+    if (q0 >= n) return;
+    if (tq) {
+        const uint64_t base = q0 - q0 % tq;
+        const uint32_t nq = (uint32_t)min<uint64_t>(tq, n - base);
+        uint64_t l = 0;
+        if (lane < nq) {
+            const uint64_t b = offs[base + lane], e = offs[base + lane + 1];
+            l = e > b ? e - b : 0;
+        }
+        if (short_sets(l, nq)) return;
+    }
+    for (uint64_t q = q0; q < min(n, q0 + take); q++) {
+        answer_set<SEG, G>(ix, terms, offs, q, out, opt, M, res, invalid, lane);
+        OneWave().sync();
+    }
 }
 
 static constexpr uint32_t kMaxLds = 64 * 1024;  // of the general path
@@ -773,8 +1021,9 @@ int launch_query_kmers(rambo_s *h, const uint64_t *kmers, uint64_t n, uint64_t *
     return RAMBO_OK;
 }
 
-static int general_query_termsets(rambo_s *h, const uint64_t *terms, const uint64_t *offs, uint64_t n, uint64_t *out,
-                                  hipStream_t s) {
+// A wave a set: all sets, or those of long groups of tq.
+static int launch_sets_long(rambo_s *h, const uint64_t *terms, const uint64_t *offs, uint64_t n, uint64_t *out,
+                            hipStream_t s, const QueryOpts &opt, uint32_t tq) {
     const Index ix = make_index(h);
     const int seg = default_seg(h->RW), G = (int)h->RW / seg;
     const int WPB = 4;
@@ -784,41 +1033,68 @@ static int general_query_termsets(rambo_s *h, const uint64_t *terms, const uint6
         use_res = 0;
         lds = (size_t)WPB * wave_lds(h->R * h->RW, h->W, false, false).total * 4;
     }
-    const uint64_t blocks = (n + WPB - 1) / WPB;
+    uint32_t take = 1;
+    while (2 * take <= tq && n > (uint64_t)take * h->n_cu * 128) take *= 2;
+    const uint64_t blocks = (n + (uint64_t)WPB * take - 1) / ((uint64_t)WPB * take);
     if (blocks > 0x7FFFFFFFULL) return fail(RAMBO_EINVAL, "rambo_query_term_sets: batch too large");
-    QueryOpts opt{h->resolve, h->early_exit, h->probe_counter, SCHED_SWEEP, nullptr, h->d_emptyq};
 #define RAMBO_SPLIT_BODY_                                                                                  \
-    hipLaunchKernelGGL((k_query_termsets<SEG, G>), dim3((unsigned)blocks), dim3(64 * WPB), lds, s, ix, terms, offs, \
-                       n, out, opt, use_res, h->d_invalid)
+    hipLaunchKernelGGL((k_sets_long<SEG, G>), dim3((unsigned)blocks), dim3(64 * WPB), lds, s, ix, terms, offs, n, out, \
+                       opt, use_res, h->d_invalid, tq, take)
     RAMBO_DISPATCH_DEFAULT_SPLIT(seg, G)
 #undef RAMBO_SPLIT_BODY_
     HIP_CHECK(hipGetLastError());
     return RAMBO_OK;
 }
 
+// A workgroup a set up to four a compute unit (3,000 sets of 64 words, Wiki-like: 54
+// us, 38 with a wave each; 1,000 30 and 32), then groups of sets, short and long
+// ones; a wave a set for the candidate strategy and for indexes whose T does not fit
+// LDS.
 int launch_query_termsets(rambo_s *h, const uint64_t *terms, const uint64_t *offs, uint64_t n, uint64_t *out,
                           hipStream_t s) {
-    if (!group_resolve(h)) return general_query_termsets(h, terms, offs, n, out, s);
+    const QueryOpts opt{h->resolve, h->early_exit, h->probe_counter, SCHED_SWEEP, nullptr, h->d_emptyq};
+    const uint32_t team = n <= 4 * (uint64_t)h->n_cu ? team_waves(h, n) : 1;
+    if (team > 1) {
+        const Index ix = make_index(h);
+        const int seg = default_seg(h->RW), G = (int)h->RW / seg, use_res = seq_lds_result(h->W) ? 1 : 0;
+        const size_t lds = team_lds(h, team, use_res != 0);
+#define RAMBO_SPLIT_BODY_                                                                                  \
+    hipLaunchKernelGGL((k_sets_team<SEG, G>), dim3((unsigned)n), dim3(64 * team), lds, s, ix, terms, offs, out, opt,   \
+                       h->d_invalid, use_res)
+        RAMBO_DISPATCH_DEFAULT_SPLIT(seg, G)
+#undef RAMBO_SPLIT_BODY_
+        HIP_CHECK(hipGetLastError());
+        return RAMBO_OK;
+    }
+    // a wave a set where the resolve is short (W <= 16) and the chip not yet full: the
+    // second launch costs more than the groups save (5,000 sets of 4 terms at K=100
+    // 27 us, 33 in groups; 30,000 65 and 44)
+    const bool few = h->W <= 16 && n <= 32 * (uint64_t)h->n_cu;
+    // T and the masks of four waves at least
+    const size_t tbytes = (size_t)t_words(h->R, h->B) * 8, mbytes = (size_t)h->R * h->RW * 4;
+    if (few || !group_resolve(h) || tbytes + 4 * mbytes + 64 > h->lds_max)
+        return launch_sets_long(h, terms, offs, n, out, s, opt, 0);
     const TermIndex ix = term_index(h);
-    // sets of a group: 64, or fewer (to 4) where that would leave waves of the
-    // chip without work -- below four groups a compute unit; at eight times
-    // that size smaller groups lose (100,000 sets: 0.14 ms in groups of 64, 0.23
-    // in groups of 16, whose transposes are as many each)
+    // sets of a group: 64, or fewer (to 4) where that would leave half of the
+    // chip's places for workgroups without one (100,000 sets: 0.14 ms in groups of
+    // 64, 0.23 in groups of 16, whose transposes are as many each)
     uint32_t tq = 64;
-    while (tq > 4 && n < (uint64_t)h->n_cu * 4 * tq) tq >>= 1;
+    const uint64_t places = (uint64_t)h->n_cu * (16 / group_shape(h, n, tq, 8, 8).waves);
+    while (tq > 4 && n <= places * tq / 2) tq >>= 1;
     const GroupShape g = group_shape(h, n, tq, 8, 8);
     if (g.groups > 0x7FFFFFFFu) return fail(RAMBO_EINVAL, "rambo_query_term_sets: batch too large");
-    QueryOpts opt{h->resolve, h->early_exit, h->probe_counter, SCHED_SWEEP, nullptr, h->d_emptyq};
+    const uint32_t mwaves = (uint32_t)std::min<size_t>(g.waves, (h->lds_max - 64 - tbytes) / mbytes);
+    const size_t lds = tbytes + mwaves * mbytes;
     const dim3 grid(g.groups, g.slices), block(64 * g.waves);
     if (h->RW == 1)
-        hipLaunchKernelGGL(k_sets_group<1>, grid, block, g.lds, s, ix, terms, offs, n, out, opt, h->d_invalid, 0u, tq);
+        hipLaunchKernelGGL(k_sets_group<1>, grid, block, lds, s, ix, terms, offs, n, out, opt, h->d_invalid, 0u, tq, mwaves);
     else if (h->RW == 2)
-        hipLaunchKernelGGL(k_sets_group<2>, grid, block, g.lds, s, ix, terms, offs, n, out, opt, h->d_invalid, 0u, tq);
+        hipLaunchKernelGGL(k_sets_group<2>, grid, block, lds, s, ix, terms, offs, n, out, opt, h->d_invalid, 0u, tq, mwaves);
     else
-        hipLaunchKernelGGL(k_sets_group<4>, grid, block, g.lds, s, ix, terms, offs, n, out, opt, h->d_invalid,
-                           h->log2RW - 2, tq);
+        hipLaunchKernelGGL(k_sets_group<4>, grid, block, lds, s, ix, terms, offs, n, out, opt, h->d_invalid,
+                           h->log2RW - 2, tq, mwaves);
     HIP_CHECK(hipGetLastError());
-    return RAMBO_OK;
+    return launch_sets_long(h, terms, offs, n, out, s, opt, tq);
 }
 
 }  // namespace rambo
