@@ -345,6 +345,20 @@ __global__ __launch_bounds__(256) void k_terms_lane(TermIndex ix, const uint64_t
 #pragma unroll
         for (int s = 0; s < SEG; s++) acc[0].w[s] = 0;
     }
+    const uint32_t nq = (uint32_t)min<uint64_t>(64, n - base);
+    bool live = go;
+#pragma unroll
+    for (int r = 2; r < MAXR; r++)
+        if (r < (int)ix.R) live = live && some(r);
+    if (__ballot(live) == 0) {
+        // no document for any of the terms (one k-mer that no document holds,
+        // K=10,000: 23 us through the resolve, 21 without)
+        const uint32_t words = ((ix.W + 15) / 16 + gridDim.y - 1) / gridDim.y * 16;
+        const uint32_t w0 = min(ix.W, blockIdx.y * words), w1 = min(ix.W, w0 + words);
+        for (uint32_t q = 0; q < nq; q++)
+            for (uint32_t w = w0 + lane; w < w1; w += 64) out[(base + q) * ix.W + w] = 0;
+        return;
+    }
     const uint32_t nb = t_blocks(ix.B);
 #pragma unroll
     for (int r = 0; r < MAXR; r++) {
@@ -359,7 +373,7 @@ __global__ __launch_bounds__(256) void k_terms_lane(TermIndex ix, const uint64_t
     }
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
-    resolve_group<16>(ix, T, out, base, (uint32_t)min<uint64_t>(64, n - base), 0, 1, lane, tp, Slice{blockIdx.y, gridDim.y});
+    resolve_group<16>(ix, T, out, base, nq, 0, 1, lane, tp, Slice{blockIdx.y, gridDim.y});
 }
 
 // Wider rows: G = 2^lg lanes share a term's row (4 words each) and a workgroup
