@@ -402,8 +402,8 @@ typedef struct {
     int seg;          /* 32-bit row words one lane reads: 1, 2 or 4 (row split
                          over row_words / seg lanes) */
     int tile;         /* windows per work item, a multiple of 64; at most: a batch
-                         too small to keep the chip busy with items that long
-                         is cut into shorter ones */
+                         that leaves too few windows to probe to keep the chip
+                         busy with items that long is cut into shorter ones */
     int waves_per_cu; /* resident waves per compute unit of the persistent grid */
     int wpb;          /* waves per workgroup: 1, 2 or 4 */
     int grab;         /* work items taken per queue access */

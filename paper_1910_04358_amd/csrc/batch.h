@@ -16,6 +16,9 @@ struct BatchBufs {
     uint32_t *order;           // [4][cap] reads by size class of their first tile
     unsigned long long *cls;   // reads of size class v at cls[16 v]
     unsigned long long *head;  // queue position
+    unsigned long long *work;  // windows of the reads that the scout pass leaves, in 16 parts (part v at
+                               // work[16 v]); zero between batches
+    uint32_t *tile;            // windows per work item of this batch
     uint32_t *smask;           // [cap][RW] repetition-0 AND over the scout windows (SCHED_PRESCOUT)
     uint32_t *live;            // [cap] bit 0: read not ended by the scout pass; bit 1: a scout
                                // window was valid (SCHED_PRESCOUT)

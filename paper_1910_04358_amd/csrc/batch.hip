@@ -36,10 +36,31 @@ namespace rambo {
 // (the four class counters are 128 bytes apart: their atomics use different
 // cache lines)
 // A direct launch's header (own): written by its first kernel.
+constexpr uint32_t kWorkParts = 16;
 __global__ void k_batch_reset(BatchBufs bb, InputHdr val, InputHdr *own) {
     if (threadIdx.x == 0) *bb.head = 0;
     if (threadIdx.x == 0 && own) *own = val;
     if (threadIdx.x < 4) bb.cls[16 * threadIdx.x] = 0;
+    if (threadIdx.x < kWorkParts) bb.work[16 * threadIdx.x] = 0;
+}
+
+// Windows per work item: `most`, the tuned tile, or fewer where the batch's items
+// would then be too few to keep the chip busy, down to `least` -- a tile takes about
+// as long as G (lanes that split a row) times its windows. What counts are the
+// windows that are left to probe: those of the reads that the scout pass has not
+// ended (without one, of all reads). Best tiles of 64 .. 2,048 measured, reads of
+// which 4 % (K=101,000, G=8) and 25 % (K=10,000, G=1) are left: G=1 512 at 500 to
+// 8,000 reads, 1,024 at 30,000, 2,048 at 100,000; G=8 64 at 64 to 8,000 reads, 128
+// at 30,000, 256 at 100,000, 512 at 300,000: 1,500 items, at least 512 / G windows
+// each. (By the number of reads alone, 8,000 reads of 10 kbp that all live came in
+// 1.2 million items of 64: 21.4 ms at K=101,000, 19.6 with tiles of 1,024.)
+// left: the windows in this lane's part. All 64 lanes; the same in every wave.
+__device__ __forceinline__ uint32_t batch_tile(uint64_t left, uint32_t least, uint32_t most) {
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) left += __shfl_xor(left, d);
+    uint32_t t = least;
+    while (t < most && 2 * (uint64_t)t <= left / 1500) t *= 2;
+    return min(t, most);
 }
 
 // With a scout pass before it (prescout), reads that pass ended are
@@ -55,27 +76,42 @@ __global__ void k_batch_reset(BatchBufs bb, InputHdr val, InputHdr *own) {
 // neither the reset nor the scan's launches (1,999 reads: 24 us in five
 // launches, now one of 7).
 template <uint32_t kPrepReads, uint32_t kThreads, bool kOne>
-__global__ __launch_bounds__(kThreads) void k_batch_prep(const InputHdr *in, uint32_t mw, uint32_t rw, uint32_t tile,
-                                                         BatchBufs bb, int prescout, uint64_t *__restrict__ part) {
+__global__ __launch_bounds__(kThreads) void k_batch_prep(const InputHdr *in, uint32_t mw, uint32_t rw, uint32_t least,
+                                                         uint32_t most, BatchBufs bb, int prescout,
+                                                         uint64_t *__restrict__ part) {
     constexpr uint32_t kWaves = kThreads / 64;
-    const uint64_t n = in->n;
-    const uint64_t *__restrict__ offs = in->offs;
+    const InputHdr hd = *in;
+    const uint64_t n = hd.n;
+    const uint64_t *__restrict__ offs = hd.offs;
     const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     bool real[kPrepReads];
     uint32_t cls[kPrepReads];
-    uint64_t extra[kPrepReads];
+    uint64_t extra[kPrepReads], nws[kPrepReads];
+    // (every load before the first use)
+    uint64_t left = 0;
+    if (prescout) left = lane < kWorkParts ? bb.work[16 * lane] : 0;
+    else if (lane == 0 && n) left = offs[n] - offs[0];
+#pragma unroll
+    for (uint32_t k = 0; k < kPrepReads; k++) {
+        const uint64_t i = ((uint64_t)blockIdx.x * kPrepReads + k) * kThreads + threadIdx.x;
+        real[k] = i < n;
+        nws[k] = 0;
+        if (real[k]) {
+            const uint64_t beg = offs[i], end = offs[i + 1];
+            const uint32_t live = prescout ? bb.live[i] : 1u;
+            nws[k] = n_windows(beg, end);
+            real[k] = live & 1u;
+        }
+    }
+    const uint32_t tile = batch_tile(left, least, most);
+    if (blockIdx.x == 0 && threadIdx.x == 0) *bb.tile = tile;
 #pragma unroll
     for (uint32_t k = 0; k < kPrepReads; k++) {
         const uint64_t i0 = ((uint64_t)blockIdx.x * kPrepReads + k) * kThreads, i = i0 + threadIdx.x;
-        real[k] = i < n;
         cls[k] = 0;
         extra[k] = 0;
-        if (real[k] && prescout && !(bb.live[i] & 1u)) {
-            real[k] = false;
-        } else if (real[k]) {
-            const uint64_t beg = offs[i], end = offs[i + 1];
-            const uint64_t nw = n_windows(beg, end > beg ? end : beg);
-            const uint64_t tiles = nw ? (nw + tile - 1) / tile : 1;
+        if (real[k]) {
+            const uint64_t nw = nws[k], tiles = nw ? (nw + tile - 1) / tile : 1;
             extra[k] = tiles - 1;
             cls[k] = (uint32_t)min<uint64_t>(3, min<uint64_t>(nw, tile) * 4 / tile);
         }
@@ -219,8 +255,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu((NARROW && 
     const uint64_t gmask = (GS >= 64) ? ~0ULL : (((1ULL << GS) - 1) << (lane - sub));  // the group's lanes
     constexpr uint32_t GPB = 256 / GS;  // groups per workgroup
     const uint64_t stride = (uint64_t)gridDim.x * GPB;
-    __shared__ unsigned long long blk_issued;
-    if (threadIdx.x == 0) blk_issued = 0;
+    __shared__ unsigned long long blk_issued, blk_left;
+    if (threadIdx.x == 0) blk_issued = blk_left = 0;
     // (the queue that is built next starts empty)
     if (blockIdx.x == 0 && threadIdx.x == 0) *bb.head = 0;
     if (blockIdx.x == 0 && threadIdx.x < 4) bb.cls[16 * threadIdx.x] = 0;
@@ -329,6 +365,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu((NARROW && 
 #pragma unroll
                 for (int s = 0; s < SEG; s++) bb.smask[i * ix.RW + seg * SEG + s] = acc.w[s];
             if (sub == 0) bb.live[i] = (live ? 1u : 0u) | (saw ? 2u : 0u);
+            if (live && sub == 0) atomicAdd(&blk_left, (unsigned long long)nw);
             if (!live) {
                 if (opt.counts) {
                     if (sub == 0) opt.counts[i] = 0;
@@ -354,11 +391,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu((NARROW && 
         }
         __builtin_amdgcn_s_waitcnt(0);
     }
-    // one counter update per workgroup (same-address atomics serialise)
-    if (opt.probes) {
-        if (lane == 0 && issued) atomicAdd(&blk_issued, (unsigned long long)issued);
-        __syncthreads();
-        if (threadIdx.x == 0 && blk_issued) atomicAdd(opt.probes, blk_issued * ix.eta);
+    // one counter update per workgroup (same-address atomics serialise), and the
+    // windows left spread over several
+    if (opt.probes && lane == 0 && issued) atomicAdd(&blk_issued, (unsigned long long)issued);
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        if (blk_left) atomicAdd(bb.work + 16 * (blockIdx.x % kWorkParts), blk_left);
+        if (opt.probes && blk_issued) atomicAdd(opt.probes, blk_issued * ix.eta);
     }
 }
 
@@ -416,8 +455,7 @@ __device__ __forceinline__ bool read_dead(const Index &ix, const uint32_t *rm, u
 // (2 waves per SIMD); 3 waves fit without spilling.
 template <int SEG, int G>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(G == 1 ? 1 : 3))) void k_batch_main(Index ix, const InputHdr *in, uint64_t *__restrict__ out,
-                                                    BatchBufs bb, QueryOpts opt, int use_res, uint32_t tile,
-                                                    uint32_t grab) {
+                                                    BatchBufs bb, QueryOpts opt, int use_res, uint32_t grab) {
     const uint8_t *__restrict__ seqs = in->seqs;
     const uint64_t *__restrict__ offs = in->offs;
     extern __shared__ __align__(16) uint64_t smem64[];
@@ -430,6 +468,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(G == 1 ? 1 
     uint8_t *stage = nullptr;
 
     const uint64_t n = in->n;
+    const uint32_t tile = __builtin_amdgcn_readfirstlane(*bb.tile);
+    // (read by the queue's kernels, which have ended: zero for the next batch)
+    if (blockIdx.x == 0 && threadIdx.x < kWorkParts) bb.work[16 * threadIdx.x] = 0;
     const uint64_t n_extra = bb.extra_off[n];
     const uint64_t c3 = uniform64(bb.cls[48]), c2 = uniform64(bb.cls[32]), c1 = uniform64(bb.cls[16]);
     const uint64_t total = c3 + c2 + c1 + uniform64(bb.cls[0]) + n_extra;  // queued reads and extra tiles
@@ -546,20 +587,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(G == 1 ? 1 
 }
 
 
-// Windows per work item: the tuned tile, or fewer where a batch of cap reads
-// would leave the chip waiting for its last items -- a tile takes about as long
-// as G (lanes that split a row) times its windows, the batch as long as its
-// reads. Best tiles of 64 .. 2,048 measured: G=1 512 at 500 to 8,000 reads,
-// 1,024 at 30,000, 2,048 at 100,000; G=8 64 at 64 to 8,000 reads, 128 at 30,000,
-// 256 at 100,000, 512 at 300,000 (2,000 reads at K=10,000: 111 us with 512,
-// 135 with 1,024; 8,000 at K=101,000: 147 with 64, 239 with 1,024).
-static uint32_t batch_tile(const rambo_s *h, const Tune &tu, uint64_t cap) {
-    const uint64_t G = std::max<uint64_t>(1, h->RW / (uint32_t)tu.seg);
-    uint64_t t = std::max<uint64_t>(64, 512 / G);
-    while (2 * t <= cap / (48 * G)) t *= 2;
-    return (uint32_t)std::min<uint64_t>(t, (uint64_t)tu.tile);
-}
-
 // Resident workgroups per compute unit of a kernel at a launch shape, asked of
 // the runtime once per shape.
 template <class F>
@@ -633,10 +660,11 @@ static int enqueue_prep(rambo_s *h, const Tune &tu, BatchGraph &bg, uint64_t n, 
             HIP_CHECK(hipGetLastError());
         }
     }
-    const uint32_t tile = batch_tile(h, tu, n);
+    const uint32_t most = (uint32_t)tu.tile;
+    const uint32_t least = std::min(most, std::max<uint32_t>(64, 512 / (uint32_t)std::max(1, (int)h->RW / tu.seg)));
     if (one) {
-        hipLaunchKernelGGL((k_batch_prep<2, 1024, true>), dim3(1), dim3(1024), 0, s, bg.in, mw, h->RW, tile, bg.bb,
-                           pre ? 1 : 0, bg.parts);
+        hipLaunchKernelGGL((k_batch_prep<2, 1024, true>), dim3(1), dim3(1024), 0, s, bg.in, mw, h->RW, least, most,
+                           bg.bb, pre ? 1 : 0, bg.parts);
         HIP_CHECK(hipGetLastError());
         return RAMBO_OK;
     }
@@ -645,18 +673,17 @@ static int enqueue_prep(rambo_s *h, const Tune &tu, BatchGraph &bg, uint64_t n, 
     const uint32_t per = (n + 255) / 256 > 8 * (uint64_t)h->n_cu ? 4 : 1;
     const dim3 grid((unsigned)((n + 256 * per - 1) / (256 * per)));
     if (per == 4)
-        hipLaunchKernelGGL((k_batch_prep<4, 256, false>), grid, dim3(256), 0, s, bg.in, mw, h->RW, tile, bg.bb,
-                           pre ? 1 : 0, bg.parts);
+        hipLaunchKernelGGL((k_batch_prep<4, 256, false>), grid, dim3(256), 0, s, bg.in, mw, h->RW, least, most,
+                           bg.bb, pre ? 1 : 0, bg.parts);
     else
-        hipLaunchKernelGGL((k_batch_prep<1, 256, false>), grid, dim3(256), 0, s, bg.in, mw, h->RW, tile, bg.bb,
-                           pre ? 1 : 0, bg.parts);
+        hipLaunchKernelGGL((k_batch_prep<1, 256, false>), grid, dim3(256), 0, s, bg.in, mw, h->RW, least, most,
+                           bg.bb, pre ? 1 : 0, bg.parts);
     HIP_CHECK(hipGetLastError());
     // the header's first field is the number of reads
     return launch_scan_parts(bg.bb.extra, &bg.in->n, n, bg.bb.extra_off, bg.parts, per, s);
 }
 
-static int enqueue_main(rambo_s *h, const Tune &tu, BatchGraph &bg, uint64_t n, uint64_t *out, hipStream_t s,
-                        const IdsOut &io) {
+static int enqueue_main(rambo_s *h, const Tune &tu, BatchGraph &bg, uint64_t *out, hipStream_t s, const IdsOut &io) {
     const Index ix = make_index(h);
     const uint32_t mw = h->R * h->RW;
     const int G = (int)h->RW / tu.seg;
@@ -676,7 +703,7 @@ static int enqueue_main(rambo_s *h, const Tune &tu, BatchGraph &bg, uint64_t n, 
         const int per_cu = std::max(1, std::min(fit, tu.waves_per_cu / tu.wpb));                         \
         bg.blocks = (unsigned)(h->n_cu * per_cu);                                                          \
         hipLaunchKernelGGL((k_batch_main<SEG, G>), dim3(bg.blocks), dim3(64 * tu.wpb), lds, s, ix, bg.in, out,  \
-                           bg.bb, opt, use_res, batch_tile(h, tu, n), (uint32_t)tu.grab);                  \
+                           bg.bb, opt, use_res, (uint32_t)tu.grab);                  \
     }
     RAMBO_DISPATCH_SPLIT(tu.seg, G)
 #undef RAMBO_SPLIT_BODY_
@@ -709,6 +736,9 @@ static int capture(rambo_s *h, hipGraph_t *g, hipGraphExec_t *exec, const std::f
     return RAMBO_OK;
 }
 
+// Queue position, class counters, work left and tile: a 128-byte line each.
+constexpr size_t kHeadBytes = 128 * (1 + 4 + kWorkParts + 1);
+
 // Queue state for up to cap reads; without an external header, one of its own.
 static int alloc_state(rambo_s *h, BatchGraph &bg, uint64_t cap, bool batch_bufs, const InputHdr *in_dev) {
     const size_t mw = (size_t)h->R * h->RW;
@@ -724,7 +754,7 @@ static int alloc_state(rambo_s *h, BatchGraph &bg, uint64_t cap, bool batch_bufs
         b_parts = al(scan_parts_needed(cap, 1) * 8);
         b_order = al(4 * cap * 4);
     }
-    const size_t total = b_mask + b_done + b_extra + b_off + b_parts + b_order + b_smask + b_live + 640 + 256;
+    const size_t total = b_mask + b_done + b_extra + b_off + b_parts + b_order + b_smask + b_live + kHeadBytes + 256;
     if (hipMalloc(&bg.mem, total) != hipSuccess) {
         (void)hipGetLastError();
         bg.mem = nullptr;
@@ -741,7 +771,9 @@ static int alloc_state(rambo_s *h, BatchGraph &bg, uint64_t cap, bool batch_bufs
     bg.bb.order = (uint32_t *)p; p += b_order;
     bg.bb.head = (unsigned long long *)p;  // its own 128-byte line (every wave's queue atomic)
     bg.bb.cls = bg.bb.head + 16;           // class v at cls[16 v]: the next four lines
-    p += 640;
+    bg.bb.work = bg.bb.cls + 4 * 16;       // part v at work[16 v]
+    bg.bb.tile = (uint32_t *)(bg.bb.work + kWorkParts * 16);
+    p += kHeadBytes;
     bg.bb.cap = cap;
     bg.cap = cap;
     bg.own = in_dev ? nullptr : (InputHdr *)p;
@@ -760,12 +792,16 @@ int make_batch_graph(rambo_s *h, const Tune &tu, const InputHdr *in_dev, uint64_
     bg->tune = tu;
     std::lock_guard<std::mutex> g(h->mu);
     int st = alloc_state(h, *bg, cap, true, in_dev);
+    if (st != RAMBO_OK) return st;
+    hipLaunchKernelGGL(k_batch_reset, dim3(1), dim3(64), 0, h->aux, bg->bb, InputHdr{}, (InputHdr *)nullptr);
+    HIP_CHECK(hipGetLastError());
+    HIP_CHECK(hipStreamSynchronize(h->aux));
     if (st == RAMBO_OK)
         st = capture(h, &bg->graph_prep, &bg->exec_prep,
                      [&](hipStream_t s) { return enqueue_prep(h, tu, *bg, cap, nullptr, out, IdsOut(), s); });
     if (st == RAMBO_OK)
         st = capture(h, &bg->graph_main, &bg->exec_main,
-                     [&](hipStream_t s) { return enqueue_main(h, tu, *bg, cap, out, s, IdsOut()); });
+                     [&](hipStream_t s) { return enqueue_main(h, tu, *bg, out, s, IdsOut()); });
     if (st != RAMBO_OK) return st;
     res = bg;
     return RAMBO_OK;
@@ -845,10 +881,14 @@ static int run_batch(rambo_s *h, const Tune &tu, const uint8_t *seqs, const uint
     if (st != RAMBO_OK) return st;
     const InputHdr val{n, offs, seqs, 0};
     HIP_CHECK(hipEventRecord(bg->ev[0], s));
+    if (!bg->used) {
+        hipLaunchKernelGGL(k_batch_reset, dim3(1), dim3(64), 0, s, bg->bb, val, (InputHdr *)nullptr);
+        HIP_CHECK(hipGetLastError());
+    }
     st = enqueue_prep(h, tu, *bg, n, &val, out, io, s);
     if (st == RAMBO_OK) {
         HIP_CHECK(hipEventRecord(bg->ev[1], s));
-        st = enqueue_main(h, tu, *bg, n, out, s, io);
+        st = enqueue_main(h, tu, *bg, out, s, io);
     }
     HIP_CHECK(hipEventRecord(bg->ev[2], s));
     bg->stream = s;
@@ -939,6 +979,13 @@ static int time_candidate(rambo_s *h, const Tune &tu, const uint8_t *seqs, const
     return st;
 }
 
+// Windows per item of the last batch (which has ended).
+static int last_tile(rambo_s *h, uint32_t *tile) {
+    std::lock_guard<std::mutex> g(h->mu);
+    HIP_CHECK(hipMemcpy(tile, h->last_graph->bb.tile, sizeof *tile, hipMemcpyDeviceToHost));
+    return RAMBO_OK;
+}
+
 int autotune(rambo_s *h, const uint8_t *seqs, const uint64_t *offs, uint64_t n, uint64_t *out, hipStream_t s) {
     Tune best = h->tune;
     best.seg = default_seg(h->RW);
@@ -967,9 +1014,14 @@ int autotune(rambo_s *h, const uint8_t *seqs, const uint64_t *offs, uint64_t n, 
     // two rounds of coordinate search (the second revisits every axis from
     // the first round's shape); a candidate must beat the best by 2 %
     for (int round = 0; round < 2; round++) {
+        int cut = 1 << 30;  // the tile that the batch's larger ones are cut to, once seen
         for (int tile : {128, 256, 512, 1024, 2048, 4096}) {
             Tune t = best; t.tile = tile;
-            if (t.tile != best.tile && (st = consider(t))) return st;
+            if (std::min(t.tile, cut) == std::min(best.tile, cut)) continue;
+            if ((st = consider(t))) return st;
+            uint32_t ran = 0;
+            if ((st = last_tile(h, &ran))) return st;
+            if ((int)ran < t.tile) cut = (int)ran;
         }
         for (int wpc : {8, 12, 16, 20, 24, 32}) {
             Tune t = best; t.waves_per_cu = wpc;
