@@ -25,6 +25,13 @@ struct BatchBufs {
     uint64_t cap;
 };
 
+// Events of a direct launch: before prep, before main, after main. Kept apart from
+// the state, which other calls may take while rambo_last_batch_ms still asks for them.
+struct BatchEvents {
+    hipEvent_t e[3] = {nullptr, nullptr, nullptr};
+    ~BatchEvents();
+};
+
 // Work-queue state for batches of up to cap reads, with the captured graphs of
 // the server's slots (prep: scout pass and queue; absent for the plain form) or,
 // for the query entry point, without any: its launches are direct. The batch is
@@ -41,10 +48,9 @@ struct BatchGraph {
     void *mem = nullptr;
     hipGraph_t graph_prep = nullptr, graph_main = nullptr;
     hipGraphExec_t exec_prep = nullptr, exec_main = nullptr;
-    bool timed = false;
-    hipEvent_t ev[3] = {nullptr, nullptr, nullptr};  // before prep, before main, after main
-    hipStream_t stream = nullptr;                    // of the last direct launch
-    bool used = false;                               // there was one
+    std::shared_ptr<BatchEvents> ev;  // of the last direct launch
+    hipStream_t stream = nullptr;     // its stream
+    bool used = false;                // there was one
     ~BatchGraph();
 };
 

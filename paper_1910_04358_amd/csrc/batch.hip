@@ -711,9 +711,19 @@ static int enqueue_main(rambo_s *h, const Tune &tu, BatchGraph &bg, uint64_t *ou
     return RAMBO_OK;
 }
 
+BatchEvents::~BatchEvents() {
+    for (auto &x : e)
+        if (x) (void)hipEventDestroy(x);
+}
+
+static int make_events(std::shared_ptr<BatchEvents> &res) {
+    auto ev = std::make_shared<BatchEvents>();
+    for (auto &x : ev->e) HIP_CHECK(hipEventCreate(&x));
+    res = ev;
+    return RAMBO_OK;
+}
+
 BatchGraph::~BatchGraph() {
-    for (auto &e : ev)
-        if (e) (void)hipEventDestroy(e);
     if (exec_prep) (void)hipGraphExecDestroy(exec_prep);
     if (exec_main) (void)hipGraphExecDestroy(exec_main);
     if (graph_prep) (void)hipGraphDestroy(graph_prep);
@@ -780,10 +790,7 @@ static int alloc_state(rambo_s *h, BatchGraph &bg, uint64_t cap, bool batch_bufs
     bg.in = in_dev ? in_dev : bg.own;
     // launches of the query entry point are timed (rambo_last_batch_ms); the
     // server's graphs are not (three fewer operations per batch)
-    bg.timed = in_dev == nullptr;
-    if (bg.timed)
-        for (auto &e : bg.ev) HIP_CHECK(hipEventCreate(&e));
-    return RAMBO_OK;
+    return in_dev ? RAMBO_OK : make_events(bg.ev);
 }
 
 int make_batch_graph(rambo_s *h, const Tune &tu, const InputHdr *in_dev, uint64_t cap, uint64_t *out,
@@ -835,7 +842,7 @@ int launch_batch_graph(rambo_s *h, BatchGraph &bg, hipStream_t s) {
 constexpr size_t kPool = 16;
 static int take_state(rambo_s *h, uint64_t n, hipStream_t s, std::shared_ptr<BatchGraph> &res) {
     auto &pool = h->batch_pool;
-    auto ended = [](const BatchGraph &b) { return hipEventQuery(b.ev[2]) == hipSuccess; };
+    auto ended = [](const BatchGraph &b) { return hipEventQuery(b.ev->e[2]) == hipSuccess; };
     size_t best = pool.size();
     for (size_t k = 0; k < pool.size(); k++)
         if (pool[k]->cap >= n && (best == pool.size() || pool[k]->cap < pool[best]->cap) &&
@@ -858,7 +865,7 @@ static int take_state(rambo_s *h, uint64_t n, hipStream_t s, std::shared_ptr<Bat
             for (size_t k = 1; k < pool.size(); k++)
                 if (pool[k]->cap > pool[best]->cap) best = k;
             if (pool[best]->cap < n) {
-                HIP_CHECK(hipEventSynchronize(pool[best]->ev[2]));
+                HIP_CHECK(hipEventSynchronize(pool[best]->ev->e[2]));
                 auto bg = std::make_shared<BatchGraph>();
                 const int st = alloc_state(h, *bg, n, true, nullptr);
                 if (st != RAMBO_OK) return st;
@@ -868,7 +875,7 @@ static int take_state(rambo_s *h, uint64_t n, hipStream_t s, std::shared_ptr<Bat
     }
     (void)hipGetLastError();
     res = pool[best];
-    if (res->used) HIP_CHECK(hipStreamWaitEvent(s, res->ev[2], 0));
+    if (res->used) HIP_CHECK(hipStreamWaitEvent(s, res->ev->e[2], 0));
     return RAMBO_OK;
 }
 
@@ -879,21 +886,27 @@ static int run_batch(rambo_s *h, const Tune &tu, const uint8_t *seqs, const uint
     std::shared_ptr<BatchGraph> bg;
     int st = take_state(h, n, s, bg);
     if (st != RAMBO_OK) return st;
+    // (the last batched call keeps its times)
+    if (!note && h->last_ev == bg->ev && (st = make_events(bg->ev)) != RAMBO_OK) return st;
     const InputHdr val{n, offs, seqs, 0};
-    HIP_CHECK(hipEventRecord(bg->ev[0], s));
+    const hipEvent_t *ev = bg->ev->e;
+    HIP_CHECK(hipEventRecord(ev[0], s));
     if (!bg->used) {
         hipLaunchKernelGGL(k_batch_reset, dim3(1), dim3(64), 0, s, bg->bb, val, (InputHdr *)nullptr);
         HIP_CHECK(hipGetLastError());
     }
     st = enqueue_prep(h, tu, *bg, n, &val, out, io, s);
     if (st == RAMBO_OK) {
-        HIP_CHECK(hipEventRecord(bg->ev[1], s));
+        HIP_CHECK(hipEventRecord(ev[1], s));
         st = enqueue_main(h, tu, *bg, out, s, io);
     }
-    HIP_CHECK(hipEventRecord(bg->ev[2], s));
+    HIP_CHECK(hipEventRecord(ev[2], s));
     bg->stream = s;
     bg->used = true;
-    if (st == RAMBO_OK && note) h->last_graph = bg;
+    if (st == RAMBO_OK && note) {
+        h->last_graph = bg;
+        h->last_ev = bg->ev;
+    }
     return st;
 }
 
@@ -901,6 +914,7 @@ void drop_graphs(rambo_s *h) {
     h->batch_pool.clear();
     h->resident.clear();
     h->last_graph.reset();
+    h->last_ev.reset();
 }
 
 // ---------------------------------------------------------------------------
@@ -1105,15 +1119,20 @@ RAMBO_API int rambo_autotune(rambo_t *h, const uint8_t *seqs, const uint64_t *of
 
 RAMBO_API int rambo_last_batch_ms(rambo_t *h, float *graph_ms, float *kernel_ms) {
     if (!h || !graph_ms || !kernel_ms) return fail(RAMBO_EINVAL, "rambo_last_batch_ms: null argument");
-    std::shared_ptr<BatchGraph> bg;
+    std::shared_ptr<BatchEvents> ev;
     {
         std::lock_guard<std::mutex> g(h->mu);
-        bg = h->last_graph;
+        ev = h->last_ev;
     }
-    if (!bg || !bg->timed) return fail(RAMBO_EINVAL, "rambo_last_batch_ms: no batched launch yet");
-    HIP_CHECK(hipEventSynchronize(bg->ev[2]));
-    HIP_CHECK(hipEventElapsedTime(graph_ms, bg->ev[0], bg->ev[2]));
-    HIP_CHECK(hipEventElapsedTime(kernel_ms, bg->ev[1], bg->ev[2]));
+    if (!ev) return fail(RAMBO_EINVAL, "rambo_last_batch_ms: no batched launch yet");
+    HIP_CHECK(hipEventSynchronize(ev->e[2]));
+    // (read under the lock: another thread's batch may have taken the state and its
+    // events meanwhile; then it is the most recent one, and waited for)
+    std::lock_guard<std::mutex> g(h->mu);
+    if (h->last_ev) ev = h->last_ev;
+    HIP_CHECK(hipEventSynchronize(ev->e[2]));
+    HIP_CHECK(hipEventElapsedTime(graph_ms, ev->e[0], ev->e[2]));
+    HIP_CHECK(hipEventElapsedTime(kernel_ms, ev->e[1], ev->e[2]));
     return RAMBO_OK;
 }
 

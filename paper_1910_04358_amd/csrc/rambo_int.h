@@ -48,7 +48,8 @@ struct Tune {
     int sched = 2;        // probe schedule of a read's windows (SCHED_*; 2 = scout)
 };
 
-struct BatchGraph;  // batched-form state for one set of buffers (batch.hip)
+struct BatchGraph;   // batched-form state (batch.h)
+struct BatchEvents;  // the times of a batch
 
 }  // namespace rambo
 
@@ -100,7 +101,8 @@ struct rambo_s {
     std::mutex mu;              // guards the batched form's states and tuner
     std::vector<std::shared_ptr<rambo::BatchGraph>> batch_pool;  // queue states of the query entry point
     std::map<uint64_t, int> resident;               // workgroups a compute unit holds, by kernel and shape
-    std::shared_ptr<rambo::BatchGraph> last_graph;  // most recently launched
+    std::shared_ptr<rambo::BatchGraph> last_graph;  // of the last batched call
+    std::shared_ptr<rambo::BatchEvents> last_ev;    // its events
 };
 
 namespace rambo {
