@@ -451,6 +451,7 @@ RAMBO_API int rambo_query_term_sets(rambo_t *h, const uint64_t *terms, const uin
 RAMBO_API int rambo_query_seqs_ids(rambo_t *h, const uint8_t *seqs, const uint64_t *offsets, uint64_t n,
                                    uint64_t *scratch, uint32_t *ids, uint64_t *id_offsets, uint64_t ids_cap,
                                    void *stream) {
+    clear_ids_total();
     if (!h) return fail(RAMBO_EINVAL, "rambo_query_seqs_ids: null handle");
     if (!id_offsets) return fail(RAMBO_EINVAL, "rambo_query_seqs_ids: null id_offsets");
     if (h->opaque) return fail(RAMBO_EINVAL, "rambo_query_seqs_ids: the index holds opaque terms, not 31-mers");

@@ -60,6 +60,7 @@ using namespace rambo;
 RAMBO_API int rambo_query_seqs_ids_noalloc(rambo_t *h, const uint8_t *seqs, const uint64_t *offsets, uint64_t n,
                                            uint64_t *bits, uint32_t *ids, uint64_t *id_offsets, uint64_t ids_cap,
                                            void *stream) {
+    clear_ids_total();
     if (!h) return fail(RAMBO_EINVAL, "rambo_query_seqs_ids_noalloc: null handle");
     if (!id_offsets) return fail(RAMBO_EINVAL, "rambo_query_seqs_ids_noalloc: null id_offsets");
     if (h->opaque)

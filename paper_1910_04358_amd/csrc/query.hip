@@ -373,12 +373,12 @@ static constexpr uint64_t kSmallIds = 2048;
 
 // total of this thread's last id-list call
 static thread_local uint64_t g_ids_total = 0;
+void clear_ids_total() { g_ids_total = 0; }
 
 int launch_ids(rambo_s *h, const uint64_t *bits, uint64_t n, uint32_t *ids, uint64_t *id_off, uint64_t ids_cap,
                hipStream_t s, const IdsOut &io, uint64_t *aux, uint64_t *host) {
     const uint32_t W = (uint32_t)h->W;
     uint64_t total = 0;
-    g_ids_total = 0;
     if (n == 0) {
         HIP_CHECK(hipMemsetAsync(id_off, 0, 8, s));
         HIP_CHECK(hipStreamSynchronize(s));

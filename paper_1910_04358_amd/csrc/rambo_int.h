@@ -174,6 +174,8 @@ int launch_query_seqs_plain(rambo_s *h, const uint8_t *seqs, const uint64_t *off
 // without a term reach the host through it, and io.noterm is left zero for the
 // next call; without, by copies.
 uint64_t ids_aux_words(uint64_t n);
+// rambo_last_ids_total is 0 from here on: first in every id-list call
+void clear_ids_total();
 int launch_ids(rambo_s *h, const uint64_t *bits, uint64_t n, uint32_t *ids, uint64_t *id_off, uint64_t ids_cap,
                hipStream_t s, const IdsOut &io, uint64_t *aux, uint64_t *host);
 // *p = v on stream s (a one-thread kernel: no memset node in captured work)

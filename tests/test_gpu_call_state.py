@@ -35,3 +35,37 @@ def test_batch_times_are_of_the_last_batched_call():
     assert again != times and again[0] < times[0]
     torch.cuda.synchronize()
     idx.close()
+
+
+def test_ids_total_of_a_rejected_call_is_zero():
+    import ctypes
+    import torch
+    idx, ((seqs, offs),) = index_and_reads((300,))
+    total = rb.lib().rambo_last_ids_total
+    ids, off = idx.query_seqs_ids(seqs, offs, ids_cap=70 * 300, check=False)
+    assert ids.numel() == total() > 0
+    with pytest.raises(rb.RamboError):  # too small: the total is known
+        idx.query_seqs_ids(seqs, offs, ids_cap=1, check=False)
+    assert total() == ids.numel()
+    scratch = torch.empty((300, idx.W), dtype=torch.int64, device="cuda")
+    p = [ctypes.c_void_p(t.data_ptr()) for t in (seqs, offs, scratch, ids, off)]
+    lib = rb.lib()
+    for call in (lib.rambo_query_seqs_ids, lib.rambo_query_seqs_ids_noalloc):
+        def good():
+            call(idx._h, p[0], p[1], 300, p[2], p[3], p[4], ids.numel(), None)
+            assert total() == ids.numel()
+        good()
+        assert call(None, p[0], p[1], 300, p[2], p[3], p[4], ids.numel(), None) == rb.EINVAL
+        assert total() == 0
+        good()
+        assert call(idx._h, None, p[1], 300, p[2], p[3], p[4], ids.numel(), None) == rb.EINVAL
+        assert total() == 0
+        good()
+        assert call(idx._h, p[0], p[1], 300, p[2], p[3], None, ids.numel(), None) == rb.EINVAL
+        assert total() == 0
+    good()
+    terms = rb.Rambo(10, 4, 1, 64, 1, 1, opaque_terms=True)
+    assert lib.rambo_query_seqs_ids(terms._h, p[0], p[1], 300, p[2], p[3], p[4], 0, None) == rb.EINVAL
+    assert total() == 0
+    terms.close()
+    idx.close()
