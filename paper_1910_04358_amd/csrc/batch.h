@@ -51,6 +51,7 @@ struct BatchGraph {
     std::shared_ptr<BatchEvents> ev;  // of the last direct launch
     hipStream_t stream = nullptr;     // its stream
     bool used = false;                // there was one
+    uint64_t turn = 0;                // its place in the order of the handle's launches
     ~BatchGraph();
 };
 

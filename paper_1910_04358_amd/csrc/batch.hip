@@ -837,8 +837,9 @@ int launch_batch_graph(rambo_s *h, BatchGraph &bg, hipStream_t s) {
 // Queue state for a call of n reads on stream s, from the handle's pool: one
 // whose last call was on s (the new call follows it) or has ended, of the fewest
 // reads that hold n; otherwise a new one, up to kPool of them (the ended ones
-// that are too small are freed first); otherwise the one that has waited
-// longest, which s then waits for. Called with h->mu held.
+// that are too small are freed first); otherwise, of those that hold n, the one
+// whose call was launched first, which s then waits for (or, if none does, the
+// first launched of all, replaced by a larger one). Called with h->mu held.
 constexpr size_t kPool = 16;
 static int take_state(rambo_s *h, uint64_t n, hipStream_t s, std::shared_ptr<BatchGraph> &res) {
     auto &pool = h->batch_pool;
@@ -862,8 +863,10 @@ static int take_state(rambo_s *h, uint64_t n, hipStream_t s, std::shared_ptr<Bat
             best = pool.size() - 1;
         } else {
             best = 0;
-            for (size_t k = 1; k < pool.size(); k++)
-                if (pool[k]->cap > pool[best]->cap) best = k;
+            for (size_t k = 1; k < pool.size(); k++) {
+                const bool fits = pool[k]->cap >= n, had = pool[best]->cap >= n;
+                if (fits != had ? fits : pool[k]->turn < pool[best]->turn) best = k;
+            }
             if (pool[best]->cap < n) {
                 HIP_CHECK(hipEventSynchronize(pool[best]->ev->e[2]));
                 auto bg = std::make_shared<BatchGraph>();
@@ -903,6 +906,7 @@ static int run_batch(rambo_s *h, const Tune &tu, const uint8_t *seqs, const uint
     HIP_CHECK(hipEventRecord(ev[2], s));
     bg->stream = s;
     bg->used = true;
+    bg->turn = ++h->batch_turns;
     if (st == RAMBO_OK && note) {
         h->last_graph = bg;
         h->last_ev = bg->ev;

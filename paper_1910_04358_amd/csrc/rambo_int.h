@@ -100,6 +100,7 @@ struct rambo_s {
     hipStream_t aux = nullptr;  // internal stream (graph capture, sync helpers)
     std::mutex mu;              // guards the batched form's states and tuner
     std::vector<std::shared_ptr<rambo::BatchGraph>> batch_pool;  // queue states of the query entry point
+    uint64_t batch_turns = 0;                       // direct batch launches so far
     std::map<uint64_t, int> resident;               // workgroups a compute unit holds, by kernel and shape
     std::shared_ptr<rambo::BatchGraph> last_graph;  // of the last batched call
     std::shared_ptr<rambo::BatchEvents> last_ev;    // its events

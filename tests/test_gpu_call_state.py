@@ -69,3 +69,33 @@ def test_ids_total_of_a_rejected_call_is_zero():
     assert total() == 0
     terms.close()
     idx.close()
+
+
+def test_more_streams_than_queue_states():
+    """Batches of changing sizes on 20 streams, all in flight at once: the calls past
+    the 16th wait for states that others hold."""
+    import torch
+    sizes = (30_000, 5_000, 12_000, 60_000)
+    idx, sets = index_and_reads(sizes)
+    idx.set_mode(rb.MODE_PLAIN)
+    want = []
+    for seqs, offs in sets:  # (in calls of 1,000, which take no queue)
+        n = offs.numel() - 1
+        out = torch.empty((n, idx.W), dtype=torch.int64, device="cuda")
+        for i in range(0, n, 1_000):
+            idx.query_seqs(seqs, offs[i:min(n, i + 1_000) + 1], out=out[i:i + 1_000], check=False)
+        want.append(out)
+    idx.set_mode(rb.MODE_BATCHED)
+    idx.set_tune(rb.Tune(4, 1024, 16, 4, 1, 2))
+    streams = [torch.cuda.Stream() for _ in range(20)]
+    outs = []
+    torch.cuda.synchronize()
+    for rep in range(3):
+        for j, st in enumerate(streams):
+            k = (j + rep) % 4
+            out = torch.empty_like(want[k])
+            out.record_stream(st)
+            outs.append((k, idx.query_seqs(*sets[k], out=out, stream=st, check=False)))
+    torch.cuda.synchronize()
+    assert all(torch.equal(o, want[k]) for k, o in outs)
+    idx.close()
