@@ -38,9 +38,14 @@
  *    queries that hold no term (RAMBO_OK_EMPTYQ, not an error).
  *  - Queries may run concurrently on one handle. Insertions and queries must
  *    be ordered by the caller; a query that overlaps an insertion is
- *    unsupported. Batched-form queries take their work-queue state from the
- *    handle (up to 16 states, of the size of the batches met, kept until it is
- *    destroyed or folded): calls that overlap in time take different ones.
+ *    unsupported. Batched-form queries, and plain-form ones of thousands of
+ *    reads, take their work-queue state from the handle (up to 16 states, of the
+ *    size of the batches met; about 44 bytes and, for each 32-bit word of a row,
+ *    4 (R + 1) bytes a read): calls that overlap in time take different ones.
+ *  - What a handle keeps for later calls (those states, and the scratch of bulk
+ *    insertions, see rambo_insert_seqs) is freed when the handle is folded or
+ *    destroyed, or when memory for another call on it is short; a plain-form
+ *    query or an insertion that finds none does without.
  */
 #ifndef RAMBO_H
 #define RAMBO_H
@@ -282,9 +287,9 @@ int rambo_insert_seqs(rambo_t *h, const uint64_t *doc_ids, const uint8_t *seqs,
  * cells 0 .. B/2-1 in every repetition, leaving an index of B/2 cells with the
  * same R, m and hash functions (a document's cell becomes phi_r(d) mod B/2),
  * the same as building with B/2 cells directly. B must be even. Smaller and
- * faster, with a higher false-positive rate. Allocates the folded rows before
- * freeing the old ones (needs the folded size free), synchronous; resets the
- * batched form's launch shape. */
+ * faster, with a higher false-positive rate. Frees what the handle keeps for
+ * later calls, and allocates the folded rows before freeing the old ones (needs
+ * the folded size free), synchronous; resets the batched form's launch shape. */
 int rambo_fold(rambo_t *h);
 
 /* ---------------------------------------------------------------------- */

@@ -66,6 +66,27 @@ static void derive_hashes(rambo_s *h) {
     }
 }
 
+void give_back(rambo_s *h, bool locked) {
+    free_parts(h);
+    std::unique_lock<std::mutex> g(h->mu, std::defer_lock);
+    if (!locked) g.lock();
+    drop_ended_states(h);
+}
+
+hipError_t device_alloc(rambo_s *h, void **p, size_t bytes) {
+    hipError_t e = hipMalloc(p, bytes);
+    if (e != hipSuccess) {
+        (void)hipGetLastError();
+        give_back(h);
+        e = hipMalloc(p, bytes);
+    }
+    if (e != hipSuccess) {
+        (void)hipGetLastError();
+        *p = nullptr;
+    }
+    return e;
+}
+
 static void free_device(rambo_s *h) {
     if (h->rows) (void)hipFree(h->rows);
     if (h->d_hp) (void)hipFree(h->d_hp);
@@ -282,7 +303,7 @@ RAMBO_API int rambo_dump_bfu(rambo_t *h, uint32_t r, uint32_t b, uint64_t *out) 
     if (!h || !out || r >= h->R || b >= h->B) return fail(RAMBO_EINVAL, "rambo_dump_bfu: bad argument");
     const uint64_t words = (h->m + 63) / 64;
     uint64_t *d = nullptr;
-    HIP_CHECK(hipMalloc(&d, words * 8));
+    HIP_CHECK(device_alloc(h, (void **)&d, words * 8));
     int st = launch_dump_bfu(h, r, b, d, h->aux);
     if (st == RAMBO_OK && hipStreamSynchronize(h->aux) != hipSuccess) st = fail(RAMBO_EDEVICE, "rambo_dump_bfu: kernel failed");
     if (st == RAMBO_OK && hipMemcpy(out, d, words * 8, hipMemcpyDeviceToHost) != hipSuccess)
@@ -300,6 +321,7 @@ RAMBO_API int rambo_fold(rambo_t *h) {
     while (rw < need) { rw <<= 1; lg++; }
     const uint64_t bytes = (uint64_t)h->R * h->m * rw * 4;
     uint32_t *nrows = nullptr;
+    give_back(h);  // (all work has ended: everything kept for later calls)
     if (hipMalloc(&nrows, bytes) != hipSuccess) {
         (void)hipGetLastError();
         return fail(RAMBO_ENOMEM, "rambo_fold: cannot allocate %llu bytes for the folded index",
@@ -358,7 +380,7 @@ RAMBO_API int rambo_insert(rambo_t *h, uint64_t doc_id, const uint64_t *kmers, u
             return fail(RAMBO_EINVAL, "rambo_insert: value %llu at %llu is not a 31-mer code",
                         (unsigned long long)kmers[i], (unsigned long long)i);
     uint64_t *d = nullptr;
-    HIP_CHECK(hipMalloc(&d, n * 8 + 3 * 8));
+    HIP_CHECK(device_alloc(h, (void **)&d, n * 8 + 3 * 8));
     const uint64_t meta[3] = {doc_id, 0, n};  // doc_ids[1], offsets[2]
     int st = RAMBO_OK;
     if (hipMemcpyAsync(d, kmers, n * 8, hipMemcpyHostToDevice, h->aux) != hipSuccess ||
@@ -411,9 +433,18 @@ RAMBO_API int rambo_query_kmers(rambo_t *h, const uint64_t *kmers, uint64_t n, u
     // host arrays: synchronous copy in, query, copy out
     const hipStream_t s = h->aux;
     uint64_t *dk = nullptr, *dout = nullptr;
-    HIP_CHECK(hipMallocAsync((void **)&dk, n * 8, s));
+    auto alloc = [&](uint64_t **p, uint64_t bytes) {
+        hipError_t e = hipMallocAsync((void **)p, bytes, s);
+        if (e != hipSuccess) {
+            (void)hipGetLastError();
+            give_back(h);
+            e = hipMallocAsync((void **)p, bytes, s);
+        }
+        return e;
+    };
+    HIP_CHECK(alloc(&dk, n * 8));
     int st = RAMBO_OK;
-    if (hipMallocAsync((void **)&dout, n * h->W * 8, s) != hipSuccess) {
+    if (alloc(&dout, n * h->W * 8) != hipSuccess) {
         (void)hipGetLastError();
         dout = nullptr;
         st = fail(RAMBO_ENOMEM, "rambo_query_kmers: cannot allocate %llu result bytes on the device",
@@ -468,9 +499,9 @@ RAMBO_API int rambo_query_seqs_ids(rambo_t *h, const uint8_t *seqs, const uint64
         h->d_ids_wm = nullptr;
         h->d_ids_aux = nullptr;
         h->ids_counts_cap = 0;
-        HIP_CHECK(hipMalloc(&h->d_ids_counts, n * 8));
-        HIP_CHECK(hipMalloc(&h->d_ids_wm, n * ((h->W + 63) / 64) * 8));
-        HIP_CHECK(hipMalloc(&h->d_ids_aux, ids_aux_words(n) * 8));
+        HIP_CHECK(device_alloc(h, (void **)&h->d_ids_counts, n * 8));
+        HIP_CHECK(device_alloc(h, (void **)&h->d_ids_wm, n * ((h->W + 63) / 64) * 8));
+        HIP_CHECK(device_alloc(h, (void **)&h->d_ids_aux, ids_aux_words(n) * 8));
         h->ids_counts_cap = n;
     }
     if (!h->ids_host && hipHostMalloc((void **)&h->ids_host, 16) != hipSuccess) {

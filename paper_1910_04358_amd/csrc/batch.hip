@@ -855,13 +855,8 @@ static int take_state(rambo_s *h, uint64_t n, hipStream_t s, std::shared_ptr<Bat
             if (pool[k]->cap < n && ended(*pool[k])) pool.erase(pool.begin() + k);
             else k++;
         (void)hipGetLastError();
-        if (pool.size() < kPool) {
-            auto bg = std::make_shared<BatchGraph>();
-            const int st = alloc_state(h, *bg, std::max<uint64_t>(n, 4096), true, nullptr);
-            if (st != RAMBO_OK) return st;
-            pool.push_back(bg);
-            best = pool.size() - 1;
-        } else {
+        uint64_t cap = std::max<uint64_t>(n, 4096);
+        if (pool.size() >= kPool) {
             best = 0;
             for (size_t k = 1; k < pool.size(); k++) {
                 const bool fits = pool[k]->cap >= n, had = pool[best]->cap >= n;
@@ -869,11 +864,22 @@ static int take_state(rambo_s *h, uint64_t n, hipStream_t s, std::shared_ptr<Bat
             }
             if (pool[best]->cap < n) {
                 HIP_CHECK(hipEventSynchronize(pool[best]->ev->e[2]));
-                auto bg = std::make_shared<BatchGraph>();
-                const int st = alloc_state(h, *bg, n, true, nullptr);
-                if (st != RAMBO_OK) return st;
-                pool[best] = bg;
+                pool.erase(pool.begin() + best);
+                best = pool.size();
+                cap = n;
             }
+        }
+        if (pool.size() < kPool) {
+            auto bg = std::make_shared<BatchGraph>();
+            int st = alloc_state(h, *bg, cap, true, nullptr);
+            if (st == RAMBO_ENOMEM) {
+                give_back(h, true);
+                bg = std::make_shared<BatchGraph>();
+                st = alloc_state(h, *bg, n, true, nullptr);
+            }
+            if (st != RAMBO_OK) return st;
+            pool.push_back(bg);
+            best = pool.size() - 1;
         }
     }
     (void)hipGetLastError();
@@ -912,6 +918,15 @@ static int run_batch(rambo_s *h, const Tune &tu, const uint8_t *seqs, const uint
         h->last_ev = bg->ev;
     }
     return st;
+}
+
+void drop_ended_states(rambo_s *h) {
+    auto &pool = h->batch_pool;
+    for (size_t k = 0; k < pool.size();)
+        if (hipEventQuery(pool[k]->ev->e[2]) == hipSuccess) pool.erase(pool.begin() + k);
+        else k++;
+    (void)hipGetLastError();  // (a query that found work still running)
+    h->last_graph.reset();
 }
 
 void drop_graphs(rambo_s *h) {
@@ -1000,6 +1015,8 @@ static int time_candidate(rambo_s *h, const Tune &tu, const uint8_t *seqs, const
 // Windows per item of the last batch (which has ended).
 static int last_tile(rambo_s *h, uint32_t *tile) {
     std::lock_guard<std::mutex> g(h->mu);
+    *tile = ~0u;
+    if (!h->last_graph) return RAMBO_OK;
     HIP_CHECK(hipMemcpy(tile, h->last_graph->bb.tile, sizeof *tile, hipMemcpyDeviceToHost));
     return RAMBO_OK;
 }

@@ -409,6 +409,15 @@ static uint64_t bytes_from(const void *p) {
     return (uint64_t)((const char *)base + size - (const char *)p);
 }
 
+void free_parts(rambo_s *h) {
+    std::lock_guard<std::mutex> g(h->parts_mu);
+    if (!h->d_parts) return;
+    if (h->parts_done) (void)hipEventSynchronize(h->parts_done);
+    (void)hipFree(h->d_parts);
+    h->d_parts = nullptr;
+    h->parts_bytes = 0;
+}
+
 // Positions that an insertion of n_docs documents is taken to hold, where the
 // buffer does not say: the index's K documents fill its filters to three quarters
 // at most (2 m ln 2 / eta terms a filter, B of them for the K documents), or 2^17

@@ -144,7 +144,15 @@ struct QueryOpts {
 rambo_s *create_index(uint64_t K, uint32_t B, uint32_t R, uint64_t m, uint32_t eta, uint64_t seed, uint32_t flags,
                       const uint64_t *gids);
 
+// Device memory for the handle's own use, like hipMalloc; if there is none, once more
+// after give_back. The error state is left clear.
+hipError_t device_alloc(rambo_s *h, void **p, size_t bytes);
+// Frees what the handle keeps for later calls: the insertions' scratch and the
+// queue states of batches that have ended. With locked, h->mu is held.
+void give_back(rambo_s *h, bool locked = false);
+
 // build.hip
+void free_parts(rambo_s *h);  // the insertions' scratch
 // (positions: k-mers of all the documents where the caller knows, else 0)
 int launch_build_kmers(rambo_s *h, const uint64_t *kmers, const uint64_t *koff, const uint64_t *doc_ids,
                        uint64_t n_docs, hipStream_t s, uint64_t positions = 0);
@@ -188,6 +196,7 @@ int query_seqs_batched(rambo_s *h, const uint8_t *seqs, const uint64_t *offs, ui
 int query_seqs_plain(rambo_s *h, const uint8_t *seqs, const uint64_t *offs, uint64_t n, uint64_t *out, hipStream_t s,
                      const IdsOut &io = IdsOut());
 void drop_graphs(rambo_s *h);
+void drop_ended_states(rambo_s *h);  // h->mu held
 
 // Row split: a lane reads SEG words of a row, G = row_words / SEG lanes share
 // one term. The instantiated (SEG, G) pairs:

@@ -416,8 +416,8 @@ static int setup_slot(rambo_server_s *s, Slot &sl) {
     HIP_CHECK(hipEventCreateWithFlags(&sl.done, hipEventDisableTiming));
     HIP_CHECK(hipHostMalloc((void **)&sl.h_stage, stage, hipHostMallocDefault));
     HIP_CHECK(hipHostMalloc((void **)&sl.h_out, R * h->W * 8, hipHostMallocDefault));
-    HIP_CHECK(hipMalloc(&sl.d_stage, stage));
-    HIP_CHECK(hipMalloc(&sl.d_out, R * h->W * 8));
+    HIP_CHECK(device_alloc(h, (void **)&sl.d_stage, stage));
+    HIP_CHECK(device_alloc(h, (void **)&sl.d_out, R * h->W * 8));
     HIP_CHECK(hipHostGetDevicePointer((void **)&sl.hd_stage, sl.h_stage, 0));
     HIP_CHECK(hipHostGetDevicePointer((void **)&sl.hd_out, sl.h_out, 0));
     if (s->cfg.policy == RAMBO_SERVE_CONTINUOUS) {

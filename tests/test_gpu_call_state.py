@@ -99,3 +99,36 @@ def test_more_streams_than_queue_states():
     torch.cuda.synchronize()
     assert all(torch.equal(o, want[k]) for k, o in outs)
     idx.close()
+
+
+def test_fold_gives_back_what_calls_kept():
+    """The scratch of a bulk insertion and the queue states of batches do not stand in
+    the way of the folded rows."""
+    import torch
+    from tests.gpu_util import to_dev
+
+    def free_bytes():
+        torch.cuda.synchronize()
+        return torch.cuda.mem_get_info()[0]
+
+    K, B, R, m, eta, L, n = 150, 64, 2, 1 << 21, 3, 80_000, 300_000
+    docs = torch.randint(0, 4, (K * L,), device="cuda", dtype=torch.uint8)
+    docs = torch.tensor(list(b"ACGT"), dtype=torch.uint8, device="cuda")[docs.to(torch.int64)]
+    ids = to_dev(np.arange(K, dtype=np.uint64))
+    off = to_dev(np.arange(K + 1, dtype=np.uint64) * np.uint64(L))
+    roff = to_dev(np.arange(n + 1, dtype=np.uint64) * np.uint64(31))
+    out = torch.empty((n, 3), dtype=torch.int64, device="cuda")
+    for _ in range(2):  # (the first loads the kernels)
+        idx = rb.Rambo(K, B, R, m, eta, 9101)
+        fresh = free_bytes()
+        idx.insert_seqs(ids, docs, off)
+        idx.query_seqs(docs, roff, out=out, check=False)
+        want = out.clone()
+        kept = fresh - free_bytes()
+        idx.fold()
+        rows = R * m * 4  # (64 cells of two words to 32 of one)
+        left = fresh + rows - free_bytes()
+        assert torch.equal(idx.query_seqs(docs, roff, check=False) & want, want)
+        idx.close()
+    assert kept > 100 << 20, kept
+    assert left < 8 << 20, (kept, left)
