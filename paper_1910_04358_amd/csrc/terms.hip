@@ -1016,22 +1016,28 @@ int launch_query_kmers(rambo_s *h, const uint64_t *kmers, uint64_t n, uint64_t *
         if (h->RW == 1) hipLaunchKernelGGL(k_terms_lane<1>, grid, block, lds, s, ix, kmers, n, out, h->d_invalid);
         else if (h->RW == 2) hipLaunchKernelGGL(k_terms_lane<2>, grid, block, lds, s, ix, kmers, n, out, h->d_invalid);
         else hipLaunchKernelGGL(k_terms_lane<4>, grid, block, lds, s, ix, kmers, n, out, h->d_invalid);
-    } else {
-        // where a T of 64 terms would take more than half the LDS, and so leave one
-        // workgroup a compute unit, groups of 32 (0.64 -> 0.55 ms, see the kernel);
-        // elsewhere they would only read the documents' cells twice as often
-        const bool half = t_words(h->R, h->B) * 8 > h->lds_max / 2;
-        const GroupShape g = group_shape(h, n, half ? 32 : 64, 16, half ? 4 : 8);
-        if (g.groups > 0x7FFFFFFFu) return fail(RAMBO_EINVAL, "rambo_query_kmers: batch too large");
+        HIP_CHECK(hipGetLastError());
+        return RAMBO_OK;
+    }
+    // where a T of 64 terms would take more than half the LDS, and so leave one
+    // workgroup a compute unit, groups of 32 (0.64 -> 0.55 ms, see the kernel);
+    // elsewhere they would only read the documents' cells twice as often
+    const bool half = t_words(h->R, h->B) * 8 > h->lds_max / 2;
+    const uint32_t tq = half ? 32 : 64;
+    // (a launch has fewer than 2^32 threads: 4 to 16 of them a term)
+    const uint64_t most = 0xFFFFFFFFull / (64 * 16) * tq;
+    for (uint64_t at = 0; at < n; at += most) {
+        const uint64_t m = std::min(n - at, most);
+        const GroupShape g = group_shape(h, m, tq, 16, half ? 4 : 8);
         const dim3 grid(g.groups, g.slices), block(64 * g.waves);
         if (half)
-            hipLaunchKernelGGL(k_terms_group<uint32_t>, grid, block, g.lds, s, ix, kmers, n, out, h->d_invalid,
-                               h->log2RW - 2);
+            hipLaunchKernelGGL(k_terms_group<uint32_t>, grid, block, g.lds, s, ix, kmers + at, m, out + at * h->W,
+                               h->d_invalid, h->log2RW - 2);
         else
-            hipLaunchKernelGGL(k_terms_group<uint64_t>, grid, block, g.lds, s, ix, kmers, n, out, h->d_invalid,
-                               h->log2RW - 2);
+            hipLaunchKernelGGL(k_terms_group<uint64_t>, grid, block, g.lds, s, ix, kmers + at, m, out + at * h->W,
+                               h->d_invalid, h->log2RW - 2);
+        HIP_CHECK(hipGetLastError());
     }
-    HIP_CHECK(hipGetLastError());
     return RAMBO_OK;
 }
 
