@@ -66,3 +66,29 @@ def test_items_follow_the_windows_left(B):
         assert torch.equal(idx.query_seqs(dev[k][0], dev[k][1], check=False), want[k]), k
     idx.sync()
     idx.close()
+
+
+@pytest.mark.parametrize("B,n", [(100, 2_048), (100, 4_097), (100, 600_000), (300, 70_000)])
+def test_queues_of_every_size_equal_teams(B, n):
+    import torch
+    K, R, m, eta, seed = 70, 3, 1 << 18, 2, 8980 + B
+    dm = gen.DocModel(seed=B + 29, n_docs=K, length=3_000, docs_per_anc=7, mu_lo=0.01, mu_hi=0.01)
+    idx = rb.Rambo(K, B, R, m, eta, seed)
+    build_gpu_seqs(idx, dm, 0, K)
+    rm = gen.ReadModel(qseed=n, src_lo=0, src_hi=K, len_kind=0, median=90, sigma=0.9, lo=20, hi=2_900, err_lo=0.0,
+                       err_hi=0.003)
+    r = gen.reads(dm, rm, n)
+    seqs, offs = to_dev(r.seqs), to_dev(r.offsets)
+    want = by_teams(idx, seqs, offs, n)
+    assert torch.equal(idx.query_seqs(seqs, offs, check=False), want)
+    idx.set_mode(rb.MODE_BATCHED)
+    for sched in (2, 1):
+        for tile in (64, 2048):
+            t = idx.get_tune()
+            t.seg, t.tile, t.sched = 4, tile, sched
+            idx.set_tune(t)
+            got = torch.full_like(want, -1)
+            idx.query_seqs(seqs, offs, out=got, check=False)
+            assert torch.equal(got, want), (sched, tile)
+    idx.sync()
+    idx.close()
