@@ -292,6 +292,15 @@ def time_steps(fn, steps, warmup):
     return e0.elapsed_time(e1) / steps
 
 
+def plain_by_parts(idx, seqs, offs, out, part=1_000):
+    """The batch's answers in the plain form, in calls small enough for its own
+    kernel (larger ones take the batched launches): the reference of every form."""
+    n = offs.numel() - 1
+    for i in range(0, n, part):
+        idx.query_seqs(seqs, offs[i:min(n, i + part) + 1], out=out[i:i + part], check=False)
+    return out
+
+
 def pipelined_run(idx, seqs, offs, ref, steps, warmup):
     """The same batch passes, consecutive ones alternating between two streams
     (each with its own output buffer and queue state): a batch's scout pass and queue building can run while the
@@ -459,7 +468,9 @@ def main():
     if args.only != "batched":
         idx.set_mode(MODE_PLAIN)
         plain_ms = time_steps(step, args.steps, args.warmup)
-        ref = out.clone()
+        ref = plain_by_parts(idx, seqs, offs, torch.empty_like(out))
+        if not torch.equal(out, ref):
+            raise SystemExit("plain results differ from the plain kernel's on parts of the batch")
         idx.set_probe_counter(probes)
         step()
         torch.cuda.synchronize()
