@@ -62,7 +62,7 @@ __global__ __launch_bounds__(256) void k_query_seqs_plain(Index ix, const uint8_
 // reads at K=10,000: 53 us a call, now 21).
 //
 // With early exit the waves first scout (repetition 0 on 64 windows 31 apart, then
-// on the rest of those) where the parts take several steps, or where the batch's
+// on the rest of those) where the parts take many steps, or where the batch's
 // rows are what it waits for (kTeamScout bases, about 8 us of rows): most reads
 // that no document holds end there. Without, 4,000 reads of 10 kbp with an error
 // in a thousand bases took 789 us at K=101,000, now 60 (55 with one wave per read,
@@ -95,7 +95,7 @@ __global__ __launch_bounds__(1024) void k_query_seqs_team(Index ix, const uint8_
     constexpr uint32_t kGrain = 64 / G;  // terms that the wave's lanes take together
     const uint64_t part = ((nwin + kGrain - 1) / kGrain + waves - 1) / waves * kGrain;  // windows per wave
     const bool ee = opt.early_exit != 0;
-    const bool scouts = ee && nwin > 0 && (part > 64 || offs[n] - offs[0] >= kTeamScout);
+    const bool scouts = ee && nwin > 0 && (part > 128 || offs[n] - offs[0] >= kTeamScout);
     // waves that probe anything
     const uint32_t used = scouts ? waves : part ? (uint32_t)((nwin + part - 1) / part) : 0;
     if (threadIdx.x == 0) issued = kept = 0;
@@ -191,14 +191,16 @@ size_t team_lds(const rambo_s *h, uint32_t waves, bool use_res) {
     return (size_t)waves * wave_lds(h->R * h->RW, h->W, false, false).total * 4 + (use_res ? (size_t)h->W * 8 : 0);
 }
 
-// Waves per read of a batch of n reads (1: the one-wave kernel): a workgroup of
-// 16 waves a compute unit at most, then two of 8, then four a read until one
-// wave per read fills the chip. Times (one call alone, us) at K=10,000 and
-// K=101,000 with 1 wave: 16 reads 57-86 and 24-100, 257 81-110 and 120-140, 512
-// 95-111 and 123-156, 2,000 167-227 and 133-176, 4,000 194-239 and 175-195,
-// 8,000 261-272 and 217-241; with 16 waves at 257 reads 49-60 and 47-52 (4: 55-66
-// and 57-62); with 8 at 512 57-65 and 49-53; with 4 at 2,000 114-135 and 77-85,
-// at 4,000 172-187 and 118-124, at 8,000 293-315 and 197-218.
+// Waves per read of a batch of n reads (1: the one-wave kernel): 16 while every
+// compute unit holds one such workgroup (and a little past that, where a second one
+// waits), then two workgroups of 8, then four a read until one wave per read fills
+// the chip. The lines lie where it makes little difference (whole calls, us, with 16
+// / 8 / 4 waves): K=10,000 (a lane a term) 256 reads 57 / 59 / 57, 288 58 / 59 / 57,
+// 320 58 / 59 / 57, 512 66 / 65 / 62, 768 86 / 79 / 77; K=101,000 (8 lanes a term)
+// 256 reads 45 / 42 / 54, 288 46 / 44 / 55, 512 50 / 47 / 58, 768 57 / 50 / 61. With
+// one wave 16 reads took 57-86 and 24-100, 257 81-110 and 120-140, 2,000 167-227 and
+// 133-176, 8,000 261-272 and 217-241; with 4 2,000 114-135 and 77-85, 8,000 293-315
+// and 197-218.
 uint32_t team_waves(const rambo_s *h, uint64_t n) {
     const uint64_t cu = (uint64_t)h->n_cu;
     uint32_t t = n <= cu + cu / 8 ? 16 : n <= 2 * cu ? 8 : n <= 16 * cu ? 4 : 1;  // (past that only under capture and the like)
