@@ -364,8 +364,8 @@ uint64_t rambo_last_ids_total(void);
  * RAMBO_NOALLOC_MAX_READS + 1 + RAMBO_NOALLOC_MAX_READS / 1024 + 64 uint64
  * words (about 8 MiB), held on each device the library runs on until the
  * process ends. n may be at most RAMBO_NOALLOC_MAX_READS (RAMBO_EINVAL
- * beyond). Always the plain form (one wavefront per read), whatever
- * rambo_set_mode chose. Synchronous on `stream`. Every call on one device
+ * beyond). Always the plain form's own kernels, whatever rambo_set_mode
+ * chose. Synchronous on `stream`. Every call on one device
  * shares that device's array, which keeps the last call's contents: calls
  * from threads of this process are serialised by the library; calls that
  * overlapped on one GPU would race. */

@@ -992,7 +992,7 @@ static int time_candidate(rambo_s *h, const Tune &tu, const uint8_t *seqs, const
     hipEvent_t a, b;
     HIP_CHECK(hipEventCreate(&a));
     HIP_CHECK(hipEventCreate(&b));
-    int st = run_batch(h, tu, seqs, offs, n, out, s);  // warm-up (and graph build)
+    int st = run_batch(h, tu, seqs, offs, n, out, s);  // warm-up (and queue state)
     if (st == RAMBO_OK) st = run_batch(h, tu, seqs, offs, n, out, s);
     float best = 1e30f;
     for (int rep = 0; rep < 5 && st == RAMBO_OK; rep++) {

@@ -259,32 +259,6 @@ __device__ __forceinline__ uint32_t and_across_groups(uint32_t v) {
     }
 }
 
-template <int SEG, int G>
-__device__ __forceinline__ void reduce_groups(Seg<SEG> (&acc)[MAXR], uint32_t R) {
-#pragma unroll
-    for (int r = 0; r < MAXR; r++)
-        if (r < (int)R)
-#pragma unroll
-            for (int s = 0; s < SEG; s++) acc[r].w[s] = and_across_groups<G>(acc[r].w[s]);
-}
-
-// After reduce_groups: is the mask of some repetition empty? (wave-uniform)
-template <int SEG, int G>
-__device__ __forceinline__ bool some_rep_empty(const Seg<SEG> (&acc)[MAXR], uint32_t R) {
-    const uint64_t group0 = (G >= 64) ? ~0ULL : ((1ULL << G) - 1);
-    bool empty = false;
-#pragma unroll
-    for (int r = 0; r < MAXR; r++) {
-        if (r < (int)R) {
-            uint32_t o = 0;
-#pragma unroll
-            for (int s = 0; s < SEG; s++) o |= acc[r].w[s];
-            empty |= (__ballot(o != 0) & group0) == 0;
-        }
-    }
-    return empty;
-}
-
 // Rows of term x in repetitions FIRST .. FIRST+COUNT-1 (those below R), with
 // ETA hash functions each: all loads issued before any is used (so a wave
 // keeps COUNT * ETA row reads in flight), then ANDed into cm -- per
