@@ -757,8 +757,8 @@ __global__ __launch_bounds__(1024) void k_sets_team(Index ix, const uint64_t *__
             if (ee && !alive) break;
         }
         if (opt.probes && lane == 0 && got) atomicAdd(&issued, (unsigned long long)got);
-        __syncthreads();
     }
+    if (live) __syncthreads();
     if (opt.probes && threadIdx.x == 0 && issued) atomicAdd(opt.probes, issued * ix.eta);
     if (live) {
         for (uint32_t w = threadIdx.x; w < mw; w += blockDim.x) {
