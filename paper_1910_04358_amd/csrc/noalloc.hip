@@ -4,7 +4,7 @@
 // in per-handle device buffers that it allocates (and grows) on demand. This
 // variant takes them from one fixed array of the library instead, so a call
 // makes no allocation of any kind: the caller passes the inputs and outputs,
-// the query runs in the plain form (one wave per read, which needs no other
+// the query runs in the plain form's kernels (which need no other
 // scratch), and the answer sizes, the count of reads without a term and the
 // scan's block sums live in `noalloc_scratch`.
 //

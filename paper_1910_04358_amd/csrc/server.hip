@@ -423,7 +423,7 @@ static int setup_slot(rambo_server_s *s, Slot &sl) {
     if (s->cfg.policy == RAMBO_SERVE_CONTINUOUS) {
         Tune large = h->tune;
         if (!h->tuned) large.seg = default_seg(h->RW);
-        // small batches: the plain kernel, one wave per read, on the pinned
+        // small batches: the plain form's kernel for their size, on the pinned
         // areas; large ones: the persistent form with the handle's tuned
         // shape on the device copy
         const uint64_t small_cap = std::min<uint64_t>(R, kZeroCopyMaxReads), mid_cap = std::min<uint64_t>(R, 2048);
