@@ -184,6 +184,7 @@ constexpr uint32_t kGroupAdds = 9;     // bits a thread adds between flushes: ni
 constexpr uint32_t kUnroll = 4;        // positions of a thread whose loads go together
 constexpr uint32_t kTileBits = 20;     // an apply tile, at most: 128 KB of rows
 constexpr uint32_t kBucketBits = 19;   // a bucket, at least
+constexpr uint32_t kApplyGroups = 4096;  // of an apply launch, at most (a multiple of eight: a workgroup's tiles are one XCD's)
 
 // Where a partitioned insertion keeps its bits: segment (b, g) holds those of
 // bucket b that workgroup g found, at most cap of them (a multiple of 16), as
@@ -326,9 +327,8 @@ __global__ __launch_bounds__(1024) void k_part_scatter(Index ix, Docs in, Parts 
 // are many tiles, and by the atomics where there are few: tiles of 128 KB, one
 // workgroup a compute unit, against 64 KB, two: 5 x 10^10 bits at 64 / 128 tiles a
 // bucket, scatter included, 1.10 / 1.53 s; 2.4 x 10^9 at 2 / 4, 14.0 / 14.2 ms.
-// The grid is what is resident and strides over the tiles (a multiple of eight
-// workgroups, so that each stays on its tiles' XCD): with a workgroup a tile a
-// launch that found nothing to do took 130 us at 131,072 tiles.
+// A workgroup a tile up to kApplyGroups, which stride over the tiles then: a
+// launch that finds nothing to do takes 130 us with 131,072 workgroups.
 __global__ __launch_bounds__(1024) void k_part_apply(Index ix, Docs in, Parts pt, uint32_t r, uint32_t pass,
                                                     uint32_t tiles, uint32_t lgt) {
     extern __shared__ __align__(16) uint32_t smem32[];
@@ -501,9 +501,7 @@ static int launch_parts(rambo_s *h, const Docs &in, uint64_t most, hipStream_t s
     const Index ix = make_index(h);
     const size_t lds = (size_t)(kStage + kBuckets * 2) * 4;
     const uint32_t lgt = std::min<uint32_t>(bucket_bits, kTileBits), tiles = 1u << (bucket_bits - lgt);
-    // (64 KB of LDS a workgroup of 512 threads: two a compute unit, else one)
-    const unsigned per_cu = lgt > kBucketBits ? 1 : 2;
-    const unsigned apply = std::min<unsigned>(((pt.buckets + 7) / 8) * 8 * tiles, ((unsigned)h->n_cu * per_cu + 7) / 8 * 8);
+    const unsigned apply = std::min<unsigned>(((pt.buckets + 7) / 8) * 8 * tiles, kApplyGroups);
     const unsigned reps = together ? h->R : 1;
     for (uint64_t c = 0; c < passes; c++)
         for (uint32_t r = 0; r < h->R; r += reps) {
