@@ -184,7 +184,7 @@ constexpr uint32_t kGroupAdds = 9;     // bits a thread adds between flushes: ni
 constexpr uint32_t kUnroll = 4;        // positions of a thread whose loads go together
 constexpr uint32_t kTileBits = 20;     // an apply tile, at most: 128 KB of rows
 constexpr uint32_t kBucketBits = 19;   // a bucket, at least
-constexpr uint32_t kApplyGroups = 4096;  // of an apply launch, at most (a multiple of eight: a workgroup's tiles are one XCD's)
+constexpr uint32_t kApplyGroups = 4096;  // of an apply launch that has one a tile, at most
 
 // Where a partitioned insertion keeps its bits: segment (b, g) holds those of
 // bucket b that workgroup g found, at most cap of them (a multiple of 16), as
@@ -327,8 +327,11 @@ __global__ __launch_bounds__(1024) void k_part_scatter(Index ix, Docs in, Parts 
 // are many tiles, and by the atomics where there are few: tiles of 128 KB, one
 // workgroup a compute unit, against 64 KB, two: 5 x 10^10 bits at 64 / 128 tiles a
 // bucket, scatter included, 1.10 / 1.53 s; 2.4 x 10^9 at 2 / 4, 14.0 / 14.2 ms.
-// A workgroup a tile up to kApplyGroups, which stride over the tiles then: a
-// launch that finds nothing to do takes 130 us with 131,072 workgroups.
+// A workgroup a tile up to kApplyGroups; past that the grid is what is resident and
+// strides over the tiles (a launch that finds nothing to do takes 130 us with
+// 131,072 workgroups; striding costs 2 % of a launch of a few tiles a workgroup).
+// A larger grid that strides would have the resident workgroups leave a bucket
+// before its last tiles (K=101,000, 96 GiB, 128 tiles a bucket: 4.8 s to build, 4.1).
 __global__ __launch_bounds__(1024) void k_part_apply(Index ix, Docs in, Parts pt, uint32_t r, uint32_t pass,
                                                     uint32_t tiles, uint32_t lgt) {
     extern __shared__ __align__(16) uint32_t smem32[];
@@ -501,7 +504,10 @@ static int launch_parts(rambo_s *h, const Docs &in, uint64_t most, hipStream_t s
     const Index ix = make_index(h);
     const size_t lds = (size_t)(kStage + kBuckets * 2) * 4;
     const uint32_t lgt = std::min<uint32_t>(bucket_bits, kTileBits), tiles = 1u << (bucket_bits - lgt);
-    const unsigned apply = std::min<unsigned>(((pt.buckets + 7) / 8) * 8 * tiles, kApplyGroups);
+    // (resident: 64 KB of LDS a workgroup of 512 threads, two a compute unit, else one)
+    const unsigned resident = ((unsigned)h->n_cu * (lgt > kBucketBits ? 1 : 2) + 7) / 8 * 8;
+    unsigned apply = ((pt.buckets + 7) / 8) * 8 * tiles;
+    if (apply > kApplyGroups) apply = resident;
     const unsigned reps = together ? h->R : 1;
     for (uint64_t c = 0; c < passes; c++)
         for (uint32_t r = 0; r < h->R; r += reps) {
